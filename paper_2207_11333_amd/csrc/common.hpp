@@ -117,7 +117,7 @@ struct SegB {
   const void *ptr; // [rows, ld] row-major, k-contiguous, 16-byte aligned rows
   int ld;          // leading dimension (elements; rows 16-byte multiples)
   int k;           // segment length (multiple of the K tile)
-  int boff;        // column offset of this segment inside the B rows
+  int boff;        // column of this segment in the B rows: the sum of the k before it
 };
 struct GemmNTB {
   SegB seg[kMaxSeg];

@@ -16,21 +16,33 @@
 // of that row.  The loads of a tile (A rows, weight rows, BF16 weight low
 // halves) are dealt to the waves in turn, the same number to each.
 //
-// Pipeline: three LDS stages; tiles t + 1 and t + 2 are in flight while tile t
-// computes.  Each wave counts its own DMA loads (vmcnt) and one plain
-// s_barrier per tile (the fence of __syncthreads would wait for every load in
-// flight) makes every wave's loads visible and frees the stage read by the
-// previous tile.  The barrier sits before the tile's last products, which
-// cover the next tile's fragment reads.
+// Pipeline: a ring of NST LDS stages; tiles t + 1 .. t + NST - 1 are in flight
+// while tile t computes.  Each wave counts its own DMA loads (vmcnt) and one
+// plain s_barrier per tile (the fence of __syncthreads would wait for every
+// load in flight) makes every wave's loads visible and frees the stage read
+// by the previous tile.  The barrier sits before the tile's last products,
+// which cover the next tile's fragment reads.
 //
-// Measured: a wave's LDS-DMA loads are served about one at a time, so the copy
-// rate grows with the waves that issue them (a streaming test: four waves per
-// CU about 8 TB/s from L2, sixteen about 25, whatever the number of loads each
-// keeps in flight); every configuration runs eight waves.  Two tile shapes:
-// 128 x 128 (waves of 64 x 32) for grids that fill the GPU, 64 x 64 (waves of
-// 32 x 16) for smaller ones, whose time is set by how many tiles run at once
-// (update linear, BF16, alone: 80 against 105 us for the register-staged
-// kernel at 40k rows; 9.7 against 14.3 us at 4.5k rows with 64 x 64 tiles).
+// What bounds it: a workgroup's K loop is a chain of short steps (64 x 64
+// tiles: 128 to 512 matrix-core cycles a wave and step), so whatever a step
+// does beside its products lengthens every workgroup.  The loads themselves
+// are not the limit (a streaming test: eight waves with two loads each in
+// flight copy 54 bytes a cycle and CU from L2, four waves with four loads as
+// much).  Each lane therefore keeps its load addresses and moves them on by a
+// constant; looking up the segment and forming row addresses for every tile
+// (scalar loads, waits and 64-bit products) cost about as long as the
+// products: with addresses kept, FP32 at 4.5k rows and H = 128 the update
+// linear 22.3 -> 17.7 us, message 10.5 -> 9.5, layer-input gradient
+// 16.5 -> 12.9; BF16 update 10.7 -> 8.9 us; one molecule (29 rows, a single
+// row tile) BF16 update 9.1 -> 7.8 us.  128 x 128 tiles, whose products
+// are longer, gained nothing (105 us BF16 update at 40k rows).
+//
+// Two tile shapes: 128 x 128 (waves of 64 x 32) for grids that fill the GPU,
+// 64 x 64 (waves of 32 x 16) for smaller ones, whose time is set by how many
+// tiles run at once.  Eight waves in both.  Stages: five for the 64 x 64
+// tiles of the forward pass, which run alone; three where another kernel
+// needs LDS on the same CU (the layer-input gradient, beside the weight
+// gradients) and for 128 x 128 (144 KB in BF16).
 //
 // Products and their order per output are those of the register-staged
 // kernel when it runs unsplit (FP32: per 16 k, four k-slots of
@@ -45,7 +57,6 @@ namespace {
 typedef __attribute__((address_space(3))) void lds_t;
 
 constexpr int kQRow = 128; // bytes per LDS row (one K tile)
-constexpr int kQStages = 3;
 constexpr int kQWGM = 2, kQWGN = 4; // waves of a workgroup
 
 // s_waitcnt immediate for vmcnt(n) with lgkmcnt(0) (expcnt left alone)
@@ -53,22 +64,35 @@ template <int N> struct WaitVm {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   static constexpr int value = 0x0070 | (N & 15) | ((N >> 4) << 14);
 };
+// wait until at most n groups of PER loads are in flight (n uniform, <= MAX)
+template <int PER, int MAX> __device__ __forceinline__ void wait_groups(int n) {
+  if constexpr (MAX > 0) {
+    if (n >= MAX) {
+      __builtin_amdgcn_s_waitcnt(WaitVm<PER * MAX>::value);
+      return;
+    }
+    wait_groups<PER, MAX - 1>(n);
+  } else {
+    __builtin_amdgcn_s_waitcnt(WaitVm<0>::value);
+  }
+}
 
 // PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo.
-// BM x BN tile, WGM x WGN waves.
-template <int PREC, int BM, int BN, int WGM, int WGN, int TAG>
+// BM x BN tile, WGM x WGN waves, NST LDS stages.
+template <int PREC, int BM, int BN, int WGM, int WGN, int NST, int TAG>
 __global__ void __launch_bounds__(64 * WGM * WGN, 1)
 k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   using T = typename Prec<PREC>::T;
   constexpr bool SPLIT = PREC == 1;
-  constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  constexpr int BKE = kQRow / (int)sizeof(T); // k per K tile
+  constexpr int ESZ = (int)sizeof(T);
+  constexpr int BKE = kQRow / ESZ; // k per K tile
   constexpr int NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
-  constexpr int IA = BM / 8, IB = BN / 8, IT = IA + IB * (SPLIT ? 2 : 1);
-  static_assert(IT % NW == 0 && TM >= 1 && TN >= 1, "tile shape");
-  constexpr int DMA = IT / NW; // DMA loads per wave per K tile
+  constexpr int IA = BM / 8, IB = BN / 8; // DMA loads (8 rows each) of A and of one B half
+  static_assert(IA % NW == 0 && IB % NW == 0 && TM >= 1 && TN >= 1, "tile shape");
+  constexpr int UA = IA / NW, UB = IB / NW; // per wave
+  constexpr int DMA = UA + UB * (SPLIT ? 2 : 1);
   constexpr int SA = BM * kQRow, SB = BN * kQRow, STAGE = SA + SB * (SPLIT ? 2 : 1);
-  __shared__ __attribute__((aligned(1024))) char smem[kQStages * STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];
 
   const int M = g.M_fixed >= 0 ? g.M_fixed : dims->N;
   int mtiles = (M + BM - 1) / BM;
@@ -88,57 +112,68 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     n0 = (tile % ntiles_n) * BN;
     m0 = mt * BM;
   }
-  const int tid = threadIdx.x, w = tid >> 6, L = tid & 63;
+  const int tid = threadIdx.x, L = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (w / WGN) * WM, wn0 = (w % WGN) * WN;
 
-  // K tiles over the segments: segment q holds tiles [cum[q], cum[q + 1])
-  int cum[kMaxSeg + 1];
-  cum[0] = 0;
-#pragma unroll
-  for (int q = 0; q < kMaxSeg; ++q) cum[q + 1] = cum[q] + (q < g.nseg ? g.seg[q].k / BKE : 0);
-  const int KT = cum[kMaxSeg];
+  int KT = 0;
+  for (int q = 0; q < g.nseg; ++q) KT += g.seg[q].k / BKE;
 
-  // DMA load u of this wave is load w + NW u of the tile: A rows, then weight
-  // rows, then (BF16) weight low halves, 8 rows each.  Rows and columns past
-  // the matrix read clamped (valid) rows, whose products land only in
-  // outputs that are never stored.
+  // This wave's DMA loads of a K tile: UA of A rows, UB of weight rows and
+  // (BF16) UB of weight low halves, 8 rows each; load u of a kind covers rows
+  // 8 (w + NW u) .. of the tile.  Each lane keeps the 64-bit address of its
+  // 16 bytes and moves it on by one K tile per issue, so a tile's loads cost
+  // two additions each; the segment's fields are read only where a segment
+  // begins (the weights' columns run on through the segments).  Rows and
+  // columns past the matrix read clamped (valid) rows, whose products land
+  // only in outputs that are never stored.
   const int dr = L >> 3;
-  const int dk = EPC * ((L & 7) ^ dr); // first k of the chunk this lane loads
-  int rowi[DMA], kind[DMA], ldsoff[DMA];
+  const int db = 16 * ((L & 7) ^ dr); // first byte of the chunk this lane loads
+  const char *pa[UA], *pb[UB], *pl[SPLIT ? UB : 1];
+  int rowa[UA];
 #pragma unroll
-  for (int u = 0; u < DMA; ++u) {
-    const int gi = w + NW * u;
-    if (gi < IA) {
-      kind[u] = 0;
-      const int m = min(m0 + 8 * gi + dr, m_hi - 1);
-      rowi[u] = g.perm ? g.perm[m] : m;
-      ldsoff[u] = 8 * gi * kQRow;
-    } else {
-      const int bi = gi - IA, half = bi / IB, bb = bi - half * IB;
-      kind[u] = 1 + half;
-      rowi[u] = min(n0 + 8 * bb + dr, g.Ncols - 1);
-      ldsoff[u] = SA + half * SB + 8 * bb * kQRow;
-    }
+  for (int u = 0; u < UB; ++u) {
+    const int r = min(n0 + 8 * (w + NW * u) + dr, g.Ncols - 1);
+    const size_t off = (size_t)ESZ * ((size_t)bq * g.bstride + (size_t)r * g.ldb) + db;
+    pb[u] = static_cast<const char *>(g.B) + off;
+    if constexpr (SPLIT) pl[u] = static_cast<const char *>(g.B_lo) + off;
   }
-  const T *Bq = static_cast<const T *>(g.B) + (size_t)bq * g.bstride;
-  const T *Lq = SPLIT ? static_cast<const T *>(g.B_lo) + (size_t)bq * g.bstride : Bq;
-
-  // the loads of K tile t into the stage at byte offset st
-  auto issue = [&](int t, int st) {
-    int q = 0;
 #pragma unroll
-    for (int u = 1; u < kMaxSeg; ++u) q += (t >= cum[u]) ? 1 : 0;
-    const int k0 = (t - cum[q]) * BKE;
-    const T *ap = static_cast<const T *>(g.seg[q].ptr) + k0 + dk;
-    const int lda = g.seg[q].ld;
-    const size_t bo = (size_t)g.seg[q].boff + k0 + dk;
+  for (int u = 0; u < UA; ++u) {
+    const int m = min(m0 + 8 * (w + NW * u) + dr, m_hi - 1);
+    rowa[u] = g.perm ? g.perm[m] : m;
+  }
+  int q = 0, left = 0; // next segment, K tiles left in the current one
+  auto dma = [](const char *src, char *dst) {
+    // the builtin takes a non-const pointer: without the cast the host pass
+    // drops the kernel templates (their launch handles stay undefined)
+    __builtin_amdgcn_global_load_lds((void *)src, (lds_t *)dst, 16, 0, 0);
+  };
+  // the next K tile's loads into the stage at byte offset st
+  auto issue = [&](int st) {
+    if (left == 0) {
+      const char *ap = static_cast<const char *>(g.seg[q].ptr) + db;
+      const int lda = g.seg[q].ld;
+      left = g.seg[q].k / BKE;
+      ++q;
 #pragma unroll
-    for (int u = 0; u < DMA; ++u) {
-      const T *src = kind[u] == 0 ? ap + (size_t)rowi[u] * lda
-                                  : (kind[u] == 1 ? Bq : Lq) + (size_t)rowi[u] * g.ldb + bo;
-      // the builtin takes a non-const pointer: without the cast the host pass
-      // drops the kernel templates (their launch handles stay undefined)
-      __builtin_amdgcn_global_load_lds((void *)src, (lds_t *)(smem + st + ldsoff[u]), 16, 0, 0);
+      for (int u = 0; u < UA; ++u) pa[u] = ap + (size_t)rowa[u] * lda * ESZ;
+    }
+    --left;
+    char *d = smem + st + 8 * kQRow * w;
+#pragma unroll
+    for (int u = 0; u < UA; ++u) {
+      dma(pa[u], d + 8 * kQRow * NW * u);
+      pa[u] += kQRow;
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      dma(pb[u], d + SA + 8 * kQRow * NW * u);
+      pb[u] += kQRow;
+      if constexpr (SPLIT) {
+        dma(pl[u], d + SA + SB + 8 * kQRow * NW * u);
+        pl[u] += kQRow;
+      }
     }
   };
 
@@ -181,10 +216,10 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   auto mm = [&](const V (&a)[TM], const V (&b)[TN]) { mma_frags<PREC, TM, TN>(a, b, acc); };
-  auto next = [](int st) { return st == (kQStages - 1) * STAGE ? 0 : st + STAGE; };
+  auto next = [](int st) { return st == (NST - 1) * STAGE ? 0 : st + STAGE; };
 
   // tile t (register set S, LDS stage st): its first products; then, if a
-  // tile follows, wait for it, refill this stage with tile t + 3 and read
+  // tile follows, wait for it, refill this stage with tile t + NST and read
   // tile t + 1's fragments; then the last products
   auto step = [&](auto set, int t, int st) {
     constexpr int S = decltype(set)::value;
@@ -195,11 +230,10 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     }
     __builtin_amdgcn_sched_barrier(0);
     if (t + 1 < KT) {
-      if (t + 2 < KT) __builtin_amdgcn_s_waitcnt(WaitVm<DMA>::value);
-      else __builtin_amdgcn_s_waitcnt(WaitVm<0>::value);
+      wait_groups<DMA, NST - 2>(KT - 2 - t);
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      if (t + 3 < KT) issue(t + 3, st);
+      if (t + NST < KT) issue(st);
       read(IC<1 - S>{}, next(st));
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -207,12 +241,8 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     else mm(fa[S][1], fb[S][1]);
   };
 
-  issue(0, 0);
-  if (KT > 1) issue(1, STAGE);
-  if (KT > 2) issue(2, 2 * STAGE);
-  if (KT > 2) __builtin_amdgcn_s_waitcnt(WaitVm<2 * DMA>::value);
-  else if (KT > 1) __builtin_amdgcn_s_waitcnt(WaitVm<DMA>::value);
-  else __builtin_amdgcn_s_waitcnt(WaitVm<0>::value);
+  for (int t = 0, st = 0; t < NST && t < KT; ++t, st += STAGE) issue(st);
+  wait_groups<DMA, NST - 1>(KT - 1);
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
   read(IC<0>{}, 0);
@@ -277,6 +307,11 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 
 inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
+// LDS stages (160 KB of LDS per CU; see the head of this file)
+constexpr int stages(int prec, int tile, int tag) {
+  return tile == 64 ? (tag == 4 ? 3 : 5) : 3;
+}
+
 // the large tile when its grid fills every CU at least once
 bool large_tiles(int capM, const GemmNTB &g) {
   return (long long)(cdiv(capM, 128) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, 128) >= 256;
@@ -290,11 +325,12 @@ bool gemm_ntb_ok(const GemmNTB &g, int precision) {
   if ((precision == 1) != (g.B_lo != nullptr) || (precision == 0 && g.Cb)) return false;
   if ((g.ldb * esz) % 16 || !al16(g.B) || (g.B_lo && !al16(g.B_lo))) return false;
   if (g.perm && (!g.brow || g.nb < 1 || (g.bstride * esz) % 16)) return false;
+  int boff = 0; // the segments' weight columns follow one another from 0
   for (int q = 0; q < g.nseg; ++q) {
     const SegB &s = g.seg[q];
-    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esz) % 16 ||
-        (s.boff * esz) % 16)
+    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esz) % 16 || s.boff != boff)
       return false;
+    boff += s.k;
   }
   return true;
 }
@@ -311,8 +347,8 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
   switch (key) {
 #define HGNN_NTB(P, BB, T)                                                                     \
   case P * 1000 + BB * 10 + T:                                                                 \
-    hipExtLaunchKernelGGL(k_gemm_ntb<P, BB, BB, kQWGM, kQWGN, T>, grid, block, 0, s, ev0, ev1,  \
-                          0, dims, g, nt);                                                     \
+    hipExtLaunchKernelGGL((k_gemm_ntb<P, BB, BB, kQWGM, kQWGN, stages(P, BB, T), T>), grid, block, \
+                          0, s, ev0, ev1, 0, dims, g, nt);                                     \
     break;
 #define HGNN_NTB_TAGS(P, BB) HGNN_NTB(P, BB, 0) HGNN_NTB(P, BB, 1) HGNN_NTB(P, BB, 2) HGNN_NTB(P, BB, 4)
     HGNN_NTB_TAGS(0, 64)
