@@ -40,11 +40,9 @@ UPDATE_GEMM_TRAFFIC = ("update_gemm_c1_fp32_traffic.txt",
 SITE_TRAFFIC = {
     "update_gemm": UPDATE_GEMM_TRAFFIC,
     "update_wgrad": ("update_wgrad_c1_fp32_traffic.txt",
-                     ["csrc/gemm_tn.hip", "csrc/mfma_tile.hpp"]),
+                     ["csrc/wgrad.hip", "csrc/mfma_tile.hpp"]),
     "aggregate_bwd": ("aggregate_bwd_c1_fp32_traffic.txt",
                       ["csrc/agg_fused.hip", "csrc/agg_msg.hpp", "csrc/mfma_tile.hpp"]),
-    "message_wgrad": ("message_wgrad_c1_fp32_traffic.txt",
-                      ["csrc/gemm_tn.hip", "csrc/mfma_tile.hpp"]),
     "agg_input_gemm": ("agg_input_gemm_c1_fp32_traffic.txt",
                        ["csrc/gemm_nt.hip", "csrc/mfma_tile.hpp"]),
 }
@@ -77,14 +75,15 @@ def measured_traffic(name, sources):
 # Layers after the first run the message and update linears in the LDS-DMA
 # form (k_gemm_ntb: FP32 on the inputs, BF16 on operand copies), FP32 also the
 # layer-input gradient; the first layer and the other BF16 sites the
-# register-staged kernel.  BF16 weight gradients run k_gemm_tn_tr.
+# register-staged kernel.  Weight gradients launched layer by layer (recomputation,
+# large batches) run k_wgrad in FP32 and k_gemm_tn_tr in BF16.
 SITES = {
     "message_gemm": ("S1 message linear",
                      "k_gemm_nt<P, 64, 128, *, 2, 4, *> | k_gemm_ntb<P, *, *, 2, 4, 2>", "mfma"),
     "aggregate": ("S2 aggregation", "k_aggregate<1>", "hbm"),
     "update_gemm": ("S3 update linear",
                     "k_gemm_nt<P, 64, 128, *, 1, 4, *> | k_gemm_ntb<P, *, *, 2, 4, 1>", "mfma"),
-    "update_wgrad": ("S6 update weight gradient", "k_gemm_tn<P, 64, 64, 1> | k_gemm_tn_tr<1, *>",
+    "update_wgrad": ("S6 update weight gradient", "k_wgrad | k_gemm_tn_tr<1, *>",
                      "mfma"),
     "agg_input_gemm": ("S6 aggregate-input gradient", "k_gemm_nt<P, 64, 128, *, 3, 4, *>", "mfma"),
     # by degree bucket dA is formed inside the adjoint (one fused kernel, dA
@@ -92,7 +91,7 @@ SITES = {
     "aggregate_bwd": ("S6 dA + S7 aggregation adjoint, fused", "k_agg_bwd_fused<P, 1, *>", "hbm"),
     "input_gemm": ("S6+S8 layer-input gradient",
                    "k_gemm_nt<P, 64, 128, *, 4, 4, *> | k_gemm_ntb<0, 64, 64, 2, 4, 4>", "mfma"),
-    "message_wgrad": ("S8 message weight gradient", "k_gemm_tn<P, 64, 64, 2> | k_gemm_tn_tr<2, *>",
+    "message_wgrad": ("S8 message weight gradient", "k_wgrad | k_gemm_tn_tr<2, *>",
                       "mfma"),
 }
 
@@ -144,6 +143,11 @@ def time_sites(m, step, steps, w, N, E, sites=tuple(SITES)):
         work, per_step = site_work(site, w, N, E)
         avg = ms / 1e3 / n
         what, kern, bound = SITES[site]
+        if site == "update_wgrad" and n == steps and w.num_layers > 1:
+            # small batches: every layer's weight gradients in one launch
+            work = w.num_layers * (work + site_work("message_wgrad", w, N, E)[0])
+            per_step = 1
+            what, kern = "S6 + S8 weight gradients, all layers", "k_wgrad_all<P, *>"
         if bound == "hbm":
             ach, peak, unit = work / avg / 1e9, HBM_PEAK_GBS, "GB/s"
         else:

@@ -315,10 +315,13 @@ int hgnn_op_fetch(hgnn_ctx *ctx, int32_t which, int32_t layer, void *dst_dev,
  * weight-gradient GEMM, 5 aggregate-gradient GEMM, 6 aggregation adjoint,
  * 7 input-gradient GEMM, 8 message weight-gradient GEMM (these time the
  * kernel alone, not a split-K reduction after it), 9 the CSR build of a
- * training-path forward (all of its launches).  For GraphSAGE models site 3 is the layer GEMM and
- * 4 its weight gradient; for CGCNN models 2 is the gated aggregation, 4 the
- * layer weight gradient, 6 the aggregation adjoint and 7 the input-gradient
- * GEMM.  Synchronises the device. */
+ * training-path forward (all of its launches).  Where a backward pass forms
+ * the weight gradients of all layers in one launch (contexts of fewer than
+ * 16384 nodes that keep their activations), that launch is site 4 and site 8
+ * has none.  For GraphSAGE models site 3 is the layer GEMM and 4 its weight
+ * gradient; for CGCNN models 2 is the gated aggregation, 4 the layer weight
+ * gradient, 6 the aggregation adjoint and 7 the input-gradient GEMM.
+ * Synchronises the device. */
 int hgnn_timer_start(hgnn_ctx *ctx, int32_t site, int32_t max_launches);
 /* Sum of the bracketed durations (ms) and the number of launches; stops the
  * timer.  Waits for the recorded events. */

@@ -161,16 +161,51 @@ struct GemmTN {
   int Ncols;       // total columns of Yv
   float *P;        // partials [splits (+ nb), M, Ncols]
   int splits;
-  // Degree-bucketed chunks (perm non-null): the node chunks are taken per
-  // bucket over the permuted rows (as in GemmNT), nb more partials than
-  // splits; chunk z writes zscale[2 z] = s+(q), zscale[2 z + 1] = s-(q) of
-  // its bucket q from the scaler table (0, 0 for an empty chunk).
+  // degree-bucketed chunks (perm non-null): see WgJob
   const int *perm;
   const int *brow;
   int nb;
   const float *table;
   float *zscale;
 };
+
+// One weight-gradient product of wgrad.hip: P[z] [M, N + 4] = X^T [Y | 1] over
+// chunk z of the node rows, Y the segments side by side (N columns), column N
+// the sum of X's rows (columns N + 1 .. N + 3 are zero).
+struct WgSeg {
+  const float *ptr; // [rows, ld], 16-byte aligned rows
+  int ld, ncols;    // multiples of 4
+};
+struct WgJob {
+  const float *X; // [rows, ldx], columns m < M
+  int ldx, M;
+  WgSeg seg[2];
+  int nseg, N;
+  float *P;       // partials [splits (+ nb)][M][N + 4]
+  int splits;
+  int zfull;      // chunks that the reduction's order is made for (>= splits + nb)
+  // Chunks of the rows as they lie or, degree-bucketed (perm non-null), per
+  // bucket over the permuted rows (as in GemmNT), nb more partials than
+  // splits; chunk z writes zscale[2 z] = s+(q), zscale[2 z + 1] = s-(q) of
+  // its bucket q from the scaler table (0, 0 for an empty chunk).
+  const int *perm, *brow;
+  int nb;
+  const float *table;
+  float *zscale;
+  int sum_from; // rows of P from here on need only column N (M: none)
+  int rot;      // XCD of chunk 0 (deals the chunks of a list of jobs evenly)
+};
+bool wg_job_ok(const WgJob &j);
+int wg_blocks(const WgJob &j, int tile);
+// One FP32 product by itself.
+hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEvent_t ev0 = nullptr,
+                        hipEvent_t ev1 = nullptr);
+// n products in device memory in one launch (a whole backward pass's): tile is
+// the output tile side, 128 or 64, most the largest wg_blocks(job, tile).
+hipError_t launch_wgrad_all(const Dims *dims, const WgJob *tab, int n, int most, int precision,
+                            int tile, hipStream_t s, hipEvent_t ev0 = nullptr,
+                            hipEvent_t ev1 = nullptr);
+int wg_tile_all(int blocks128, int precision);
 
 // Ordered reduction of the bucketed update weight gradient: P has Z
 // partials of [M = H, Ncols = Fp + 4H + 4] (columns: h block, A block, the
@@ -179,7 +214,7 @@ struct GemmTN {
 struct ReduceUpd {
   const float *P;
   const float *zscale; // [Z][2]
-  int Z, M, Ncols, F, Fp, H;
+  int Z, zfull, M, Ncols, F, Fp, H; // zfull: as in ReduceMap
   float *dWp;          // [H, F + 12H] packed
   float *dbp;          // [H]
 };
@@ -201,7 +236,11 @@ struct ReduceRoute {
 };
 struct ReduceMap {
   const float *P;
-  int splits, M, Ncols;
+  int splits;
+  // the count that fixes the order of the sum (at least splits): chunks from
+  // splits on are absent, as if zero
+  int zfull;
+  int M, Ncols;
   int main_cols, F, Fp;
   // number of leading Fp-wide column blocks padded from F (0 counts as 1):
   // block b, column w < F maps to b F + w; later columns shift by npad (Fp - F)
@@ -254,14 +293,11 @@ hipError_t launch_calib_copy(const float *src, float *dst, long long n, hipStrea
 // Split count launch_gemm_nt will use, and the partial buffer it needs.
 int nt_splits(int capM, int Ncols, int Ktot, int precision);
 size_t nt_partial_floats(int capM, int Ncols, int Ktot, int precision);
-// Grid capacity: g.splits chunks, plus g.nb when bucketed.
 // tag names the launch site in profiles (1 update, 2 message weight gradient)
-hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision,
-                          hipStream_t s, int tag = 0, hipEvent_t ev0 = nullptr,
-                          hipEvent_t ev1 = nullptr);
+hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision, hipStream_t s,
+                          int tag = 0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // reduce.hip
 hipError_t launch_reduce_map(const ReduceMap &r, hipStream_t s);
-hipError_t launch_reduce_upd(const ReduceUpd &r, hipStream_t s);
 // Up to three reductions in one launch (a layer's weight gradients): job k
 // is the ReduceUpd u when upd[k], else m[k]; the launcher fills G and grid.
 // At most one job is a ReduceUpd.
@@ -273,6 +309,16 @@ struct ReduceJobs {
   int G[3], grid[3];
 };
 hipError_t launch_reduce_jobs(ReduceJobs j, hipStream_t s);
+// The reductions of a whole backward pass in one launch, from n jobs in device
+// memory.
+struct ReduceJob {
+  int upd, G, blocks;
+  ReduceUpd u;
+  ReduceMap m;
+};
+// fills G and blocks of the jobs, returns the most blocks of a job
+int reduce_layout(ReduceJob *jobs, int n);
+hipError_t launch_reduce_all(const ReduceJob *tab, int n, int most, hipStream_t s);
 // Column sums of X [dims->N, C] (leading dimension ldx) over Z fixed row
 // chunks into P [Z][C][4] (sum in element 0, zeros after): partials in the
 // layout of a weight-gradient GEMM's sum column, for launch_reduce_map.

@@ -59,24 +59,6 @@ typedef __attribute__((address_space(3))) void lds_t;
 constexpr int kQRow = 128; // bytes per LDS row (one K tile)
 constexpr int kQWGM = 2, kQWGN = 4; // waves of a workgroup
 
-// s_waitcnt immediate for vmcnt(n) with lgkmcnt(0) (expcnt left alone)
-template <int N> struct WaitVm {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  static constexpr int value = 0x0070 | (N & 15) | ((N >> 4) << 14);
-};
-// wait until at most n groups of PER loads are in flight (n uniform, <= MAX)
-template <int PER, int MAX> __device__ __forceinline__ void wait_groups(int n) {
-  if constexpr (MAX > 0) {
-    if (n >= MAX) {
-      __builtin_amdgcn_s_waitcnt(WaitVm<PER * MAX>::value);
-      return;
-    }
-    wait_groups<PER, MAX - 1>(n);
-  } else {
-    __builtin_amdgcn_s_waitcnt(WaitVm<0>::value);
-  }
-}
-
 // PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo.
 // BM x BN tile, WGM x WGN waves, NST LDS stages.
 template <int PREC, int BM, int BN, int WGM, int WGN, int NST, int TAG>

@@ -1,6 +1,8 @@
-// TN-form MFMA GEMM (the weight gradients of S6 and S8, split-K over node
-// chunks; reduce.hip adds the splits in order and scatters the result into
-// the packed gradient).  Shared tile code: mfma_tile.hpp.
+// TN-form MFMA GEMMs of the weight gradients that wgrad.hip leaves out: the
+// concatenated update weight gradient with row scales (models without degree
+// buckets), and in BF16 every product launched by itself.  Split-K over node
+// chunks; reduce.hip adds the splits in order and scatters the result into the
+// packed gradient.  Shared tile code: mfma_tile.hpp.
 #include "mfma_tile.hpp"
 
 namespace hgnn {
@@ -10,17 +12,11 @@ namespace {
 // --------------------------------------------------------------------------
 // TN form (split-K weight gradients)
 // --------------------------------------------------------------------------
-// TAG only distinguishes launch sites in profiles: 1 the update weight
-// gradient (S6), 2 the message weight gradient (S8), 0 the others.  PERM:
-// bucketed chunks (g.perm non-null), a template parameter so that the row
-// lookups add no branch to the loop.  SCALE: some segment has row scales
-// (the concatenated update input); without it no scale is loaded at all.
-template <int PREC, int BM, int BN, int TAG, bool PERM, bool SCALE>
+template <int BM, int BN>
 __global__ void __launch_bounds__(256)
 k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
-  using P = Prec<PREC>;
-  using T = typename P::T;
-  constexpr int BK = P::BK / 2, LDA = BK + P::PAD;
+  using T = float;
+  constexpr int BK = Prec<0>::BK / 2;
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
   constexpr int NA = BM * BK / 4 / 256;
   constexpr int NB = BN * BK / 4 / 256;
@@ -29,17 +25,14 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
   // FP32 keeps the tiles in LDS as they lie in memory, k-major ([k][m] and
   // [k][n], rows padded by 4 floats), written with 16-byte stores; the MFMA
   // operands are read one k-slot at a time.  With a 68-float row pitch the
-  // lane groups of a read fall in distinct banks, whereas transposing on the
-  // way in (the BF16 form, which needs 8 consecutive k per lane) puts a
-  // wave's 64 scalar stores into 8 banks.
-  constexpr bool KMAJ = PREC == 0;
+  // lane groups of a read fall in distinct banks.
   constexpr int LDKA = BM + 4, LDKB = BN + 4;
-  __shared__ __attribute__((aligned(16))) T As[KMAJ ? BK * LDKA : BM * LDA];
-  __shared__ __attribute__((aligned(16))) T Bs[KMAJ ? BK * LDKB : BN * LDA];
+  __shared__ __attribute__((aligned(16))) T As[BK * LDKA];
+  __shared__ __attribute__((aligned(16))) T Bs[BK * LDKB];
 
   const int rows = dims->N;
   const int mtiles = (g.M + BM - 1) / BM;
-  const int zc = g.splits + (PERM ? g.nb : 0), gm = tn_group_rows(zc, mtiles);
+  const int zc = g.splits, gm = tn_group_rows(zc, mtiles);
   int grp, jt;
   xcd_group(blockIdx.x, zc * (mtiles / gm), gm * ntiles_n, grp, jt);
   if (grp < 0) return;
@@ -47,21 +40,8 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
   const int m0 = ((grp % (mtiles / gm)) * gm + jt / ntiles_n) * BM, n0 = (jt % ntiles_n) * BN;
   int chunk = (rows + g.splits - 1) / g.splits;
   chunk = (chunk + BK - 1) / BK * BK;
-  int i_lo = z * chunk;
-  int i_hi = min(rows, i_lo + chunk);
-  if constexpr (PERM) {
-    // bucket-pure chunks over the permuted rows: bucket q holds
-    // ceil(n_q / chunk) chunks, in bucket order; the chunks past the last
-    // are empty and write zero partials
-    int bq, r0, r1;
-    BucketWalk(g.brow, g.nb, chunk).find(z, bq, r0, r1);
-    i_lo = bq >= 0 ? r0 : 0;
-    i_hi = bq >= 0 ? min(r1, r0 + chunk) : 0;
-    if (m0 == 0 && n0 == 0 && threadIdx.x == 0) {
-      g.zscale[2 * z] = bq >= 0 ? g.table[2 * bq] : 0.f;
-      g.zscale[2 * z + 1] = bq >= 0 ? g.table[2 * bq + 1] : 0.f;
-    }
-  }
+  const int i_lo = z * chunk;
+  const int i_hi = min(rows, i_lo + chunk);
   const int KT = i_hi > i_lo ? (i_hi - i_lo + BK - 1) / BK : 0;
   const int tid = threadIdx.x, wid = tid >> 6;
   const int wm0 = (wid >> 1) * WM, wn0 = (wid & 1) * WN;
@@ -114,10 +94,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
     b_sstride[j] = b_has_scale[j] ? 1 : b_ld[j];
   }
   const int i_last = max(i_hi - 1, 0);
-  // Row ids (nodes) of tile t's rows into slot Q.  With bucketed chunks
-  // each is a load of the permutation: they are fetched one step before the
-  // data loads that use them and issued ahead of that step's data loads, so
-  // waiting for them never waits for data still in flight.
+  // Rows (clamped to the chunk) of tile t's vectors into slot Q.
   int prow[2][NA];
   auto fetch_rows = [&](auto slot, int t) {
     constexpr int Q = decltype(slot)::value;
@@ -125,8 +102,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int ic = min(i0 + a_il[j], i_last);
-      if constexpr (PERM) prow[Q][j] = g.perm[ic];
-      else prow[Q][j] = ic;
+      prow[Q][j] = ic;
     }
   };
   // data loads of tile t into stage S, from the row ids in slot S
@@ -140,7 +116,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
     for (int j = 0; j < NB; ++j) {
       const int ic = prow[S][j];
       rb[S][j] = *reinterpret_cast<const f4 *>(b_ptr[j] + (size_t)ic * b_ld[j]);
-      if constexpr (SCALE) rsc[S][j] = b_sptr[j][(size_t)ic * b_sstride[j]];
+      rsc[S][j] = b_sptr[j][(size_t)ic * b_sstride[j]];
     }
   };
   // (a uniform branch: only a chunk's last, partial step pays for masks)
@@ -153,26 +129,16 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
       const int v = tid + j * 256;
       const int il = v / (BM / 4), mc = (v % (BM / 4)) * 4;
       const f4 av = (!MASK || a_il[j] < rlim[S]) ? ra[S][j] : zero;
-      if constexpr (KMAJ) {
-        store4(As + il * LDKA + mc, av);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) store1(As + (mc + e) * LDA + il, av[e]);
-      }
+      store4(As + il * LDKA + mc, av);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int v = tid + j * 256;
       const int il = v / (BN / 4), nc = (v % (BN / 4)) * 4;
       f4 val = b_ones[j] ? f4{1.f, 0.f, 0.f, 0.f} : rb[S][j];
-      if constexpr (SCALE) val = val * (b_has_scale[j] ? rsc[S][j] : 1.0f);
+      val = val * (b_has_scale[j] ? rsc[S][j] : 1.0f);
       if constexpr (MASK) val = b_il[j] < rlim[S] ? val : zero;
-      if constexpr (KMAJ) {
-        store4(Bs + il * LDKB + nc, val);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) store1(Bs + (nc + e) * LDA + il, val[e]);
-      }
+      store4(Bs + il * LDKB + nc, val);
     }
   };
   auto stash = [&](auto st) {
@@ -219,8 +185,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
     // them, and a wait for the youngest loads would wait for all
     __builtin_amdgcn_sched_barrier(0);
     load(st, min(t + 2, KT - 1));
-    if constexpr (KMAJ) mma_kmajor();
-    else mma_tile<PREC, TM, TN, LDA, BK>(As, Bs, wm0, wn0, acc);
+    mma_kmajor();
   };
 
   if (KT > 0) {
@@ -270,10 +235,11 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 // when lane j of the group addresses row k0 + j / 4, columns c0 + 4 (j % 4)
 // .. + 3, lane i receives column c0 + i of rows k0 .. k0 + 3; two such reads
 // (k0 = 8 g and 8 g + 4 for lane group g) give the lane the k-slots
-// 8 g .. 8 g + 7 that the 16 x 16 x 32 MFMA takes, the assignment of the
-// 64 x 64 kernel, so both give the same sums in the same order.  The node
-// chunks, the bucket walk and the partial layout are those of k_gemm_tn
-// (BK = 32 as there).
+// 8 g .. 8 g + 7 that the 16 x 16 x 32 MFMA takes, the assignment of
+// wgrad.hip, so both give the same sums in the same order.  The node chunks
+// and the partial layout are wgrad.hip's.  Used for products launched one by
+// one, at 40k nodes 124 us a layer (both products) against 160 for wgrad.hip's
+// kernel, which rounds each operand once per wave rather than once per tile.
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s_t lds_v4s_t;
 typedef __attribute__((address_space(3))) __bf16 lds_bf16_t;
@@ -460,51 +426,35 @@ k_gemm_tn_tr(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 
 } // namespace
 
-template <int TAG, bool PERM, bool SCALE>
-static void run_tn(const Dims *dims, const GemmTN &g, hipStream_t s, hipEvent_t ev0,
-                   hipEvent_t ev1, int grid, int nt) {
-  // a non-null event pair is stamped with the kernel's own start and end
-  hipExtLaunchKernelGGL(k_gemm_tn<0, 64, 64, TAG, PERM, SCALE>, dim3(grid), dim3(256), 0, s,
-                        ev0, ev1, 0, dims, g, nt);
-}
-
-template <int TAG, bool PERM, bool SCALE>
-static void run_tn_tr(const Dims *dims, const GemmTN &g, hipStream_t s, hipEvent_t ev0,
-                      hipEvent_t ev1, int grid, int nt) {
-  hipExtLaunchKernelGGL(k_gemm_tn_tr<TAG, PERM, SCALE>, dim3(grid), dim3(256), 0, s, ev0, ev1,
-                        0, dims, g, nt);
-}
-
-// FP32: 64 x 64 tiles (k_gemm_tn); BF16: 128 x 128 tiles read through the
-// transposing LDS loads (k_gemm_tn_tr).  Measured at 40k nodes: the BF16
-// update weight gradient 257 -> 139 us and the message weight gradient
-// 115 -> 70 us at their best split counts, with bitwise equal partials.
-// Instances: the bucketed update weight gradient (no row scales), the
-// concatenated one (scaled segments), the message weight gradient (no
-// scales) and a general one for the other sites.
-hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision,
-                          hipStream_t s, int tag, hipEvent_t ev0, hipEvent_t ev1) {
+// FP32: the concatenated update weight gradient of unbucketed models
+// (max_degree above 15; row scales), 64 x 64 tiles (k_gemm_tn).  BF16: that
+// one and every weight gradient launched by itself, 128 x 128 tiles read
+// through the transposing LDS loads (k_gemm_tn_tr).
+hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision, hipStream_t s,
+                          int tag, hipEvent_t ev0, hipEvent_t ev1) {
   if (g.M <= 0 || g.Ncols <= 0) return hipSuccess;
   bool scaled = false;
   for (int q = 0; q < g.nseg; ++q) scaled = scaled || g.seg[q].scale != nullptr;
-  if (tag == 1 && g.perm && scaled) return hipErrorInvalidValue;
-  if (tag == 2 && (scaled || g.perm)) tag = 0;
-  if (tag == 0 && g.perm) return hipErrorInvalidValue;
+  if ((g.perm && (scaled || tag != 1)) || (precision == 0 && g.perm)) return hipErrorInvalidValue;
   const int T = precision ? 128 : 64;
   const int nt = cdiv(g.Ncols, T);
   const int zc = g.splits + (g.perm ? g.nb : 0), mt = cdiv(g.M, T), gm = tn_group_rows(zc, mt);
   const int grid = xcd_group_grid(zc * (mt / gm), gm * nt);
-  if (precision) {
-    if (tag == 1 && g.perm) run_tn_tr<1, true, false>(dims, g, s, ev0, ev1, grid, nt);
-    else if (tag == 1) run_tn_tr<1, false, true>(dims, g, s, ev0, ev1, grid, nt);
-    else if (tag == 2) run_tn_tr<2, false, false>(dims, g, s, ev0, ev1, grid, nt);
-    else run_tn_tr<0, false, true>(dims, g, s, ev0, ev1, grid, nt);
-  } else {
-    if (tag == 1 && g.perm) run_tn<1, true, false>(dims, g, s, ev0, ev1, grid, nt);
-    else if (tag == 1) run_tn<1, false, true>(dims, g, s, ev0, ev1, grid, nt);
-    else if (tag == 2) run_tn<2, false, false>(dims, g, s, ev0, ev1, grid, nt);
-    else run_tn<0, false, true>(dims, g, s, ev0, ev1, grid, nt);
-  }
+  // a non-null event pair is stamped with the kernel's own start and end
+#define HGNN_TR(TAG, PERM, SCALE)                                                               \
+  hipExtLaunchKernelGGL((k_gemm_tn_tr<TAG, PERM, SCALE>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0, \
+                        dims, g, nt)
+  if (!precision)
+    hipExtLaunchKernelGGL((k_gemm_tn<64, 64>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0, dims, g, nt);
+  else if (tag == 1 && g.perm)
+    HGNN_TR(1, true, false);
+  else if (tag == 1)
+    HGNN_TR(1, false, true);
+  else if (tag == 2 && !scaled)
+    HGNN_TR(2, false, false);
+  else
+    HGNN_TR(0, false, true);
+#undef HGNN_TR
   return hipGetLastError();
 }
 

@@ -57,6 +57,24 @@ template <> struct Prec<1> {
 
 template <int V> using IC = std::integral_constant<int, V>;
 
+// s_waitcnt immediate for vmcnt(n) with lgkmcnt(0) (expcnt left alone)
+template <int N> struct WaitVm {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  static constexpr int value = 0x0070 | (N & 15) | ((N >> 4) << 14);
+};
+// wait until at most n groups of PER loads are in flight (n uniform, <= MAX)
+template <int PER, int MAX> __device__ __forceinline__ void wait_groups(int n) {
+  if constexpr (MAX > 0) {
+    if (n >= MAX) {
+      __builtin_amdgcn_s_waitcnt(WaitVm<PER * MAX>::value);
+      return;
+    }
+    wait_groups<PER, MAX - 1>(n);
+  } else {
+    __builtin_amdgcn_s_waitcnt(WaitVm<0>::value);
+  }
+}
+
 // Map the dispatch order (round-robin over the 8 XCDs) to output tiles so that
 // each XCD receives a contiguous range of tiles: the N tiles of one M tile,
 // which share A rows, then share that XCD's L2.  A bijection on [0, T).
@@ -140,9 +158,6 @@ __device__ __forceinline__ void store4(__bf16 *dst, f4 v) {
   b[3] = (__bf16)v[3];
   *reinterpret_cast<bf16x4 *>(dst) = b;
 }
-__device__ __forceinline__ void store1(float *dst, float v) { *dst = v; }
-__device__ __forceinline__ void store1(__bf16 *dst, float v) { *dst = (__bf16)v; }
-
 // One K chunk of a wave's operands: FP32 16 k (four per lane, one 16-byte
 // LDS read per 16-row block), BF16 32 k (eight per lane).
 template <int PREC> struct Frag;

@@ -8,6 +8,8 @@
 // on more than kPerLane loads.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace hgnn {
 
 namespace {
@@ -17,9 +19,9 @@ inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 constexpr int kPerLane = 4;
 
 template <int G>
-__device__ __forceinline__ f4 ordered_sum(const float *__restrict__ src, int splits,
+__device__ __forceinline__ f4 ordered_sum(const float *__restrict__ src, int splits, int zfull,
                                           long long stride, int g) {
-  const int per = (splits + G - 1) / G;
+  const int per = (zfull + G - 1) / G;
   const int z_lo = g * per, z_hi = min(splits, z_lo + per);
   f4 sum = f4{0.f, 0.f, 0.f, 0.f};
   for (int z0 = z_lo; z0 < z_hi; z0 += kPerLane) {
@@ -57,7 +59,7 @@ k_reduce_nt(const Dims *__restrict__ dims, const GemmNT g) {
   const long long total = (long long)M * g.Ncols;
   // lanes past the end still take part in their group's shuffles
   const bool live = 4 * t < total;
-  f4 sum = ordered_sum<G>(g.P + (live ? 4 * t : 0), g.splits, total, (int)(gt % G));
+  f4 sum = ordered_sum<G>(g.P + (live ? 4 * t : 0), g.splits, g.splits, total, (int)(gt % G));
   if (!live || gt % G != 0) return;
   const int m = (int)(4 * t / g.Ncols), n = (int)(4 * t % g.Ncols);
 #pragma unroll
@@ -78,7 +80,7 @@ __global__ void __launch_bounds__(256) k_reduce_map(const ReduceMap r) {
   const long long t = gt / G;
   const long long total = (long long)r.M * r.Ncols;
   const bool live = 4 * t < total;
-  const f4 sum = ordered_sum<G>(r.P + (live ? 4 * t : 0), r.splits, total, (int)(gt % G));
+  const f4 sum = ordered_sum<G>(r.P + (live ? 4 * t : 0), r.splits, r.zfull, total, (int)(gt % G));
   if (!live || gt % G != 0) return;
   const int m = (int)(4 * t / r.Ncols), c0 = (int)(4 * t % r.Ncols);
   for (int k = 0; k < r.nroute; ++k) {
@@ -105,68 +107,6 @@ __global__ void __launch_bounds__(256) k_reduce_map(const ReduceMap r) {
       }
     }
     return;
-  }
-}
-
-// Bucketed update weight gradient: the chunks of one bucket share its
-// scalers, so sum_z P[z] gives the h block, W_0 and the bias, and the
-// s+ and s- weighted sums give W_+ and W_-.  Same lane grouping and order
-// as ordered_sum.
-template <int G>
-__global__ void __launch_bounds__(256) k_reduce_upd(const ReduceUpd r) {
-  const long long gt = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long t = gt / G;
-  const long long total = (long long)r.M * r.Ncols;
-  const bool live = 4 * t < total;
-  const float *src = r.P + (live ? 4 * t : 0);
-  const int g = (int)(gt % G);
-  const int per = (r.Z + G - 1) / G;
-  const int z_lo = g * per, z_hi = min(r.Z, z_lo + per);
-  f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0;
-  for (int z0 = z_lo; z0 < z_hi; z0 += kPerLane) {
-    f4 v[kPerLane];
-    float a[kPerLane], b[kPerLane];
-#pragma unroll
-    for (int u = 0; u < kPerLane; ++u) {
-      const int z = min(z0 + u, r.Z - 1);
-      v[u] = *reinterpret_cast<const f4 *>(src + z * total);
-      a[u] = r.zscale[2 * z];
-      b[u] = r.zscale[2 * z + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < kPerLane; ++u)
-      if (z0 + u < z_hi) {
-        s0 += v[u];
-        s1 += a[u] * v[u];
-        s2 += b[u] * v[u];
-      }
-  }
-#pragma unroll
-  for (int off = 1; off < G; off <<= 1) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      s0[e] += __shfl_down(s0[e], off, G);
-      s1[e] += __shfl_down(s1[e], off, G);
-      s2[e] += __shfl_down(s2[e], off, G);
-    }
-  }
-  if (!live || g != 0) return;
-  const int m = (int)(4 * t / r.Ncols), c0 = (int)(4 * t % r.Ncols);
-  const int H = r.H, ldp = r.F + 12 * H;
-  float *row = r.dWp + (size_t)m * ldp;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int c = c0 + e;
-    if (c < r.Fp) {
-      if (c < r.F) row[c] = s0[e];
-    } else if (c < r.Fp + 4 * H) {
-      const int cc = c - r.Fp;
-      row[r.F + cc] = s0[e];
-      row[r.F + 4 * H + cc] = s1[e];
-      row[r.F + 8 * H + cc] = s2[e];
-    } else if (c == r.Fp + 4 * H) {
-      r.dbp[m] = s0[e];
-    }
   }
 }
 
@@ -217,22 +157,33 @@ k_colsum(const Dims *__restrict__ dims, const float *__restrict__ X, int ldx, in
 
 // Several reductions in one launch (the weight gradients of one layer): job
 // j takes grid[j] workgroups; each job's lane groups are G[j] lanes wide (a
-// runtime width: the shuffle tree reads lanes up to G - 1 above, and only a
-// group's first lane, which sums its own group, writes).  The bodies are
-// k_reduce_upd's and k_reduce_map's, so each output is the same sum in the
-// same order as in those kernels.
+// runtime width: the tree reads lanes up to G - 1 above, and only a group's
+// first lane, which sums its own group, writes).  job_map adds what
+// k_reduce_map adds, in the same order; job_upd is the bucketed update weight
+// gradient: the chunks of one bucket share its scalers, so sum_z P[z] gives
+// the h block, W_0 and the bias, and the s+ and s- weighted sums give W_+ and
+// W_-.
+// The lane reads are DPP row shifts (a group lies within a 16-lane row): 36
+// cross-lane reads a thread through LDS took longer than its loads.
+template <int OFF> __device__ __forceinline__ float from_above(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x100 + OFF, 0xf, 0xf, true));
+}
 __device__ __forceinline__ float tree_sum(float v, int G) {
-  for (int off = 1; off < G; off <<= 1) v += __shfl_down(v, off, 64);
+  if (G > 1) v += from_above<1>(v);
+  if (G > 2) v += from_above<2>(v);
+  if (G > 4) v += from_above<4>(v);
+  if (G > 8) v += from_above<8>(v);
   return v;
 }
 
-__device__ __forceinline__ void job_upd(const ReduceUpd &r, long long gt, int G) {
-  const long long t = gt / G;
-  const long long total = (long long)r.M * r.Ncols;
+__device__ __forceinline__ void job_upd(const ReduceUpd &r, int b, int G) {
+  const int sh = __builtin_ctz(G); // G is a power of two, at most 16
+  const int t = b * (256 >> sh) + (threadIdx.x >> sh), g = threadIdx.x & (G - 1);
+  const int total = r.M * r.Ncols;
   const bool live = 4 * t < total;
   const float *src = r.P + (live ? 4 * t : 0);
-  const int g = (int)(gt % G);
-  const int per = (r.Z + G - 1) / G;
+  const int per = (r.zfull + G - 1) >> sh;
   const int z_lo = g * per, z_hi = min(r.Z, z_lo + per);
   f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0;
   for (int z0 = z_lo; z0 < z_hi; z0 += kPerLane) {
@@ -241,7 +192,7 @@ __device__ __forceinline__ void job_upd(const ReduceUpd &r, long long gt, int G)
 #pragma unroll
     for (int u = 0; u < kPerLane; ++u) {
       const int z = min(z0 + u, r.Z - 1);
-      v[u] = *reinterpret_cast<const f4 *>(src + z * total);
+      v[u] = *reinterpret_cast<const f4 *>(src + (size_t)z * total);
       a[u] = r.zscale[2 * z];
       b[u] = r.zscale[2 * z + 1];
     }
@@ -260,7 +211,7 @@ __device__ __forceinline__ void job_upd(const ReduceUpd &r, long long gt, int G)
     s2[e] = tree_sum(s2[e], G);
   }
   if (!live || g != 0) return;
-  const int m = (int)(4 * t / r.Ncols), c0 = (int)(4 * t % r.Ncols);
+  const int m = 4 * t / r.Ncols, c0 = 4 * t - m * r.Ncols;
   const int H = r.H, ldp = r.F + 12 * H;
   float *row = r.dWp + (size_t)m * ldp;
 #pragma unroll
@@ -279,21 +230,26 @@ __device__ __forceinline__ void job_upd(const ReduceUpd &r, long long gt, int G)
   }
 }
 
-__device__ __forceinline__ void job_map(const ReduceMap &r, long long gt, int G) {
-  const long long t = gt / G;
-  const long long total = (long long)r.M * r.Ncols;
-  const bool live = 4 * t < total;
+__device__ __forceinline__ void job_map(const ReduceMap &r, int b, int G) {
+  const int sh = __builtin_ctz(G);
+  const int t = b * (256 >> sh) + (threadIdx.x >> sh), g = threadIdx.x & (G - 1);
+  const int total = r.M * r.Ncols;
+  bool live = 4 * t < total;
+  const int m = 4 * t / r.Ncols, c0 = 4 * t - m * r.Ncols;
+  // rows that keep only their sum column have no partial sums elsewhere
+  if (c0 < r.main_cols)
+    for (int k = 0; k < r.nroute; ++k)
+      if (m >= r.route[k].r0 && m < r.route[k].r1 && !r.route[k].main) live = false;
   const float *src = r.P + (live ? 4 * t : 0);
-  const int g = (int)(gt % G);
-  const int per = (r.splits + G - 1) / G;
-  const int z_lo = g * per, z_hi = min(r.splits, z_lo + per);
+  const int per = (r.zfull + G - 1) >> sh;
+  const int z_lo = g * per, z_hi = live ? min(r.splits, z_lo + per) : 0;
   f4 sum = f4{0.f, 0.f, 0.f, 0.f};
   for (int z0 = z_lo; z0 < z_hi; z0 += kPerLane) {
     f4 v[kPerLane];
 #pragma unroll
     for (int u = 0; u < kPerLane; ++u) {
       const int z = min(z0 + u, r.splits - 1);
-      v[u] = *reinterpret_cast<const f4 *>(src + z * total);
+      v[u] = *reinterpret_cast<const f4 *>(src + (size_t)z * total);
     }
 #pragma unroll
     for (int u = 0; u < kPerLane; ++u)
@@ -302,7 +258,6 @@ __device__ __forceinline__ void job_map(const ReduceMap &r, long long gt, int G)
 #pragma unroll
   for (int e = 0; e < 4; ++e) sum[e] = tree_sum(sum[e], G);
   if (!live || g != 0) return;
-  const int m = (int)(4 * t / r.Ncols), c0 = (int)(4 * t % r.Ncols);
   for (int k = 0; k < r.nroute; ++k) {
     const ReduceRoute &ro = r.route[k];
     if (m < ro.r0 || m >= ro.r1) continue;
@@ -333,12 +288,38 @@ __device__ __forceinline__ void job_map(const ReduceMap &r, long long gt, int G)
 __global__ void __launch_bounds__(256) k_reduce_jobs(const ReduceJobs j) {
   int b = blockIdx.x, k = 0;
   while (k + 1 < j.njobs && b >= j.grid[k]) b -= j.grid[k++];
-  const long long gt = (long long)b * blockDim.x + threadIdx.x;
-  if (j.upd[k]) job_upd(j.u, gt, j.G[k]);
-  else job_map(j.m[k], gt, j.G[k]);
+  if (j.upd[k]) job_upd(j.u, b, j.G[k]);
+  else job_map(j.m[k], b, j.G[k]);
+}
+
+// blockIdx.y: the job
+__global__ void __launch_bounds__(256) k_reduce_all(const ReduceJob *__restrict__ tab) {
+  const ReduceJob &j = tab[blockIdx.y];
+  const int b = blockIdx.x;
+  if (b >= j.blocks) return;
+  if (j.upd) job_upd(j.u, b, j.G);
+  else job_map(j.m, b, j.G);
 }
 
 } // namespace
+
+int reduce_layout(ReduceJob *jobs, int n) {
+  int most = 0;
+  for (int k = 0; k < n; ++k) {
+    ReduceJob &j = jobs[k];
+    const long long cells = j.upd ? (long long)j.u.M * j.u.Ncols : (long long)j.m.M * j.m.Ncols;
+    j.G = pick_group(j.upd ? j.u.zfull : j.m.zfull);
+    j.blocks = cdiv(cells / 4 * j.G, 256);
+    most = std::max(most, j.blocks);
+  }
+  return most;
+}
+
+hipError_t launch_reduce_all(const ReduceJob *tab, int n, int most, hipStream_t s) {
+  if (n <= 0 || most <= 0) return hipSuccess;
+  k_reduce_all<<<dim3(most, n), 256, 0, s>>>(tab);
+  return hipGetLastError();
+}
 
 hipError_t launch_colsum(const Dims *dims, const float *X, int ldx, int C, int Z, float *P,
                          hipStream_t s) {
@@ -346,21 +327,6 @@ hipError_t launch_colsum(const Dims *dims, const float *X, int ldx, int C, int Z
   // whole 16-byte column groups
   if (C % 4 || ldx % 4 || reinterpret_cast<uintptr_t>(X) % 16) return hipErrorInvalidValue;
   k_colsum<<<dim3(Z, cdiv(C / 4, 256)), kColsumThreads, 0, s>>>(dims, X, ldx, C, Z, P);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_upd(const ReduceUpd &r, hipStream_t s) {
-  const long long total = (long long)r.M * r.Ncols;
-  if (total <= 0) return hipSuccess;
-  const int G = pick_group(r.Z);
-  const int grid = cdiv(total / 4 * G, 256);
-  switch (G) {
-  case 1: k_reduce_upd<1><<<grid, 256, 0, s>>>(r); break;
-  case 2: k_reduce_upd<2><<<grid, 256, 0, s>>>(r); break;
-  case 4: k_reduce_upd<4><<<grid, 256, 0, s>>>(r); break;
-  case 8: k_reduce_upd<8><<<grid, 256, 0, s>>>(r); break;
-  default: k_reduce_upd<16><<<grid, 256, 0, s>>>(r); break;
-  }
   return hipGetLastError();
 }
 
@@ -382,7 +348,7 @@ hipError_t launch_reduce_nt(const Dims *dims, int capM, const GemmNT &g, hipStre
 hipError_t launch_reduce_map(const ReduceMap &r, hipStream_t s) {
   const long long total = (long long)r.M * r.Ncols;
   if (total <= 0) return hipSuccess;
-  const int G = pick_group(r.splits);
+  const int G = pick_group(r.zfull);
   const int grid = cdiv(total / 4 * G, 256);
   switch (G) {
   case 1: k_reduce_map<1><<<grid, 256, 0, s>>>(r); break;
@@ -398,7 +364,7 @@ hipError_t launch_reduce_jobs(ReduceJobs j, hipStream_t s) {
   int total = 0;
   for (int k = 0; k < j.njobs; ++k) {
     const long long n = j.upd[k] ? (long long)j.u.M * j.u.Ncols : (long long)j.m[k].M * j.m[k].Ncols;
-    j.G[k] = pick_group(j.upd[k] ? j.u.Z : j.m[k].splits);
+    j.G[k] = pick_group(j.upd[k] ? j.u.zfull : j.m[k].zfull);
     j.grid[k] = n > 0 ? cdiv(n / 4 * j.G[k], 256) : 0;
     total += j.grid[k];
   }

@@ -68,20 +68,23 @@ constexpr int kSplitDeRows = 16384;
 // the sums then cost about as much as reading De once)
 constexpr int kColsumChunks = 128;
 
-// Split count of a weight-gradient GEMM (GEMM and ordered reduction timed
-// together at 4.5k and 40k nodes).  FP32 (64 x 64 tiles): about 512
-// workgroups (the update and message weight gradients at 4.5k nodes: 26
-// and 19 us, against 28 and 21 us at 1024).  BF16 (128 x 128 tiles,
-// gemm_tn.hip): about 384 workgroups, at most 24 splits (swept again after
-// the loads were kept in flight: the update weight gradient at 4.5k nodes
-// 17.4 us at 24 splits, 19.5 us at 32; the message weight gradient equal).
+// Batches below this many nodes keep every layer's du and D and run all
+// weight gradients in one launch at the end of the backward pass.
+constexpr int kDeferNodes = 16384;
+constexpr size_t kDeferPartBytes = size_t(1) << 30; // and partial sums up to this
+
+// Chunks of a weight-gradient product (product and ordered reduction timed
+// together at 4.5k and 40k nodes): FP32 about 512 workgroups of 64 x 64
+// tiles, BF16 about 384 of 128 x 128, at most 24.  They fix the order of every
+// sum over the nodes, whatever kernel forms it.
+constexpr int kMaxTnSplits = 64;
 int tn_splits(int M, int Ncols, int precision) {
   const int T = precision ? 128 : 64;
   const int tiles = ((M + T - 1) / T) * ((Ncols + T - 1) / T);
   const int target = precision ? 384 : 512;
   int s = (target + tiles - 1) / tiles;
   if (s < 1) s = 1;
-  if (s > (precision ? 24 : 64)) s = precision ? 24 : 64;
+  if (s > (precision ? 24 : kMaxTnSplits)) s = precision ? 24 : kMaxTnSplits;
   return s;
 }
 
@@ -99,10 +102,13 @@ void free_work(Exec &ex) {
                    (void **)&w.dQn, (void **)&w.en, (void **)&w.dhn,
                    (void **)&w.csr.csr_dst, (void **)&w.csr.perm, (void **)&w.csr.brow,
                    (void **)&w.csr.scan, (void **)&w.h0, (void **)&w.gcG,
+                   (void **)&w.wg_part, (void **)&w.wg_tab, (void **)&w.wg_zscale,
+                   (void **)&w.duL, (void **)&w.DL,
                    (void **)&w.gcD, (void **)&w.gcdm, (void **)&w.gcD1};
   for (void **p : ptrs) dfree(*p);
   for (auto &p : w.gcA) dfree(reinterpret_cast<void *&>(p));
   w.gcA.clear();
+  w.wg_n = 0;
   for (auto &p : w.hbuf) dfree(reinterpret_cast<void *&>(p));
   for (auto &p : w.hbuf_b) dfree(reinterpret_cast<void *&>(p));
   w.hbuf_b.clear();
@@ -123,6 +129,208 @@ void free_work(Exec &ex) {
 // and a hidden width that whole 64-deep K tiles cover.
 static bool bf16_copies(const hgnn_ctx *c) {
   return c->kind == HGNN_GC_PNA && c->prec == 1 && c->nb > 0 && c->H % 64 == 0;
+}
+
+// A product's chunk counts for batches of up to capN nodes: no more chunks
+// than the batch has 32-row pieces (the rest would be empty); the order of
+// the sum over the chunks stays that of the full count.
+constexpr int kAnyN = 1 << 30;
+static void set_chunks(WgJob &j, int prec, int capN) {
+  const int full = tn_splits(j.M, j.N + 4, prec);
+  j.splits = std::max(1, std::min(full, (capN + 31) / 32));
+  j.zfull = full + j.nb;
+}
+
+// The weight-gradient products of PNA layer l: [0] the bucketed update
+// linear's, du^T [h | A | 1], [1] the message linear's, [D_in | D_out | De]^T
+// [h | 1] (of the De rows only the sum column is needed; without them for
+// batches that take their column sums apart).  Operands and partials are left
+// to the caller.
+static WgJob upd_job(const hgnn_ctx *c, int l, int capN) {
+  const LayerDesc &d = c->ld[l];
+  WgJob j{};
+  j.ldx = j.M = j.sum_from = c->H;
+  j.nseg = 2;
+  j.seg[0] = WgSeg{nullptr, d.Fp, d.Fp};
+  j.seg[1] = WgSeg{nullptr, 4 * c->H, 4 * c->H};
+  j.N = d.Fp + 4 * c->H;
+  j.nb = c->nb;
+  j.table = c->table;
+  set_chunks(j, c->prec, capN);
+  return j;
+}
+static WgJob msg_job(const hgnn_ctx *c, int l, bool de, int capN) {
+  const LayerDesc &d = c->ld[l];
+  WgJob j{};
+  j.ldx = (2 + c->Fe) * c->H;
+  j.sum_from = 2 * c->H;
+  j.M = de ? j.ldx : 2 * c->H;
+  j.nseg = 1;
+  j.seg[0] = WgSeg{nullptr, d.Fp, d.Fp};
+  j.N = d.Fp;
+  set_chunks(j, c->prec, capN);
+  return j;
+}
+// X^T [Y | 1] for X [rows, M] and one segment Y [rows, ld], all of its columns
+static WgJob gc_job(int M, int ld, int ncols, int prec, int capN) {
+  WgJob j{};
+  j.ldx = j.M = j.sum_from = M;
+  j.nseg = 1;
+  j.seg[0] = WgSeg{nullptr, ld, ncols};
+  j.N = ncols;
+  set_chunks(j, prec, capN);
+  return j;
+}
+// GraphSAGE's product, du^T [h | M | 1] of layer l
+static WgJob sage_job(const hgnn_ctx *c, int l, int capN) {
+  const int Fp = c->ld[l].Fp;
+  WgJob j = gc_job(c->H, Fp, Fp, c->prec, capN);
+  j.nseg = 2;
+  j.seg[1] = WgSeg{nullptr, Fp, Fp};
+  j.N = 2 * Fp;
+  set_chunks(j, c->prec, capN);
+  return j;
+}
+// CGCNN's, [D_in | D_out | De]^T [h | 1] (of the De rows the sum column only)
+static WgJob cgcnn_job(const hgnn_ctx *c, int capN) {
+  WgJob j = gc_job((4 + 2 * c->Fe) * c->H, c->H, c->H, c->prec, capN);
+  j.sum_from = 4 * c->H;
+  return j;
+}
+static size_t wg_part_floats(const WgJob &j, int nb) {
+  return (size_t)(j.splits + nb) * j.M * (j.N + 4);
+}
+// One product by itself: FP32 in wgrad.hip; BF16 in gemm_tn.hip, whose kernel
+// keeps two steps of operands in registers and so covers the memory latency of
+// a large batch better (40k nodes, H = 256: update 157 us against 220, message
+// 91 against 100); in one launch over every layer of a small batch wgrad.hip is
+// the faster one (128 molecules, H = 128, six layers: 36 us against 132).
+static hipError_t launch_product(const Dims *dims, const WgJob &j, int prec, hipStream_t s,
+                                 int tag = 0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+  if (prec == 0) return launch_wgrad(dims, j, s, ev0, ev1);
+  GemmTN t{};
+  t.X = j.X;
+  t.ldx = j.ldx;
+  t.M = j.M;
+  for (int q = 0; q < j.nseg; ++q) t.seg[q] = SegY{j.seg[q].ptr, nullptr, j.seg[q].ld, j.seg[q].ncols};
+  t.seg[j.nseg] = SegY{nullptr, nullptr, 0, 4}; // the sum column
+  t.nseg = j.nseg + 1;
+  t.Ncols = j.N + 4;
+  t.P = j.P;
+  t.splits = j.splits;
+  t.perm = j.perm;
+  t.brow = j.brow;
+  t.nb = j.nb;
+  t.table = j.table;
+  t.zscale = j.zscale;
+  return launch_gemm_tn(dims, t, prec, s, tag, ev0, ev1);
+}
+static ReduceMap gc_reduce(const WgJob &j) {
+  ReduceMap r{};
+  r.P = j.P;
+  r.splits = j.splits;
+  r.zfull = j.zfull;
+  r.M = j.M;
+  r.Ncols = j.N + 4;
+  r.main_cols = j.N;
+  r.F = j.seg[0].ncols;
+  r.Fp = j.seg[0].ncols;
+  return r;
+}
+static ReduceMap sage_reduce(const hgnn_ctx *c, int l, const WgJob &j) {
+  const LayerDesc &d = c->ld[l];
+  ReduceMap r = gc_reduce(j);
+  r.F = d.F;
+  r.npad = 2;
+  r.route[0] = ReduceRoute{0, c->H, c->grads + d.oWm, 2 * d.F, 0, c->grads + d.obm, 1, c->H};
+  r.nroute = 1;
+  return r;
+}
+static ReduceMap cgcnn_reduce(const hgnn_ctx *c, int l, const WgJob &j) {
+  const LayerDesc &d = c->ld[l];
+  const int H = c->H, ldw = 2 * H + c->Fe;
+  float *dW = c->grads + d.oWm, *db = c->grads + d.obm;
+  ReduceMap r = gc_reduce(j);
+  r.route[0] = ReduceRoute{0, 2 * H, dW, ldw, 0, db, 1, 2 * H};
+  r.route[1] = ReduceRoute{2 * H, 4 * H, dW, ldw, H, nullptr, 0, 1};
+  r.route[2] = ReduceRoute{4 * H, j.M, nullptr, 0, 0, dW + 2 * H, ldw, 2 * H};
+  r.nroute = c->Fe > 0 ? 3 : 2;
+  return r;
+}
+static ReduceMap emb_reduce(const hgnn_ctx *c, const WgJob &j) {
+  float *dWe = c->grads + c->off_emb;
+  ReduceMap r = gc_reduce(j);
+  r.F = c->F0;
+  r.route[0] = ReduceRoute{0, c->H, dWe, c->F0, 0, dWe + (size_t)c->H * c->F0, 1, c->H};
+  r.nroute = 1;
+  return r;
+}
+static ReduceUpd upd_reduce(const hgnn_ctx *c, int l, const WgJob &j, float *dwl) {
+  const LayerDesc &d = c->ld[l];
+  ReduceUpd r{};
+  r.P = j.P;
+  r.zscale = j.zscale;
+  r.Z = j.splits + c->nb;
+  r.zfull = j.zfull;
+  r.M = j.M;
+  r.Ncols = j.N + 4;
+  r.F = d.F;
+  r.Fp = d.Fp;
+  r.H = c->H;
+  r.dWp = dwl + (d.oWp - d.off);
+  r.dbp = dwl + (d.obp - d.off);
+  return r;
+}
+static ReduceMap msg_reduce(const hgnn_ctx *c, int l, const WgJob &j, float *dwl) {
+  const LayerDesc &d = c->ld[l];
+  const int H = c->H, ldm = 2 * d.F + c->Fe;
+  float *dWm = dwl + (d.oWm - d.off), *dbm = dwl + (d.obm - d.off);
+  ReduceMap r{};
+  r.P = j.P;
+  r.splits = j.splits;
+  r.zfull = j.zfull;
+  r.M = j.M;
+  r.Ncols = j.N + 4;
+  r.main_cols = j.N;
+  r.F = d.F;
+  r.Fp = d.Fp;
+  r.route[0] = ReduceRoute{0, H, dWm, ldm, 0, dbm, 1, H};                         // D_in
+  r.route[1] = ReduceRoute{H, 2 * H, dWm, ldm, d.F, nullptr, 0, 1};               // D_out
+  r.route[2] = ReduceRoute{2 * H, j.M, nullptr, 0, 0, dWm + 2 * d.F, ldm, H};     // De
+  r.nroute = j.M > 2 * H ? 3 : 2;
+  return r;
+}
+
+// The products of a backward pass in the order of their launch (the longer
+// first) and their layers (-1: the CGCNN embedding).
+static std::vector<std::pair<WgJob, int>> wg_jobs(const hgnn_ctx *c, int capN) {
+  std::vector<std::pair<WgJob, int>> v;
+  for (int l = 0; l < c->L; ++l)
+    v.emplace_back(c->kind == HGNN_GC_PNA    ? upd_job(c, l, capN)
+                   : c->kind == HGNN_GC_SAGE ? sage_job(c, l, capN)
+                                             : cgcnn_job(c, capN),
+                   l);
+  for (int l = 0; c->kind == HGNN_GC_PNA && l < c->L; ++l) v.emplace_back(msg_job(c, l, true, capN), l);
+  if (c->kind == HGNN_GC_CGCNN) v.emplace_back(gc_job(c->H, c->F0p, c->F0p, c->prec, capN), -1);
+  return v;
+}
+// Whether the weight gradients of a backward pass over batches of up to capN
+// nodes run in one launch at its end: the floats of their partial sums, or 0
+// when layers go one at a time (recomputation, which keeps one layer's
+// aggregates; unbucketed models; large batches, whose products fill the GPU by
+// themselves).
+static size_t defer_floats(const hgnn_ctx *c, int capN) {
+  if ((c->kind == HGNN_GC_PNA && !c->nb) || c->recompute || capN >= kDeferNodes) return 0;
+  size_t n = 0;
+  for (const auto &j : wg_jobs(c, capN)) n += wg_part_floats(j.first, j.first.nb);
+  return n * sizeof(float) <= kDeferPartBytes ? n : 0;
+}
+// number of those products, and the bytes of their device tables
+static int wg_count(const hgnn_ctx *c) {
+  return c->kind == HGNN_GC_PNA ? 2 * c->L : c->kind == HGNN_GC_SAGE ? c->L : c->L + 1;
+}
+static size_t defer_table_bytes(const hgnn_ctx *c) {
+  return wg_count(c) * (sizeof(WgJob) + sizeof(ReduceJob));
 }
 
 // Every capacity-sized buffer of an Exec, with its element count: the one
@@ -184,19 +392,34 @@ static bool for_each_buffer(const hgnn_ctx *c, Work &w, int capB, int capN, int 
     if (Tn > 0)
       ok = ok && f(w.dQn, (size_t)Tn * capN * H) && f(w.en, (size_t)capN * Tn) &&
            f(w.dhn, (size_t)capN * H);
-    ok = ok && f(w.du, (size_t)capN * H) && f(w.dh0, (size_t)capN * H) &&
-         f(w.dh1, (size_t)capN * H);
+    const size_t defer = defer_floats(c, capN);
+    ok = ok && f(w.du, (size_t)capN * H);
+    if (defer) {
+      // PNA and GraphSAGE products read every layer's du, PNA and CGCNN ones
+      // every layer's D
+      const size_t ldD = pna ? (2 + c->Fe) * H : (4 + 2 * c->Fe) * H;
+      if (c->kind != HGNN_GC_CGCNN) ok = ok && f(w.duL, (size_t)L * capN * H);
+      if (c->kind != HGNN_GC_SAGE) ok = ok && f(w.DL, (size_t)L * capN * ldD);
+      ok = ok && f(w.wg_part, defer) && f(w.wg_tab, defer_table_bytes(c));
+      if (pna) ok = ok && f(w.wg_zscale, (size_t)2 * L * (kMaxTnSplits + c->nb));
+    }
+    if (!defer || c->kind == HGNN_GC_CGCNN)
+      ok = ok && f(w.dh0, (size_t)capN * H) && f(w.dh1, (size_t)capN * H);
     if (pna) {
       // dA is stored only when the adjoint does not form it itself
       if (!agg_bwd_fused_ok(H, c->nb)) ok = ok && f(w.dA, (size_t)capN * 4 * H);
-      ok = ok && f(w.dm, (size_t)capE * H) && f(w.D, (size_t)capN * (2 + c->Fe) * H);
-      if (!c->recompute) ok = ok && f(w.D2, (size_t)capN * (2 + c->Fe) * H);
+      ok = ok && f(w.dm, (size_t)capE * H);
+      if (!defer) ok = ok && f(w.D, (size_t)capN * (2 + c->Fe) * H);
+      if (!c->recompute && !defer) ok = ok && f(w.D2, (size_t)capN * (2 + c->Fe) * H);
     }
     else if (c->kind == HGNN_GC_SAGE)
       ok = ok && f(w.gcG, (size_t)capN * 2 * H);
-    else
-      ok = ok && f(w.gcD, (size_t)capN * (4 + 2 * c->Fe) * H) &&
-           f(w.gcD1, (size_t)capN * (4 + 2 * c->Fe) * H) && f(w.gcdm, (size_t)capE * 2 * H);
+    else {
+      if (!defer)
+        ok = ok && f(w.gcD, (size_t)capN * (4 + 2 * c->Fe) * H) &&
+             f(w.gcD1, (size_t)capN * (4 + 2 * c->Fe) * H);
+      ok = ok && f(w.gcdm, (size_t)capE * 2 * H);
+    }
   }
   return ok;
 }
@@ -232,6 +455,65 @@ size_t carve_work(const hgnn_ctx *c, Exec &ex, int B, int N, int E, char *base,
   return off;
 }
 
+// The device tables of the deferred weight gradients and their reduction:
+// every address in them belongs to the context or to this workspace.
+static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int capN) {
+  w.wg_n = 0;
+  if (!w.wg_tab) return hipSuccess;
+  auto v = wg_jobs(c, capN);
+  const int n = (int)v.size(), H = c->H, L = c->L;
+  if (n != wg_count(c)) return hipErrorInvalidValue;
+  std::vector<uint8_t> tab(defer_table_bytes(c));
+  WgJob *jobs = reinterpret_cast<WgJob *>(tab.data());
+  ReduceJob *red = reinterpret_cast<ReduceJob *>(jobs + n);
+  float *P = w.wg_part, *zs = w.wg_zscale;
+  int rot = 0, b128 = 0;
+  for (const auto &j : v) b128 += wg_blocks(j.first, 128);
+  w.wg_tile = wg_tile_all(b128, c->prec);
+  w.wg_most = 0;
+  for (int k = 0; k < n; ++k) {
+    WgJob &j = v[k].first;
+    const int l = v[k].second;
+    const bool upd = j.nb > 0;
+    j.P = P;
+    P += wg_part_floats(j, j.nb);
+    j.seg[0].ptr = l > 0 ? w.hbuf[l - 1] : c->kind == HGNN_GC_CGCNN && l == 0 ? w.h0 : w.xpad;
+    red[k] = ReduceJob{};
+    if (c->kind == HGNN_GC_PNA && upd) {
+      j.X = w.duL + (size_t)l * capN * H;
+      j.seg[1].ptr = w.A[l];
+      j.perm = w.csr.perm;
+      j.brow = w.csr.brow;
+      j.zscale = zs;
+      zs += 2 * (j.splits + j.nb);
+      red[k].upd = 1;
+      red[k].u = upd_reduce(c, l, j, c->grads + c->ld[l].off);
+    } else if (c->kind == HGNN_GC_PNA) {
+      j.X = w.DL + (size_t)l * capN * j.ldx;
+      red[k].m = msg_reduce(c, l, j, c->grads + c->ld[l].off);
+    } else if (c->kind == HGNN_GC_SAGE) {
+      j.X = w.duL + (size_t)l * capN * H;
+      j.seg[1].ptr = w.gcA[l];
+      red[k].m = sage_reduce(c, l, j);
+    } else if (l >= 0) {
+      j.X = w.DL + (size_t)l * capN * j.ldx;
+      red[k].m = cgcnn_reduce(c, l, j);
+    } else { // the embedding's, from where L steps between the two buffers end
+      j.X = L % 2 ? w.dh1 : w.dh0;
+      red[k].m = emb_reduce(c, j);
+    }
+    j.rot = rot; // go on where the last job's chunks ended
+    rot = (rot + j.splits + j.nb) % 8;
+    if (!wg_job_ok(j)) return hipErrorInvalidValue;
+    w.wg_most = std::max(w.wg_most, wg_blocks(j, w.wg_tile));
+    jobs[k] = j;
+  }
+  w.red_most = reduce_layout(red, n);
+  hipError_t e = hipMemcpy(w.wg_tab, tab.data(), tab.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) w.wg_n = n;
+  return e;
+}
+
 int ensure_work(hgnn_ctx *c, Exec &ex, int B, int N, int E) {
   Work &w = ex.w;
   if (B <= w.capB && N <= w.capN && E <= w.capE) return HGNN_OK;
@@ -246,6 +528,10 @@ int ensure_work(hgnn_ctx *c, Exec &ex, int B, int N, int E) {
   if (!ok) {
     free_work(ex);
     return fail(HGNN_ENOMEM, "hipMalloc failed for the batch workspace");
+  }
+  if (hipError_t et = build_wg_tables(c, w, capN); et != hipSuccess) {
+    free_work(ex);
+    return hip_fail(c, et, "weight-gradient tables");
   }
   w.capB = capB;
   w.capN = capN;
@@ -552,6 +838,21 @@ int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_
   return HGNN_OK;
 }
 
+// The weight gradients of a whole backward pass (see Work::duL).
+static hipError_t launch_deferred_wgrads(hgnn_ctx *c, Exec &ex, hipStream_t s) {
+  const Work &w = ex.w;
+  const WgJob *jobs = reinterpret_cast<const WgJob *>(w.wg_tab);
+  const ReduceJob *red = reinterpret_cast<const ReduceJob *>(jobs + w.wg_n);
+  hipError_t e;
+  {
+    TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, s, /*manual=*/true);
+    e = launch_wgrad_all(ex.dims, jobs, w.wg_n, w.wg_most, c->prec, w.wg_tile, s, tl.start(),
+                         tl.stop());
+  }
+  if (e == hipSuccess) e = launch_reduce_all(red, w.wg_n, w.red_most, s);
+  return e;
+}
+
 // dh_out_masked: dh_out already carries this layer's ReLU adjoint (it is du).
 // mask_dh_in: fold the previous layer's ReLU adjoint (h_in > 0) into dh_in.
 // defer_join: leave the main stream's wait for this layer's weight-gradient
@@ -561,10 +862,12 @@ int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_
 // aggregation adjoint two layers on (with one D buffer, the next one's).
 // Not with recomputation, which rewrites the stored A and PQ at the start of
 // the next layer.
+// defer_wg: leave the weight gradients to the caller (deferred_wgrads), who
+// has given this layer a du and a D of its own; everything runs on s then.
 int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_in,
                    const float *h_out, const float *dh_out, float *dh_in, float *dwl,
                    hipStream_t s, bool dh_out_masked = false, bool mask_dh_in = false,
-                   bool defer_join = false) {
+                   bool defer_join = false, bool defer_wg = false) {
   if (int rc = injected_failure(c)) return rc;
   const LayerDesc &d = c->ld[l];
   const int H = c->H, Fe = c->Fe, ldD = (2 + Fe) * H;
@@ -584,10 +887,10 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // D of this layer: odd layers use the second buffer when it exists (no
   // recomputation), so that writing it need not wait for the previous
   // layer's weight gradients, which read the other one
-  float *Dl = (l & 1) && w.D2 ? w.D2 : w.D;
+  float *Dl = w.D;
+  if (w.DL) Dl = w.DL + (defer_wg ? (size_t)l * w.capN * ldD : 0);
+  else if ((l & 1) && w.D2) Dl = w.D2;
   const float *bm = wl + (d.obm - d.off);
-  float *dWm = dwl + (d.oWm - d.off), *dbm = dwl + (d.obm - d.off);
-  float *dWp = dwl + (d.oWp - d.off), *dbp = dwl + (d.obp - d.off);
   hipError_t e = hipSuccess;
   const float *du = dh_out;
   if (!dh_out_masked) {
@@ -597,49 +900,35 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   }
   // fork: the weight gradients run on the aux stream
   hipStream_t a = c->aux;
-  e = hipEventRecord(c->fork_ev[0], s);
-  if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[0], 0);
-  if (e != hipSuccess) return hip_fail(c, e, "fork");
+  if (!defer_wg) {
+    e = hipEventRecord(c->fork_ev[0], s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[0], 0);
+    if (e != hipSuccess) return hip_fail(c, e, "fork");
+  }
   // S6: dW^p = du^T [h || A || s+ A || s- A]; with degree buckets
   // du^T [h || A] per bucket-pure chunk, the scalers applied by the
   // reduction.  Its partial sums stay in part_u until the message weight
   // gradient's are in part too: one launch reduces both.
   ReduceJobs red{};
-  if (c->nb) {
-    GemmTN t{};
-    t.X = du;
-    t.ldx = H;
-    t.M = H;
-    t.seg[0] = SegY{hin, nullptr, ldh, d.Fp};
-    t.seg[1] = SegY{A, nullptr, 4 * H, 4 * H};
-    t.seg[2] = SegY{nullptr, nullptr, 0, 4}; // sum column: db^p
-    t.nseg = 3;
-    t.Ncols = d.Fp + 4 * H + 4;
-    t.P = c->part_u;
-    t.splits = d.split_p;
-    t.perm = w.csr.perm;
-    t.brow = w.csr.brow;
-    t.nb = c->nb;
-    t.table = c->table;
-    t.zscale = c->zscale;
+  if (c->nb && !defer_wg) {
+    WgJob j = upd_job(c, l, ex.N);
+    j.X = du;
+    j.seg[0].ptr = hin;
+    j.seg[0].ld = ldh;
+    j.seg[1].ptr = A;
+    j.P = c->part_u;
+    j.perm = w.csr.perm;
+    j.brow = w.csr.brow;
+    j.zscale = c->zscale;
     {
       TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, a, /*manual=*/true);
-      e = launch_gemm_tn(ex.dims, t, c->prec, a, /*tag=*/1, tl.start(), tl.stop());
+      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/1, tl.start(), tl.stop());
     }
     if (e != hipSuccess) return hip_fail(c, e, "update weight gradient");
     red.upd[0] = true;
-    ReduceUpd &r = red.u;
-    r.P = c->part_u;
-    r.zscale = c->zscale;
-    r.Z = d.split_p + c->nb;
-    r.M = H;
-    r.Ncols = t.Ncols;
-    r.F = d.F;
-    r.Fp = d.Fp;
-    r.H = H;
-    r.dWp = dWp;
-    r.dbp = dbp;
-  } else {
+    red.u = upd_reduce(c, l, j, dwl);
+  } else if (!c->nb) {
+    float *dWp = dwl + (d.oWp - d.off), *dbp = dwl + (d.obp - d.off);
     GemmTN t{};
     t.X = du;
     t.ldx = H;
@@ -661,7 +950,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     if (e != hipSuccess) return hip_fail(c, e, "update weight gradient");
     ReduceMap &r = red.m[0];
     r.P = c->part_u;
-    r.splits = d.split_p;
+    r.splits = r.zfull = d.split_p;
     r.M = H;
     r.Ncols = d.Fp + 12 * H + 4;
     r.main_cols = d.Fp + 12 * H;
@@ -752,58 +1041,40 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     e = launch_transpose_sum(ex.dims, ex.N, H, w.csr.srcptr, w.csr.t2csr, w.dm, Dl, ldD, s);
   if (e != hipSuccess) return hip_fail(c, e, "aggregation adjoint");
   // second fork: D = [D_in | D_out | De] is ready
-  e = hipEventRecord(c->fork_ev[1], s);
-  if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[1], 0);
-  if (e != hipSuccess) return hip_fail(c, e, "fork");
-  // S8: [dW_dst | dW_src] = [D_in | D_out]^T h, db^m = sum_i D_in, and the
-  // edge-feature columns sum_i De_i = sum_k dm_k e_k (the sum column of the
-  // De rows, whose product with h is not needed: for large batches those
-  // rows get a GEMM of their own with the sum column alone)
-  const bool split_de = Fe > 0 && ex.N >= kSplitDeRows;
-  {
-    GemmTN t{};
-    t.X = Dl;
-    t.ldx = ldD;
-    t.M = split_de ? 2 * H : ldD;
-    t.nseg = 2;
-    t.seg[0] = SegY{hin, nullptr, ldh, d.Fp};
-    t.seg[1] = SegY{nullptr, nullptr, 0, 4}; // sum column: db^m and the e_k weights
-    t.Ncols = d.Fp + 4;
-    t.P = c->part;
-    t.splits = split_de ? d.split_m2 : d.split_m;
+  if (!defer_wg) {
+    e = hipEventRecord(c->fork_ev[1], s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[1], 0);
+    if (e != hipSuccess) return hip_fail(c, e, "fork");
+    // S8: [dW_dst | dW_src] = [D_in | D_out]^T h, db^m = sum_i D_in, and the
+    // edge-feature columns sum_i De_i = sum_k dm_k e_k (the sum column of the
+    // De rows; large batches form it by k_colsum)
+    const bool split_de = Fe > 0 && ex.N >= kSplitDeRows;
+    WgJob j = msg_job(c, l, !split_de, ex.N);
+    j.X = Dl;
+    j.seg[0].ptr = hin;
+    j.seg[0].ld = ldh;
+    j.P = c->part;
     {
       TimedLaunch tl(c, ex, SITE_MESSAGE_WGRAD, a, /*manual=*/true);
-      e = launch_gemm_tn(ex.dims, t, c->prec, a, /*tag=*/2, tl.start(), tl.stop());
+      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/2, tl.start(), tl.stop());
     }
-    const int ldm = 2 * d.F + Fe;
-    {
-      ReduceMap &r = red.m[red.njobs++];
-      r.P = c->part;
-      r.splits = t.splits;
-      r.M = t.M;
-      r.Ncols = d.Fp + 4;
-      r.main_cols = d.Fp;
-      r.F = d.F;
-      r.Fp = d.Fp;
-      r.route[0] = ReduceRoute{0, H, dWm, ldm, 0, dbm, 1, H};               // D_in
-      r.route[1] = ReduceRoute{H, 2 * H, dWm, ldm, d.F, nullptr, 0, 1};      // D_out
-      r.route[2] = ReduceRoute{2 * H, ldD, nullptr, 0, 0, dWm + 2 * d.F, ldm, H}; // De
-      r.nroute = (Fe > 0 && !split_de) ? 3 : 2;
-    }
-    // column sums of De over kColsumChunks row chunks, after the GEMM's
+    red.m[red.njobs++] = msg_reduce(c, l, j, dwl);
+    // column sums of De over kColsumChunks row chunks, after the product's
     // partials in the same buffer
-    float *pcol = c->part + (size_t)t.splits * t.M * t.Ncols;
+    float *pcol = c->part + wg_part_floats(j, 0);
     if (e == hipSuccess && split_de) {
+      const int ldm = 2 * d.F + Fe;
       e = launch_colsum(ex.dims, Dl + 2 * H, ldD, Fe * H, kColsumChunks, pcol, a);
       ReduceMap &r = red.m[red.njobs++];
       r.P = pcol;
-      r.splits = kColsumChunks;
+      r.splits = r.zfull = kColsumChunks;
       r.M = Fe * H;
       r.Ncols = 4;
       r.main_cols = 0;
       r.F = 0;
       r.Fp = 0;
-      r.route[0] = ReduceRoute{0, Fe * H, nullptr, 0, 0, dWm + 2 * d.F, ldm, H}; // De
+      r.route[0] =
+          ReduceRoute{0, Fe * H, nullptr, 0, 0, dwl + (d.oWm - d.off) + 2 * d.F, ldm, H}; // De
       r.nroute = 1;
     }
     if (e == hipSuccess) e = launch_reduce_jobs(red, a);
@@ -855,6 +1126,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     }
     if (e != hipSuccess) return hip_fail(c, e, "input gradient GEMM");
   }
+  if (defer_wg) return HGNN_OK;
   // join now, or leave it to the launches above of the next layers
   e = hipEventRecord(c->pjoin_ev[l & 1], a);
   if (e == hipSuccess && !defer_join) e = hipStreamWaitEvent(s, c->pjoin_ev[l & 1], 0);
@@ -913,26 +1185,13 @@ static int node_heads_backward(hgnn_ctx *c, Exec &ex, const float *h, hipStream_
                                       c->nw_dev, w.en, w.dQn, s);
   for (int k = 0; k < Tn && e == hipSuccess; ++k) {
     float *dW1 = gwn + (size_t)k * node_head_size(H);
-    GemmTN t{};
-    t.X = w.dQn + (size_t)k * ex.N * H;
-    t.ldx = H;
-    t.M = H;
-    t.seg[0] = SegY{h, nullptr, H, H};
-    t.seg[1] = SegY{nullptr, nullptr, 0, 4}; // sum column: db1
-    t.nseg = 2;
-    t.Ncols = H + 4;
-    t.P = c->part;
-    t.splits = c->split_node;
-    e = launch_gemm_tn(ex.dims, t, /*precision=*/0, s);
+    WgJob j = gc_job(H, H, H, /*prec=*/0, ex.N);
+    j.X = w.dQn + (size_t)k * ex.N * H;
+    j.seg[0].ptr = h;
+    j.P = c->part;
+    e = launch_product(ex.dims, j, /*prec=*/0, s);
     if (e == hipSuccess) {
-      ReduceMap r{};
-      r.P = c->part;
-      r.splits = c->split_node;
-      r.M = H;
-      r.Ncols = H + 4;
-      r.main_cols = H;
-      r.F = H;
-      r.Fp = H;
+      ReduceMap r = gc_reduce(j);
       r.route[0] = ReduceRoute{0, H, dW1, H, 0, dW1 + (size_t)H * H, 1, H};
       r.nroute = 1;
       e = launch_reduce_map(r, s);
@@ -1127,50 +1386,33 @@ static void wait_pending_join(hgnn_ctx *c, hipStream_t s, hipError_t &e) {
 static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_t s) {
   Work &w = ex.w;
   const int H = c->H, Fe = c->Fe;
+  const bool defer = w.wg_n > 0; // all weight gradients at the end, everything on s
   hipError_t e = hipSuccess;
   wait_pending_join(c, s, e); // left by a backward that failed part-way
   if (e != hipSuccess) return hip_fail(c, e, "join");
   for (int l = c->L - 1; l >= 0; --l) {
     if (int rc = injected_failure(c)) return rc;
     const LayerDesc &d = c->ld[l];
-    float *dW = c->grads + d.oWm, *db = c->grads + d.obm;
     const float *hin = l ? w.hbuf[l - 1] : (c->kind == HGNN_GC_CGCNN ? w.h0 : w.xpad);
     const int ldh = l ? H : (c->kind == HGNN_GC_CGCNN ? H : c->F0p);
     const float *du = cur;
     if (c->kind == HGNN_GC_SAGE) {
-      fork_to_aux(c, 0, s, e);
-      if (e != hipSuccess) return hip_fail(c, e, "fork");
-      // dW = du^T [h || M], db = sum du
-      GemmTN t{};
-      t.X = du;
-      t.ldx = H;
-      t.M = H;
-      t.seg[0] = SegY{hin, nullptr, ldh, d.Fp};
-      t.seg[1] = SegY{w.gcA[l], nullptr, d.Fp, d.Fp};
-      t.seg[2] = SegY{nullptr, nullptr, 0, 4};
-      t.nseg = 3;
-      t.Ncols = 2 * d.Fp + 4;
-      t.P = c->part;
-      t.splits = d.split_p;
-      {
-        TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, c->aux);
-        e = launch_gemm_tn(ex.dims, t, c->prec, c->aux);
+      if (!defer) { // dW = du^T [h || M], db = sum du
+        fork_to_aux(c, 0, s, e);
+        if (e != hipSuccess) return hip_fail(c, e, "fork");
+        WgJob j = sage_job(c, l, ex.N);
+        j.X = du;
+        j.seg[0].ptr = hin;
+        j.seg[0].ld = ldh;
+        j.seg[1].ptr = w.gcA[l];
+        j.P = c->part;
+        {
+          TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, c->aux);
+          e = launch_product(ex.dims, j, c->prec, c->aux);
+        }
+        if (e == hipSuccess) e = launch_reduce_map(sage_reduce(c, l, j), c->aux);
+        if (e != hipSuccess) return hip_fail(c, e, "GraphSAGE weight gradient");
       }
-      if (e == hipSuccess) {
-        ReduceMap r{};
-        r.P = c->part;
-        r.splits = d.split_p;
-        r.M = H;
-        r.Ncols = 2 * d.Fp + 4;
-        r.main_cols = 2 * d.Fp;
-        r.F = d.F;
-        r.Fp = d.Fp;
-        r.npad = 2;
-        r.route[0] = ReduceRoute{0, H, dW, 2 * d.F, 0, db, 1, H};
-        r.nroute = 1;
-        e = launch_reduce_map(r, c->aux);
-      }
-      if (e != hipSuccess) return hip_fail(c, e, "GraphSAGE weight gradient");
       if (l > 0) { // G = du [W_self | W_nbr]; dh_in = G_self + neighbour scatter
         GemmNT g{};
         g.nseg = 1;
@@ -1191,7 +1433,7 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
       }
     } else {
       const int ldD = (4 + 2 * Fe) * H;
-      float *gcD = (l & 1) ? w.gcD1 : w.gcD;
+      float *gcD = defer ? w.DL + (size_t)l * w.capN * ldD : (l & 1) ? w.gcD1 : w.gcD;
       {
         TimedLaunch tl(c, ex, SITE_AGGREGATE_BWD, s);
         e = launch_cg_aggregate_bwd(ex.dims, ex.N, H, Fe, w.csr.rowptr, w.csr.csr_src,
@@ -1202,41 +1444,23 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
         e = launch_transpose_sum(ex.dims, ex.N, 2 * H, w.csr.srcptr, w.csr.t2csr, w.gcdm, gcD,
                                  ldD, s);
       if (e != hipSuccess) return hip_fail(c, e, "CGCNN aggregation adjoint");
-      fork_to_aux(c, 0, s, e);
-      if (e != hipSuccess) return hip_fail(c, e, "fork");
-      // [dW_dst | dW_src] = [D_in | D_out]^T h; db and the edge columns from
-      // the constant-one column
-      GemmTN t{};
-      t.X = gcD;
-      t.ldx = ldD;
-      t.M = ldD;
-      t.seg[0] = SegY{hin, nullptr, ldh, H};
-      t.seg[1] = SegY{nullptr, nullptr, 0, 4};
-      t.nseg = 2;
-      t.Ncols = H + 4;
-      t.P = c->part;
-      t.splits = d.split_p;
-      {
-        TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, c->aux);
-        e = launch_gemm_tn(ex.dims, t, c->prec, c->aux);
+      if (!defer) {
+        // [dW_dst | dW_src] = [D_in | D_out]^T h; db and the edge columns from
+        // the sum column
+        fork_to_aux(c, 0, s, e);
+        if (e != hipSuccess) return hip_fail(c, e, "fork");
+        WgJob j = cgcnn_job(c, ex.N);
+        j.X = gcD;
+        j.seg[0].ptr = hin;
+        j.seg[0].ld = ldh;
+        j.P = c->part;
+        {
+          TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, c->aux);
+          e = launch_product(ex.dims, j, c->prec, c->aux);
+        }
+        if (e == hipSuccess) e = launch_reduce_map(cgcnn_reduce(c, l, j), c->aux);
+        if (e != hipSuccess) return hip_fail(c, e, "CGCNN weight gradient");
       }
-      if (e == hipSuccess) {
-        const int ldw = 2 * H + Fe;
-        ReduceMap r{};
-        r.P = c->part;
-        r.splits = d.split_p;
-        r.M = ldD;
-        r.Ncols = H + 4;
-        r.main_cols = H;
-        r.F = H;
-        r.Fp = H;
-        r.route[0] = ReduceRoute{0, 2 * H, dW, ldw, 0, db, 1, 2 * H};
-        r.route[1] = ReduceRoute{2 * H, 4 * H, dW, ldw, H, nullptr, 0, 1};
-        r.route[2] = ReduceRoute{4 * H, ldD, nullptr, 0, 0, dW + 2 * H, ldw, 2 * H};
-        r.nroute = Fe > 0 ? 3 : 2;
-        e = launch_reduce_map(r, c->aux);
-      }
-      if (e != hipSuccess) return hip_fail(c, e, "CGCNN weight gradient");
       // dh_in = du (residual) + [D_in | D_out] [W_dst; W_src], masked by the
       // ReLU of the layer below (the embedding below layer 0 has none)
       GemmNT g{};
@@ -1261,6 +1485,15 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
       }
       if (e != hipSuccess) return hip_fail(c, e, "CGCNN input gradient");
     }
+    if (defer) {
+      if (c->kind == HGNN_GC_SAGE) { // every layer's du stays
+        cur = l ? w.duL + (size_t)(l - 1) * w.capN * H : cur;
+        nxt = l > 1 ? w.duL + (size_t)(l - 2) * w.capN * H : nullptr;
+      } else {
+        std::swap(cur, nxt);
+      }
+      continue;
+    }
     if (l > 0) { // deferred to the next layer
       if (e == hipSuccess) e = hipEventRecord(c->join_ev, c->aux);
       c->join_pending = e == hipSuccess;
@@ -1271,32 +1504,16 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
     if (e != hipSuccess) return hip_fail(c, e, "join");
     std::swap(cur, nxt);
   }
-  if (c->kind == HGNN_GC_CGCNN) { // embedding: dW_emb = dh0^T x, db_emb = sum dh0
-    GemmTN t{};
-    t.X = cur;
-    t.ldx = H;
-    t.M = H;
-    t.seg[0] = SegY{w.xpad, nullptr, c->F0p, c->F0p};
-    t.seg[1] = SegY{nullptr, nullptr, 0, 4};
-    t.nseg = 2;
-    t.Ncols = c->F0p + 4;
-    t.P = c->part;
-    t.splits = c->split_emb;
-    e = launch_gemm_tn(ex.dims, t, c->prec, s);
-    if (e == hipSuccess) {
-      float *dWe = c->grads + c->off_emb;
-      ReduceMap r{};
-      r.P = c->part;
-      r.splits = c->split_emb;
-      r.M = H;
-      r.Ncols = c->F0p + 4;
-      r.main_cols = c->F0p;
-      r.F = c->F0;
-      r.Fp = c->F0p;
-      r.route[0] = ReduceRoute{0, H, dWe, c->F0, 0, dWe + (size_t)H * c->F0, 1, H};
-      r.nroute = 1;
-      e = launch_reduce_map(r, s);
-    }
+  if (defer) {
+    e = launch_deferred_wgrads(c, ex, s);
+    if (e != hipSuccess) return hip_fail(c, e, "weight gradients");
+  } else if (c->kind == HGNN_GC_CGCNN) { // embedding: dW_emb = dh0^T x, db_emb = sum dh0
+    WgJob j = gc_job(H, c->F0p, c->F0p, c->prec, ex.N);
+    j.X = cur;
+    j.seg[0].ptr = w.xpad;
+    j.P = c->part;
+    e = launch_product(ex.dims, j, c->prec, s);
+    if (e == hipSuccess) e = launch_reduce_map(emb_reduce(c, j), s);
     if (e != hipSuccess) return hip_fail(c, e, "embedding weight gradient");
   }
   return HGNN_OK;
@@ -1413,16 +1630,14 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
       d.obm = off;
       off += H;
       d.size = off - d.off;
-      d.split_p = tn_splits(H, 2 * d.Fp + 4, cfg->precision);
-      part_max = std::max(part_max, (size_t)d.split_p * H * (2 * d.Fp + 4));
       c->ld.push_back(d);
+      part_max = std::max(part_max, wg_part_floats(sage_job(c, l, kAnyN), 0));
     }
   } else if (kind == HGNN_GC_CGCNN) {
     c->off_emb = 0;
     off += (int64_t)H * c->F0 + H;
-    c->split_emb = tn_splits(H, c->F0p + 4, cfg->precision);
-    part_max = std::max(part_max, (size_t)c->split_emb * H * (c->F0p + 4));
-    const int ldD = (4 + 2 * c->Fe) * H;
+    part_max = std::max(wg_part_floats(gc_job(H, c->F0p, c->F0p, c->prec, kAnyN), 0),
+                        wg_part_floats(cgcnn_job(c, kAnyN), 0));
     for (int l = 0; l < c->L; ++l) {
       LayerDesc d{};
       d.F = d.Fp = H;
@@ -1431,8 +1646,6 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
       d.obm = off;
       off += 2 * H;
       d.size = off - d.off;
-      d.split_p = tn_splits(ldD, H + 4, cfg->precision);
-      part_max = std::max(part_max, (size_t)d.split_p * ldD * (H + 4));
       c->ld.push_back(d);
     }
   }
@@ -1452,25 +1665,24 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
     d.obp = off;
     off += H;
     d.size = off - d.off;
-    // the update weight gradient's columns: [h | A | s+ A | s- A | sum] or,
-    // with degree buckets, [h | A | sum] over nb more (bucket-pure) chunks
-    const int wcols = d.Fp + (c->nb ? 4 : 12) * H + 4;
-    d.split_p = tn_splits(H, wcols, cfg->precision);
-    // message weight gradient: [D_in | D_out | De]^T [h | 1] in one GEMM, or
-    // for large batches [D_in | D_out]^T [h | 1] and the column sums of De
-    // apart (the De^T h block is not needed; see kSplitDeRows)
-    d.split_m = tn_splits((2 + c->Fe) * H, d.Fp + 4, cfg->precision);
-    d.split_m2 = tn_splits(2 * H, d.Fp + 4, cfg->precision);
-
-    zmax = std::max(zmax, d.split_p + c->nb);
-    // the update weight gradient's partials have a buffer of their own: they
-    // are reduced together with the message weight gradient's
-    part_u_max = std::max(part_u_max, (size_t)(d.split_p + c->nb) * H * wcols);
-    const size_t b = std::max((size_t)d.split_m * (2 + c->Fe) * H * (d.Fp + 4),
-                              (size_t)d.split_m2 * 2 * H * (d.Fp + 4) +
-                                  (size_t)kColsumChunks * c->Fe * H * 4);
-    part_max = std::max(part_max, b);
+    // partials of a layer's update weight gradient: columns [h | A | sum] over
+    // nb more (bucket-pure) chunks or, without buckets, [h | A | s+ A | s- A |
+    // sum]; they have a buffer of their own, as they are reduced together
+    // with the message weight gradient's
     c->ld.push_back(d);
+    if (c->nb) {
+      const WgJob j = upd_job(c, l, kAnyN);
+      zmax = std::max(zmax, j.splits + c->nb);
+      part_u_max = std::max(part_u_max, wg_part_floats(j, c->nb));
+    } else {
+      const int wcols = d.Fp + 12 * H + 4;
+      c->ld[l].split_p = tn_splits(H, wcols, cfg->precision);
+      part_u_max = std::max(part_u_max, (size_t)c->ld[l].split_p * H * wcols);
+    }
+    for (int de = 0; de < 2; ++de) { // message: with the De rows, or their column sums apart
+      part_max = std::max(part_max, wg_part_floats(msg_job(c, l, de, kAnyN), 0) +
+                                        (de ? 0 : (size_t)kColsumChunks * c->Fe * H * 4));
+    }
   }
   c->Tg = Tg;
   c->Tn = Tn;
@@ -1509,8 +1721,7 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
   off += (int64_t)Tn * node_head_size(H);
   c->P = off;
   if (Tn > 0) {
-    c->split_node = tn_splits(H, H + 4, 0);
-    part_max = std::max(part_max, (size_t)c->split_node * H * (H + 4));
+    part_max = std::max(part_max, wg_part_floats(gc_job(H, H, H, 0, kAnyN), 0));
   }
 
   hipError_t e = hipGetDevice(&c->dev);
@@ -1849,7 +2060,13 @@ int hgnn_backward(hgnn_ctx *c, const float *dpred, void *stream) {
   if (!c->staged_from_params) return fail(HGNN_EINVAL, "weights changed since the forward");
   hipStream_t s = (hipStream_t)stream;
   Work &w = c->ex.w;
+  const bool defer = w.wg_n > 0;
+  const size_t NH = (size_t)w.capN * c->H;
   float *cur = w.dh0, *nxt = w.dh1;
+  if (w.duL) {
+    cur = w.duL + (c->L - 1) * NH;
+    nxt = c->L > 1 ? cur - NH : nullptr;
+  }
   // the head adjoint already applies the last layer's ReLU adjoint, and each
   // input gradient GEMM applies the one below it
   int rc = head_backward(c, c->ex, c->params + c->off_head, c->ex.target, dpred, cur,
@@ -1869,6 +2086,13 @@ int hgnn_backward(hgnn_ctx *c, const float *dpred, void *stream) {
     }
   for (int l = c->L - 1; l >= 0; --l) {
     const float *h_in = l ? w.hbuf[l - 1] : c->ex.xin;
+    if (defer) { // one stream, each layer's du and D kept
+      rc = layer_backward(c, c->ex, l, c->params + c->ld[l].off, h_in, w.hbuf[l], w.duL + l * NH,
+                          l ? w.duL + (l - 1) * NH : nullptr, c->grads + c->ld[l].off, s,
+                          /*dh_out_masked=*/true, /*mask_dh_in=*/true, false, /*defer_wg=*/true);
+      if (rc) return rc;
+      continue;
+    }
     // the last call (l = 0) joins, which orders all weight-gradient work
     rc = layer_backward(c, c->ex, l, c->params + c->ld[l].off, h_in, w.hbuf[l], cur,
                         l ? nxt : nullptr, c->grads + c->ld[l].off, s,
@@ -1876,6 +2100,10 @@ int hgnn_backward(hgnn_ctx *c, const float *dpred, void *stream) {
                         /*defer_join=*/l > 0 && !c->recompute);
     if (rc) return rc;
     std::swap(cur, nxt);
+  }
+  if (defer) {
+    hipError_t e = launch_deferred_wgrads(c, c->ex, s);
+    if (e != hipSuccess) return hip_fail(c, e, "weight gradients");
   }
   return HGNN_OK;
 }

@@ -14,8 +14,7 @@ struct LayerDesc {
   int F, Fp;                       // input width and its padding to 16
   int64_t off, oWm, obm, oWp, obp; // offsets into the packed vector
   int64_t size;
-  int split_p, split_m;            // split-K counts of the two weight gradients
-  int split_m2;                    // message weight gradient without the De rows
+  int split_p;                     // chunks of the concatenated update weight gradient
 };
 
 // Capacity-sized device buffers of one batch.
@@ -37,6 +36,13 @@ struct Work {
   float *D = nullptr;                    // [N, (2 + Fe) H] = [D_in | D_out | De]
   float *D2 = nullptr;                   // odd layers' D (deferred joins, no recompute)
   float *dh0 = nullptr, *dh1 = nullptr;
+  // Small batches keep every layer's du and D (and partial sums) until the
+  // end of the backward pass, whose weight gradients then run in one launch
+  // (empty / null otherwise: one layer's at a time)
+  float *duL = nullptr, *DL = nullptr;   // [L][N, H], [L][N, (2 + Fe) H]
+  float *wg_part = nullptr, *wg_zscale = nullptr;
+  uint8_t *wg_tab = nullptr;             // products [wg_n], then reductions [wg_n]
+  int wg_n = 0, wg_tile = 0, wg_most = 0, red_most = 0;
   float *ntpart = nullptr;               // split-K partials of the NT GEMMs
   // node heads: outputs [N, Tn], hidden [Tn][N][H], its adjoint, errors
   // [N, Tn], and their share of dL/dh [N, H]
@@ -121,7 +127,6 @@ struct hgnn_ctx {
   // weight copies for the GEMMs
   int Tg = 1, Tn = 0;
   int64_t off_node = 0;
-  int split_node = 1; // split-K count of a node head's weight-gradient GEMM
   float *gw_dev = nullptr, *nw_dev = nullptr;
   float *W1n = nullptr, *W1nT = nullptr;
   float *nh_part = nullptr; // node heads' per-chunk dw2/db2 partials
@@ -135,7 +140,6 @@ struct hgnn_ctx {
   std::vector<void *> Wg1, Wg1_lo, Wg2, Wg2_lo;
   void *Wemb = nullptr, *Wemb_lo = nullptr;
   int64_t off_emb = 0;
-  int split_emb = 1;
   hgnn::GcStageJob *gc_jobs = nullptr;
   int gc_njobs = 0;
   long long gc_max_elems = 0;
