@@ -254,27 +254,30 @@ struct ReduceMap {
 // ------------------------------------------------------------------------
 
 // csr.hip
+// A batch's errors are the union of this many words (the one-launch build has a
+// word per workgroup).
+constexpr int kErrWords = 64;
 struct CsrBufs {
   int *rowptr, *csr_src, *csr_eid, *deg, *srcptr, *t2csr, *node_graph;
   int *csr_dst;       // destination of each CSR position
   int *cnt_in, *cnt_out, *tmp_out, *csr_pos;
   float *csr_e;       // [E, Fe] edge attributes in CSR order
   float *sp, *sm;     // per-node degree scalers
-  int *err;           // error word
+  int *err;           // error words [kErrWords]
   // degree buckets (nb > 0): perm [N] nodes in (degree, id) order, brow
   // [nb + 1] bucket offsets into perm; scan [kScanRec per block] scratch of
   // the multi-block scan
   int *perm, *brow, *scan;
   int nb;
 };
-// sets the batch sizes; also zeroes *err when err is non-null
-hipError_t launch_set_dims(Dims *d, int B, int N, int E, int *err, hipStream_t s);
-// clear_err: zero the error word first (else the caller has).  x non-null:
-// also write the first layer's input zero-padded to Fp columns into xpad.
-hipError_t launch_csr_build(const Dims *dims, int capB, int capN, int capE,
+// Batch validation and the CSR of a batch of at most capB, capN, capE.  set:
+// these are the batch's sizes and are written to dims; else dims holds them.
+// x non-null: also write the first layer's input zero-padded to Fp columns
+// into xpad.  The error words are set to this batch's errors.
+hipError_t launch_csr_build(Dims *dims, bool set, int capB, int capN, int capE,
                             const int *graph_ptr, const int *edge_index,
                             const float *edge_attr, int Fe, int max_degree,
-                            const float *scaler_table, const CsrBufs &c, bool clear_err,
+                            const float *scaler_table, const CsrBufs &c,
                             const float *x, int F, float *xpad, int Fp, hipStream_t s);
 hipError_t launch_pad_copy(const Dims *dims, int capN, const float *x, int F,
                            float *xp, int Fp, hipStream_t s);

@@ -1,4 +1,5 @@
-// Step S0: batch validation and the destination-sorted CSR.
+// Step S0: batch validation and the destination-sorted CSR.  Small batches take
+// one launch (k_csr_small), larger ones a chain of seven.
 //
 // Edges of a batch of molecular graphs (Table 1 layout: edge_index (2, E),
 // row 0 source, row 1 destination) are grouped by destination and, within a
@@ -10,20 +11,16 @@
 // deterministic and independent of the COO edge order.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace hgnn {
 
 namespace {
 
-__global__ void k_set_dims(Dims *d, int B, int N, int E, int *err) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (d) {
-      d->B = B;
-      d->N = N;
-      d->E = E;
-      d->pad = 0;
-    }
-    if (err) *err = 0;
-  }
+__global__ void __launch_bounds__(kErrWords)
+k_set_dims(Dims *d, int B, int N, int E, int *__restrict__ err) {
+  if (threadIdx.x == 0 && d) *d = Dims{B, N, E, 0};
+  err[threadIdx.x] = 0;
 }
 
 // node -> graph id by binary search over graph_ptr (staged in LDS when it
@@ -460,23 +457,383 @@ __global__ void k_pad_copy(const Dims *__restrict__ dims, const float *__restric
   xp[t] = c < F ? x[(size_t)i * F + c] : 0.0f;
 }
 
+// The whole build in one launch, for batches whose nodes and edges fit a
+// workgroup's LDS and 16 bits.  The chain of kernels above costs its launches
+// (2 to 5 us each, every one waiting for the last) and not its work: with the
+// launch that clears the error words 20 us for one molecule (25 nodes), 26 at
+// 1.1k nodes and 2.3k edges, 31 at 4.5k and 9.3k; this kernel 6, 10 and 16.
+//
+// Every workgroup reads all edges and counts all in-degrees (the offsets and
+// degree buckets of its nodes need them), then writes the CSR of its own nodes:
+// a run of whole graphs, so that no edge of another workgroup touches them.
+// What is repeated is bound by one CU's loads and LDS (10 of the 16 us); one
+// workgroup alone takes 41 us at 4.5k nodes, most of it in the scattered
+// stores.  The code runs once per launch, so it is fetched rather than bound
+// by its instructions: loops are kept rolled (unrolled over 12 edges a thread
+// in registers it took 5 us longer).
+//
+// LDS counters, the in-degree in the low and the out-degree in the high half
+// of a word, become both prefix sums in one scan of the packed words, and then
+// cursors that place the own edges.  An edge's place in its segment is the
+// number of smaller keys there ((source, edge id) by destination; CSR position
+// by source): the order of the chain's per-segment sorts.
+//
+// Workgroups past the first `parts` only copy the padded input.  Every
+// workgroup stores an error word of its own and the first one clears the rest,
+// so that no launch has to come before.
+struct CsrSmall {
+  Dims *dims;
+  int set, B, N, E; // set: B, N, E hold and are written to dims; else read there
+  int parts, step;  // workgroups that build, and about the nodes each has
+  const int *graph_ptr, *ei;
+  const float *edge_attr;
+  int Fe, max_degree;
+  const float *table;
+  CsrBufs c;
+  const float *x;
+  int F;
+  float *xpad;
+  int Fp;
+};
+
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+// padded input, four lanes to a row, from row t0 / 4 on: whether all are finite
+__device__ __forceinline__ bool pad_rows(const CsrSmall &a, int N, int t0, int nt) {
+  bool finite = true;
+#pragma unroll 1
+  for (int r = t0 >> 2; r < N; r += nt >> 2) {
+    const float *xr = a.x + (size_t)r * a.F;
+#pragma unroll 1
+    for (int c0 = 4 * (t0 & 3); c0 < a.Fp; c0 += 16) {
+      f4 v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = c0 + k < a.F ? xr[c0 + k] : 0.f;
+      finite = finite && isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]) && isfinite(v[3]);
+      *reinterpret_cast<f4 *>(a.xpad + (size_t)r * a.Fp + c0) = v;
+    }
+  }
+  return finite;
+}
+
+// Inclusive scans over a wave by DPP (row shifts, then the last lane of a row
+// into the rows above it): no LDS traffic, which bounds this kernel.
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned dpp0(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned wave_add_scan(unsigned v) {
+  v += dpp0<0x111, 0xf>(v);
+  v += dpp0<0x112, 0xf>(v);
+  v += dpp0<0x114, 0xf>(v);
+  v += dpp0<0x118, 0xf>(v);
+  v += dpp0<0x142, 0xa>(v); // lane 15 of rows 0 and 2 into rows 1 and 3
+  v += dpp0<0x143, 0xc>(v); // lane 31 into rows 2 and 3
+  return v;
+}
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+template <int T, int CAPN, int CAPE>
+__global__ void __launch_bounds__(T) k_csr_small(const CsrSmall a) {
+  constexpr int W = T / 64, U = 2;
+  __shared__ unsigned s_ptr[CAPN + 1];     // packed degrees, then packed rowptr | srcptr << 16
+  __shared__ unsigned short s_graph[CAPN]; // node -> graph
+  // 10 bytes an edge: first the endpoints as loaded and graph_ptr, later
+  __shared__ __attribute__((aligned(16))) unsigned s_edge[CAPE * 5 / 2];
+  unsigned *s_key = s_edge; // source << 16 | edge id, by CSR position
+  // by CSR position, unordered in a segment: its destination; by source,
+  // unordered: CSR positions, and the source of each
+  unsigned short *s_dst = reinterpret_cast<unsigned short *>(s_edge + CAPE);
+  unsigned short *s_out = s_dst + CAPE, *s_src = s_out + CAPE;
+  int *s_es = reinterpret_cast<int *>(s_edge), *s_gp = s_es + 2 * CAPE;
+  __shared__ unsigned s_w[W];
+  __shared__ int s_bw[W][kMaxBuckets], s_tot[kMaxBuckets], s_bef[kMaxBuckets];
+  __shared__ int s_err, s_lo, s_hi, s_base, s_total;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int N = a.set ? a.N : a.dims->N;
+  const bool alone = gridDim.x == 1;
+  const int part = blockIdx.x;
+  if (part >= a.parts) {
+    const bool fin = pad_rows(a, N, (part - a.parts) * T + tid, ((int)gridDim.x - a.parts) * T);
+    const int bits = __syncthreads_or(!fin) ? ERR_NONFINITE : 0;
+    if (tid == 0) a.c.err[blockIdx.x] = bits;
+    return;
+  }
+  const int B = a.set ? a.B : a.dims->B, E = a.set ? a.E : a.dims->E;
+  const int nb = a.c.nb;
+  const int *s_ed = s_es + E;
+  // both rows of the edge list, as one run of 2 E words
+  constexpr int V = CAPE / (2 * T);
+  i4 ev[V];
+#pragma unroll
+  for (int u = 0; u < V; ++u) {
+    const int k = 4 * (tid + u * T);
+    if (k + 4 <= 2 * E) ev[u] = *reinterpret_cast<const i4 *>(a.ei + k);
+  }
+  if (tid < (2 * E & 3)) s_es[(2 * E & ~3) + tid] = a.ei[(2 * E & ~3) + tid];
+#pragma unroll 1
+  for (int k = tid; k <= B; k += T) s_gp[k] = a.graph_ptr[k];
+#pragma unroll 1
+  for (int i = tid; i < N; i += T) {
+    s_ptr[i] = 0;
+    s_graph[i] = 0;
+  }
+  if (tid < kMaxBuckets) s_tot[tid] = s_bef[tid] = 0;
+  if (tid == 0) {
+    s_err = s_base = s_total = 0;
+    s_lo = part ? N : 0;
+    s_hi = N;
+    if (a.set && part == 0) *a.dims = Dims{B, N, E, 0};
+  }
+  int bad = 0;
+  if (alone && a.x && !pad_rows(a, N, tid, T)) bad |= ERR_NONFINITE;
+#pragma unroll
+  for (int u = 0; u < V; ++u) {
+    const int k = 4 * (tid + u * T);
+    if (k + 4 <= 2 * E) *reinterpret_cast<i4 *>(s_es + k) = ev[u];
+  }
+  __syncthreads();
+
+  // own nodes: from the first graph that begins at or after part step to the
+  // next part's; node -> graph, eight lanes to a graph
+#pragma unroll 1
+  for (int b = tid; b <= B; b += T) {
+    const int g = s_gp[b], g1 = b ? s_gp[b - 1] : -1;
+    if (g1 >= g || (b == 0 && g != 0) || (b == B && g != N)) bad |= ERR_GRAPH_PTR;
+    const int t_lo = part * a.step, t_hi = t_lo + a.step;
+    if (part && g1 < t_lo && g >= t_lo) s_lo = g;
+    if (g1 < t_hi && g >= t_hi) s_hi = g;
+  }
+#pragma unroll 1
+  for (int b = tid >> 3; b < B; b += T / 8) {
+    const int i0 = max(s_gp[b], 0), i1 = min(s_gp[b + 1], N);
+#pragma unroll 1
+    for (int i = i0 + (tid & 7); i < i1; i += 8) s_graph[i] = (unsigned short)b;
+  }
+  // with a malformed graph_ptr no edge counts (and one workgroup owns all)
+  const bool ok = !__syncthreads_or(bad & ERR_GRAPH_PTR);
+  const int lo = ok ? s_lo : (part ? N : 0), hi = ok ? s_hi : N;
+
+  // degrees: everyone's in-degree, own nodes' out-degree
+  int total = 0, base = 0;
+#pragma unroll 1
+  for (int k = tid; k - tid < E; k += T) {
+    const int s = s_es[k], d = s_ed[k];
+    const bool in = s >= 0 && s < N && d >= 0 && d < N;
+    bool live = k < E;
+    if (live && !in) bad |= ERR_EDGE_RANGE;
+    live = live && in;
+    if (live && (!ok || s_graph[s] != s_graph[d])) {
+      bad |= ERR_EDGE_CROSS;
+      live = false;
+    }
+    if (live) {
+      const bool own = d >= lo && d < hi;
+      atomicAdd(&s_ptr[d], own && s == d ? 0x10001u : 1u);
+      if (own && s != d) atomicAdd(&s_ptr[s], 1u << 16);
+    }
+    total += __popcll(__ballot(live));
+    base += __popcll(__ballot(live && d < lo));
+  }
+  if (lane == 0) {
+    atomicAdd(&s_total, total);
+    atomicAdd(&s_base, base);
+  }
+  __syncthreads();
+
+  // nodes of every degree, and those before the own ones (lane q: bucket q)
+  if (nb) {
+    // a lane's nodes of bucket q in bits 4 q of h, those before in hb (at most
+    // CAPN / T = 6 a lane)
+    static_assert(CAPN / T < 16, "four bits a bucket");
+    unsigned long long h = 0, hb = 0;
+#pragma unroll 1
+    for (int i = tid; i < N; i += T) {
+      const unsigned long long one =
+          1ull << (4 * bucket_of((int)(s_ptr[i] & 0xffffu), a.max_degree));
+      h += one;
+      hb += i < lo ? one : 0ull;
+    }
+#pragma unroll 1
+    for (int q = 0; q < nb; ++q) {
+      const unsigned both = wave_add_scan((unsigned)(h & 15u) | (unsigned)(hb & 15u) << 16);
+      if (lane == 63) {
+        atomicAdd(&s_tot[q], (int)(both & 0xffffu));
+        atomicAdd(&s_bef[q], (int)(both >> 16));
+      }
+      h >>= 4;
+      hb >>= 4;
+    }
+    __syncthreads();
+  }
+  // lane q: the first row of bucket q
+  const int bt = lane < nb ? s_tot[lane] : 0;
+  const int brow = (int)wave_add_scan((unsigned)bt) - bt;
+  if (part == 0) {
+    if (wid == 0 && nb && lane <= nb) a.c.brow[lane] = brow;
+    if (tid == 0) a.c.rowptr[N] = a.c.srcptr[N] = s_total;
+  }
+
+  // own nodes' offsets
+  unsigned carry = (unsigned)s_base * 0x10001u;
+#pragma unroll 1
+  for (int i0 = lo; i0 < hi; i0 += T) {
+    const int i = i0 + tid;
+    const unsigned deg = i < hi ? s_ptr[i] : 0u;
+    const unsigned inc = wave_add_scan(deg);
+    const int vi = (int)(deg & 0xffffu), vo = (int)(deg >> 16);
+    const int bq = i < hi ? bucket_of(vi, a.max_degree) : -1;
+    int rank = 0, count = 0;
+#pragma unroll 1
+    for (int q = 0; q < nb; ++q) {
+      const unsigned long long m = __ballot(bq == q);
+      if (lane == q) count = __popcll(m);
+      if (bq == q) rank = __popcll(m & ((1ull << lane) - 1ull));
+    }
+    if (lane < nb) s_bw[wid][lane] = count;
+    if (lane == 63) s_w[wid] = inc;
+    __syncthreads();
+    const unsigned tot = lane < W ? s_w[lane] : 0u; // lane w: wave w's sum
+    const unsigned upto = wave_add_scan(tot);
+    const unsigned before = (unsigned)__builtin_amdgcn_readlane((int)(upto - tot), wid);
+    const unsigned all = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
+    if (i < hi) {
+      const unsigned ptr = carry + before + inc - deg;
+      s_ptr[i] = ptr;
+      a.c.node_graph[i] = s_graph[i];
+      a.c.rowptr[i] = (int)(ptr & 0xffffu);
+      a.c.srcptr[i] = (int)(ptr >> 16);
+      a.c.deg[i] = vi;
+      a.c.sp[i] = a.table[2 * bq];
+      a.c.sm[i] = a.table[2 * bq + 1];
+      if (vi > a.max_degree || vo > a.max_degree) bad |= ERR_DEGREE;
+    }
+    if (nb) {
+      int p = __shfl(brow, bq < 0 ? 0 : bq, 64) + rank;
+      if (i < hi) {
+        p += s_bef[bq];
+#pragma unroll 1
+        for (int w = 0; w < wid; ++w) p += s_bw[w][bq];
+        a.c.perm[p] = i;
+      }
+    }
+    carry += all;
+    __syncthreads();
+    if (nb && i0 + T < hi) { // the next nodes' bucket places
+      if (tid < nb)
+#pragma unroll 1
+        for (int w = 0; w < W; ++w) s_bef[tid] += s_bw[w][tid];
+      __syncthreads();
+    }
+  }
+  if (tid == 0) s_ptr[hi] = carry; // past the own nodes: degrees no longer needed
+  __syncthreads();
+  const int p_lo = s_base, p_hi = (int)(s_ptr[hi] & 0xffffu);
+
+  // place the own edges: the low half of s_ptr counts up to the segment's end
+  if (p_hi > p_lo) {
+#pragma unroll 1
+    for (int k0 = tid; k0 - tid < E; k0 += U * T) {
+      int s[U], d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(k0 + u * T, E - 1);
+        s[u] = a.ei[k];
+        d[u] = a.ei[E + k];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k0 + u * T < E && d[u] >= lo && d[u] < hi && s[u] >= lo && s[u] < hi &&
+            s_graph[s[u]] == s_graph[d[u]]) {
+          const unsigned p = atomicAdd(&s_ptr[d[u]], 1u) & 0xffffu;
+          s_key[p] = (unsigned)s[u] << 16 | (unsigned)(k0 + u * T);
+          s_dst[p] = (unsigned short)d[u];
+        }
+    }
+  }
+  __syncthreads();
+  // order the segments; s_ptr[d] now holds a segment's end, and the one before
+  // it its begin.  Longer ones than max_degree (an error) stay unordered.
+#pragma unroll 1
+  for (int p = p_lo + tid; p < p_hi; p += T) {
+    const unsigned key = s_key[p];
+    const int d = s_dst[p], k = (int)(key & 0xffffu), s = (int)(key >> 16);
+    const int p0 = d > lo ? (int)(s_ptr[d - 1] & 0xffffu) : p_lo;
+    const int n = (int)(s_ptr[d] & 0xffffu) - p0;
+    int pos = p;
+    if (n <= a.max_degree) {
+      pos = p0;
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) pos += s_key[p0 + j] < key;
+    }
+    a.c.csr_eid[pos] = k;
+    a.c.csr_src[pos] = s;
+    a.c.csr_dst[pos] = d;
+#pragma unroll 1
+    for (int f = 0; f < a.Fe; ++f) {
+      const float v = a.edge_attr[(size_t)k * a.Fe + f];
+      if (!isfinite(v)) bad |= ERR_NONFINITE;
+      a.c.csr_e[(size_t)pos * a.Fe + f] = v;
+    }
+    const unsigned q = atomicAdd(&s_ptr[s], 1u << 16) >> 16;
+    s_out[q] = (unsigned short)pos;
+    s_src[q] = (unsigned short)s;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int q = p_lo + tid; q < p_hi; q += T) {
+    const int pos = s_out[q], s = s_src[q];
+    const int q0 = s > lo ? (int)(s_ptr[s - 1] >> 16) : p_lo;
+    const int n = (int)(s_ptr[s] >> 16) - q0;
+    int r = q;
+    if (n <= a.max_degree) {
+      r = q0;
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) r += (int)s_out[q0 + j] < pos;
+    }
+    a.c.t2csr[r] = pos;
+  }
+  if (bad) atomicOr(&s_err, bad);
+  __syncthreads();
+  if (tid == 0) a.c.err[blockIdx.x] = s_err;
+  if (part == 0 && tid < kErrWords && tid >= (int)gridDim.x) a.c.err[tid] = 0;
+}
+
+// Batches the one-launch build takes, by capacity: 0 none, 1 with 256 threads
+// (16-wave barriers and their launch cost a molecule 3 us more), 2 with 1024.
+inline int small_class(int B, int N, int E) {
+  if (N <= 256 && E <= 512 && B < 256) return 1;
+  if (N <= 6144 && E <= 12288 && B < 6144) return 2;
+  return 0;
+}
+
 inline int cdiv(long long a, int b) { return (int)((a + b - 1) / b); }
 
 } // namespace
 
-hipError_t launch_set_dims(Dims *d, int B, int N, int E, int *err, hipStream_t s) {
-  k_set_dims<<<1, 64, 0, s>>>(d, B, N, E, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_csr_build(const Dims *dims, int capB, int capN, int capE,
+hipError_t launch_csr_build(Dims *dims, bool set, int capB, int capN, int capE,
                             const int *graph_ptr, const int *edge_index,
                             const float *edge_attr, int Fe, int max_degree,
-                            const float *table, const CsrBufs &c, bool clear_err,
+                            const float *table, const CsrBufs &c,
                             const float *x, int F, float *xpad, int Fp, hipStream_t s) {
-  if (clear_err) k_set_dims<<<1, 64, 0, s>>>(nullptr, 0, 0, 0, c.err);
   // Fp is a multiple of 16 (whole 16-byte groups per padded row)
   if (x && Fp % 16) return hipErrorInvalidValue;
+  const long long pad = x ? (long long)capN * (Fp / 4) : 0;
+  const bool al16 = ((uintptr_t)edge_index & 15) == 0; // its rows are read 16 bytes at a time
+  if (const int cls = al16 ? small_class(capB, capN, capE) : 0) {
+    // up to 1024 edges one workgroup (nothing to split: 6 to 8 us), which also
+    // pads a small input; above, one per 512 edges (per 256 and per 1024 within
+    // 1.2 us of it from 2.3k to 9.6k edges)
+    const int T = cls == 1 ? 256 : 1024;
+    const int parts = capE <= 1024 ? 1 : cdiv(capE, 512);
+    const bool alone = parts == 1 && pad <= 4 * T;
+    const CsrSmall a{dims, set, capB, capN, capE, parts, cdiv(capN, parts), graph_ptr, edge_index, edge_attr, Fe,
+                     max_degree, table, c, x, F, xpad, Fp};
+    const dim3 grid(alone ? 1 : std::min<int>(kErrWords, parts + cdiv(pad, T)));
+    if (cls == 1) k_csr_small<256, 256, 512><<<grid, 256, 0, s>>>(a);
+    else k_csr_small<1024, 6144, 12288><<<grid, 1024, 0, s>>>(a);
+    return hipGetLastError();
+  }
+  k_set_dims<<<1, kErrWords, 0, s>>>(set ? dims : nullptr, capB, capN, capE, c.err);
   long long nt = capN > capB ? capN : capB;
   if (x && (long long)capN * (Fp / 4) > nt) nt = (long long)capN * (Fp / 4);
   k_csr_init<<<cdiv(nt > 0 ? nt : 1, kInitThreads), kInitThreads, 0, s>>>(

@@ -2,7 +2,7 @@
 // of hgnn_forward without the stored activations, for callers that cannot
 // allocate device memory (code under stream capture, tight serving loops).
 //
-// Its whole batch workspace -- the size header, the error word, the CSR
+// Its whole batch workspace -- the size header, the error words, the CSR
 // arrays, the padded input, two rotating layer outputs, one layer's messages
 // and aggregates, the head buffers and the split-K partials of the GEMMs --
 // is carved from one file-scope device array per GPU.  Host code never passes
@@ -11,8 +11,8 @@
 // and only that pointer is used.  Every call on one GPU shares the array and
 // it keeps the last call's contents; calls that overlap on one GPU (any
 // context, any stream) race.  Nothing in the workspace needs to start at
-// zero: the size header and the error word are written first by every call
-// and the CSR build clears its own counters.
+// zero: the size header and the error words are written by every call's CSR
+// build, which clears its own counters.
 #include "runtime.hpp"
 
 #include <mutex>
@@ -23,7 +23,8 @@ namespace hgnn {
 namespace {
 
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20; // 64 MiB per GPU
-constexpr size_t kHeaderBytes = 512; // Dims at 0, the error word at 256
+constexpr size_t kHeaderBytes = 512; // Dims at 0, the error words at 256
+static_assert(256 + kErrWords * sizeof(int) <= kHeaderBytes, "header");
 constexpr int kMaxDevices = 64;
 
 std::mutex g_mu;
@@ -89,11 +90,9 @@ int hgnn_forward_noalloc(hgnn_ctx *c, const hgnn_batch *b, float *pred, float *l
   ex.w.csr.err = reinterpret_cast<int *>(base + 256);
   hipStream_t s = (hipStream_t)stream;
   Work &w = ex.w;
-  e = launch_set_dims(ex.dims, b->num_graphs, b->num_nodes, b->num_edges, w.csr.err, s);
-  if (e == hipSuccess)
-    e = launch_csr_build(ex.dims, b->num_graphs, b->num_nodes, b->num_edges, b->graph_ptr,
-                         b->edge_index, b->edge_attr, c->Fe, c->maxd, c->table, w.csr,
-                         /*clear_err=*/false, b->x, c->F0, w.xpad, c->F0p, s);
+  e = launch_csr_build(ex.dims, /*set=*/true, b->num_graphs, b->num_nodes, b->num_edges,
+                       b->graph_ptr, b->edge_index, b->edge_attr, c->Fe, c->maxd, c->table, w.csr,
+                       b->x, c->F0, w.xpad, c->F0p, s);
   if (e != hipSuccess) return hip_fail(c, e, "csr build");
   ex.B = b->num_graphs;
   ex.N = b->num_nodes;
@@ -106,7 +105,7 @@ int hgnn_forward_noalloc(hgnn_ctx *c, const hgnn_batch *b, float *pred, float *l
   if (flags & HGNN_VALIDATE) {
     int bits = 0;
     e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(&bits, w.csr.err, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_err(w.csr.err, &bits);
     if (e != hipSuccess) return hip_fail(c, e, "validate");
     if (bits) return set_error(HGNN_EINVAL, decode_err(bits));
   }

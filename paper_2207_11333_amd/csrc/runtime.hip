@@ -601,6 +601,19 @@ int check_batch_host(hgnn_ctx *c, const hgnn_batch *b) {
   return HGNN_OK;
 }
 
+int union_err(const int *words) {
+  int bits = 0;
+  for (int i = 0; i < kErrWords; ++i) bits |= words[i];
+  return bits;
+}
+
+hipError_t read_err(const int *dev, int *bits) {
+  int words[kErrWords];
+  hipError_t e = hipMemcpy(words, dev, sizeof(words), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) *bits = union_err(words);
+  return e;
+}
+
 std::string decode_err(int bits) {
   std::string m = "malformed batch:";
   if (bits & ERR_GRAPH_PTR) m += " graph_ptr does not run from 0 to num_nodes or a graph is empty;";
@@ -622,11 +635,9 @@ int prepare(hgnn_ctx *c, Exec &ex, const hgnn_batch *b, int flags, hipStream_t s
   hipError_t e;
   {
     TimedLaunch tl(c, ex, SITE_CSR, s);
-    e = launch_set_dims(ex.dims, b->num_graphs, b->num_nodes, b->num_edges, w.csr.err, s);
-    if (e == hipSuccess)
-      e = launch_csr_build(ex.dims, b->num_graphs, b->num_nodes, b->num_edges, b->graph_ptr,
-                           b->edge_index, b->edge_attr, c->Fe, c->maxd, c->table, w.csr,
-                           /*clear_err=*/false, b->x, c->F0, w.xpad, c->F0p, s);
+    e = launch_csr_build(ex.dims, /*set=*/true, b->num_graphs, b->num_nodes, b->num_edges,
+                         b->graph_ptr, b->edge_index, b->edge_attr, c->Fe, c->maxd, c->table,
+                         w.csr, b->x, c->F0, w.xpad, c->F0p, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "csr build");
   ex.x_padded = true;
@@ -642,7 +653,7 @@ int prepare(hgnn_ctx *c, Exec &ex, const hgnn_batch *b, int flags, hipStream_t s
   if (flags & HGNN_VALIDATE) {
     int bits = 0;
     e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(&bits, w.csr.err, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_err(w.csr.err, &bits);
     if (e != hipSuccess) return hip_fail(c, e, "validate");
     if (bits) return fail(HGNN_EINVAL, decode_err(bits));
   }
@@ -1757,7 +1768,7 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
   HGNN_CALLOC(c->step_dev, 1);
   HGNN_CALLOC(c->table, 2 * (c->maxd + 1));
   HGNN_CALLOC(c->ex.dims, 1);
-  HGNN_CALLOC(c->ex.w.csr.err, 1);
+  HGNN_CALLOC(c->ex.w.csr.err, kErrWords);
   HGNN_CALLOC(c->part, part_max);
   if (part_u_max) HGNN_CALLOC(c->part_u, part_u_max);
   if (c->nb) HGNN_CALLOC(c->zscale, 2 * (size_t)zmax);
@@ -1870,7 +1881,7 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
   if (e == hipSuccess) e = hipMemset(c->adam_m, 0, c->P * sizeof(float));
   if (e == hipSuccess) e = hipMemset(c->adam_v, 0, c->P * sizeof(float));
   if (e == hipSuccess) e = hipMemset(c->step_dev, 0, sizeof(long long));
-  if (e == hipSuccess) e = hipMemset(c->ex.w.csr.err, 0, sizeof(int));
+  if (e == hipSuccess) e = hipMemset(c->ex.w.csr.err, 0, kErrWords * sizeof(int));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     hgnn_destroy(c);
@@ -1993,7 +2004,7 @@ int hgnn_check(hgnn_ctx *c, void *stream) {
   HGNN_GUARD(c);
   int bits = 0;
   hipError_t e = hipStreamSynchronize((hipStream_t)stream);
-  if (e == hipSuccess) e = hipMemcpy(&bits, c->ex.w.csr.err, sizeof(int), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = read_err(c->ex.w.csr.err, &bits);
   if (e != hipSuccess) return hip_fail(c, e, "check");
   if (bits) return fail(HGNN_EINVAL, decode_err(bits));
   return HGNN_OK;

@@ -180,6 +180,8 @@ namespace hgnn {
 
 int set_error(int code, const std::string &msg);
 int hip_fail(hgnn_ctx *c, hipError_t e, const char *what);
+int union_err(const int *words);                // of kErrWords words on the host
+hipError_t read_err(const int *dev, int *bits); // synchronises
 std::string decode_err(int bits);
 void serve_shutdown(hgnn_ctx *c);
 

@@ -109,7 +109,7 @@ struct Lane {
   hipEvent_t done = nullptr;
   int32_t *d_stage = nullptr, *h_stage = nullptr;
   int32_t *d_graph_ptr = nullptr, *d_ei = nullptr;
-  float *d_pred = nullptr, *h_out = nullptr; // h_out: B preds then the error word
+  float *d_pred = nullptr, *h_out = nullptr; // h_out: B preds then the error words
   std::vector<Req *> reqs;
   size_t bytes = 0;
   bool busy = false;
@@ -160,8 +160,8 @@ int run_batch(Server &S, Lane &ln, const Bucket &bk) {
   if (e != hipSuccess) return hip_fail(c, e, "serve pack");
   const float *x = reinterpret_cast<const float *>(ln.d_stage + S.lay.off_x);
   const float *ea = c->Fe ? reinterpret_cast<const float *>(ln.d_stage + S.lay.off_ea) : nullptr;
-  e = launch_csr_build(ex.dims, bk.B, bk.N, bk.E, ln.d_graph_ptr, ln.d_ei, ea, c->Fe, c->maxd,
-                       c->table, ex.w.csr, /*clear_err=*/true, nullptr, 0, nullptr, 0, s);
+  e = launch_csr_build(ex.dims, /*set=*/false, bk.B, bk.N, bk.E, ln.d_graph_ptr, ln.d_ei,
+                       ea, c->Fe, c->maxd, c->table, ex.w.csr, nullptr, 0, nullptr, 0, s);
   if (e != hipSuccess) return hip_fail(c, e, "serve csr build");
   const float *h = x;
   for (int l = 0; l < c->L; ++l) {
@@ -230,10 +230,10 @@ int launch_lane(Server &S, Lane &ln, int nb, int nn, int ne) {
     rc = run_batch(S, ln, bk);
     if (rc) return rc;
   }
-  // predictions, then the batch's error word in the slot after the largest bucket
+  // predictions, then the batch's error words after the largest bucket
   e = hipMemcpyAsync(ln.h_out, ln.d_pred, (size_t)nb * 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(ln.h_out + S.buckets.back().B, ln.ex.w.csr.err, 4,
+    e = hipMemcpyAsync(ln.h_out + S.buckets.back().B, ln.ex.w.csr.err, 4 * kErrWords,
                        hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipEventRecord(ln.done, s);
   if (e != hipSuccess) return hip_fail(c, e, "serve download");
@@ -243,7 +243,9 @@ int launch_lane(Server &S, Lane &ln, int nb, int nn, int ne) {
 void finish_lane(Server &S, Lane &ln, bool ok, const std::string &why) {
   int err_bits = 0;
   const int capB = S.buckets.back().B;
-  std::memcpy(&err_bits, ln.h_out + capB, 4);
+  int words[kErrWords];
+  std::memcpy(words, ln.h_out + capB, sizeof(words));
+  err_bits = union_err(words);
   std::lock_guard<std::mutex> g(S.mu);
   int off = 0;
   for (Req *r : ln.reqs) {
@@ -473,14 +475,14 @@ int hgnn_serve_start(hgnn_ctx *c, const hgnn_serve_config *cfg) {
     bool ok = hipStreamCreateWithFlags(&ln->stream, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&ln->done, hipEventDisableTiming) == hipSuccess &&
               hipMalloc((void **)&ln->ex.dims, sizeof(Dims)) == hipSuccess &&
-              hipMalloc((void **)&ln->ex.w.csr.err, 256) == hipSuccess &&
+              hipMalloc((void **)&ln->ex.w.csr.err, kErrWords * sizeof(int)) == hipSuccess &&
               hipMalloc((void **)&ln->d_stage, S->lay.words * 4) == hipSuccess &&
               hipMalloc((void **)&ln->d_graph_ptr, 4 * ((size_t)capB + 1)) == hipSuccess &&
               hipMalloc((void **)&ln->d_ei, 8 * (size_t)capE) == hipSuccess &&
               hipMalloc((void **)&ln->d_pred, 4 * (size_t)capB) == hipSuccess &&
               hipHostMalloc((void **)&ln->h_stage, S->lay.words * 4, hipHostMallocDefault) ==
                   hipSuccess &&
-              hipHostMalloc((void **)&ln->h_out, 4 * ((size_t)capB + 4), hipHostMallocDefault) ==
+              hipHostMalloc((void **)&ln->h_out, 4 * ((size_t)capB + kErrWords), hipHostMallocDefault) ==
                   hipSuccess;
     if (ok) ok = ensure_work(c, ln->ex, capB, capN, capE) == HGNN_OK;
     if (!ok) {
