@@ -30,6 +30,11 @@ def hipcc() -> str:
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          # packed FP32 instructions stay off (hipcc would otherwise form them)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # kernel arguments arrive in scalar registers with the wave: its first
+         # instruction needs no load of them (1 to 2 % of the steps that are
+         # bound by their launches: one molecule 107.4 -> 105.3 us, 6 x 128
+         # training at 4.5k nodes 605 -> 598)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-function", "-I", CSRC, "-I", INCLUDE]
 
 
