@@ -85,11 +85,13 @@ k_aggregate(const Dims *__restrict__ dims, int H, const float *__restrict__ PQ,
     amax = (uint32_t)imx[0] | ((uint32_t)imx[1] << 8) | ((uint32_t)imx[2] << 16) |
            ((uint32_t)imx[3] << 24);
   }
-  float *Ai = A + (size_t)i * 4 * H;
-  *reinterpret_cast<f4 *>(Ai + c) = mu;
-  *reinterpret_cast<f4 *>(Ai + H + c) = mn;
-  *reinterpret_cast<f4 *>(Ai + 2 * H + c) = mx;
-  *reinterpret_cast<f4 *>(Ai + 3 * H + c) = sd;
+  if (A) { // else only the copy is read
+    float *Ai = A + (size_t)i * 4 * H;
+    *reinterpret_cast<f4 *>(Ai + c) = mu;
+    *reinterpret_cast<f4 *>(Ai + H + c) = mn;
+    *reinterpret_cast<f4 *>(Ai + 2 * H + c) = mx;
+    *reinterpret_cast<f4 *>(Ai + 3 * H + c) = sd;
+  }
   if (Ab) { // the BF16 copy read by the BF16 update linear (RNE, as its staging rounds)
     __bf16 *Bi = Ab + (size_t)i * 4 * H;
     const f4 v[4] = {mu, mn, mx, sd};

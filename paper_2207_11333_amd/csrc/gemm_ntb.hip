@@ -281,7 +281,7 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         if (nok && rok[i][v]) {
-          g.C[(size_t)node[i][v] * g.ldc + n] = o[i][v];
+          if (g.C) g.C[(size_t)node[i][v] * g.ldc + n] = o[i][v];
           if (g.Cb) g.Cb[(size_t)node[i][v] * g.ldcb + n] = (__bf16)o[i][v];
         }
   }
@@ -303,7 +303,8 @@ bool large_tiles(int capM, const GemmNTB &g) {
 
 bool gemm_ntb_ok(const GemmNTB &g, int precision) {
   const int bke = precision ? 64 : 32, esz = precision ? 2 : 4;
-  if (g.nseg < 1 || g.nseg > kMaxSeg || !g.B || !g.C || g.Ncols <= 0) return false;
+  if (g.nseg < 1 || g.nseg > kMaxSeg || !g.B || !(g.C || g.Cb) || g.Ncols <= 0)
+    return false;
   if ((precision == 1) != (g.B_lo != nullptr) || (precision == 0 && g.Cb)) return false;
   if ((g.ldb * esz) % 16 || !al16(g.B) || (g.B_lo && !al16(g.B_lo))) return false;
   if (g.perm && (!g.brow || g.nb < 1 || (g.bstride * esz) % 16)) return false;

@@ -114,7 +114,7 @@ int hgnn_forward_noalloc(hgnn_ctx *c, const hgnn_batch *b, float *pred, float *l
   const float *h = b->x;
   for (int l = 0; l < c->L; ++l) {
     float *out = w.hbuf[l & 1];
-    if (int rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, out, s)) return rc;
+    if (int rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, out, s, /*lean=*/true)) return rc;
     h = out;
   }
   return head_forward(c, ex, c->params + c->off_head, h, b->y, pred, loss, s);

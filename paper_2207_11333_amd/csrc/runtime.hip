@@ -90,6 +90,12 @@ int tn_splits(int M, int Ncols, int precision) {
 
 void free_work(Exec &ex) {
   Work &w = ex.w;
+  if (w.shared_A) { // these lie in A[0]
+    w.hbuf[1] = nullptr;
+    w.hbuf_b[1] = nullptr;
+    w.Ab = nullptr;
+    w.shared_A = false;
+  }
   void **ptrs[] = {(void **)&w.csr.rowptr, (void **)&w.csr.csr_src, (void **)&w.csr.csr_eid,
                    (void **)&w.csr.deg, (void **)&w.csr.srcptr, (void **)&w.csr.t2csr,
                    (void **)&w.csr.node_graph, (void **)&w.csr.cnt_in,
@@ -355,11 +361,12 @@ static bool for_each_buffer(const hgnn_ctx *c, Work &w, int capB, int capN, int 
   ok = ok && f(w.csr.scan, (size_t)((capN + kScanNodes - 1) / kScanNodes) * kScanRec);
   if (w.csr.nb) ok = ok && f(w.csr.perm, (size_t)capN) && f(w.csr.brow, (size_t)kMaxBuckets + 1);
   if (w.hbuf.size() != (size_t)nh) w.hbuf.assign(nh, nullptr);
-  for (int l = 0; l < nh && ok; ++l) ok = f(w.hbuf[l], (size_t)capN * H);
-  const bool shadows = !inference && bf16_copies(c);
+  const bool shadows = bf16_copies(c), shared = shadows && inference;
+  const int nown = shared ? 1 : nh;
+  for (int l = 0; l < nown && ok; ++l) ok = f(w.hbuf[l], (size_t)capN * H);
   if (w.hbuf_b.size() != (size_t)(shadows ? nh : 0)) w.hbuf_b.assign(shadows ? nh : 0, nullptr);
-  for (int l = 0; l < (int)w.hbuf_b.size() && ok; ++l) ok = f(w.hbuf_b[l], (size_t)capN * H);
-  if (shadows) ok = ok && f(w.Ab, (size_t)capN * 4 * H);
+  for (int l = 0; shadows && l < nown && ok; ++l) ok = f(w.hbuf_b[l], (size_t)capN * H);
+  if (shadows && !shared) ok = ok && f(w.Ab, (size_t)capN * 4 * H);
   const bool pna = c->kind == HGNN_GC_PNA;
   if (pna) {
     if (w.PQ.size() != (size_t)nstore) {
@@ -371,6 +378,15 @@ static bool for_each_buffer(const hgnn_ctx *c, Work &w, int capB, int capN, int 
     for (int l = 0; l < nstore && ok; ++l)
       ok = f(w.PQ[l], (size_t)capN * 2 * H) && f(w.A[l], (size_t)capN * 4 * H) &&
            (inference || f(w.args[l], (size_t)capN * 2 * H));
+    if (ok && shared && w.A[0]) {
+      // Inference reads FP32 aggregates in layer 0 alone: their room then holds
+      // the BF16 ones and the odd layers' outputs (3.5 of its 4 H floats a
+      // node), so that the copies cost no memory.
+      w.Ab = reinterpret_cast<__bf16 *>(w.A[0]);
+      w.hbuf[1] = w.A[0] + (size_t)capN * 2 * H;
+      w.hbuf_b[1] = reinterpret_cast<__bf16 *>(w.hbuf[1] + (size_t)capN * H);
+      w.shared_A = true;
+    }
   } else {
     if (w.gcA.size() != (size_t)L) w.gcA.assign(L, nullptr);
     for (int l = 0; l < L && ok; ++l) {
@@ -680,11 +696,16 @@ static int aggregate_into(hgnn_ctx *c, Exec &ex, int l, const float *wl, const f
 // The BF16 copy of layer l's input when the context holds one: the input is
 // the previous layer's output buffer, written together with its copy.
 static bool copies_on(const Exec &ex) { return !ex.w.hbuf_b.empty(); }
-static const __bf16 *input_copy(const Exec &ex, int l, const float *h_in) {
+// the slot of layer l's output among hbuf / hbuf_b (inference rotates two)
+static size_t out_slot(const Exec &ex, int l) { return ex.inference_only ? l & 1 : l; }
+static __bf16 *copy_of(const Exec &ex, int l, const float *h) {
   const Work &w = ex.w;
-  return (copies_on(ex) && l > 0 && (size_t)l <= w.hbuf_b.size() && h_in == w.hbuf[l - 1])
-             ? w.hbuf_b[l - 1]
-             : nullptr;
+  if (!copies_on(ex) || l < 0) return nullptr;
+  const size_t k = out_slot(ex, l);
+  return k < w.hbuf_b.size() && h == w.hbuf[k] ? w.hbuf_b[k] : nullptr;
+}
+static const __bf16 *input_copy(const Exec &ex, int l, const float *h_in) {
+  return copy_of(ex, l - 1, h_in);
 }
 
 // Layer l: S1 (P|Q GEMM), S2 (aggregation) into the given buffers.
@@ -752,7 +773,7 @@ static const float *layer_input(hgnn_ctx *c, Exec &ex, int l, const float *h_in,
 }
 
 int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_in, float *h_out,
-                  hipStream_t s) {
+                  hipStream_t s, bool lean) {
   if (int rc = injected_failure(c)) return rc;
   const LayerDesc &d = c->ld[l];
   const int H = c->H;
@@ -764,14 +785,14 @@ int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_
   // BF16 copies: of this layer's input (layers 1..), of its aggregates (for
   // the update linear) and of its output (for the next layer)
   const __bf16 *hb = input_copy(ex, l, h_in);
-  __bf16 *hb_out =
-      (copies_on(ex) && (size_t)l < w.hbuf_b.size() && h_out == w.hbuf[l]) ? w.hbuf_b[l] : nullptr;
-  rc = message_and_aggregate(c, ex, l, wl, hin, ldh, w.PQ[slot], w.A[slot],
-                             ex.inference_only ? nullptr : w.args[slot], s, hb,
-                             hb ? w.Ab : nullptr);
+  __bf16 *hb_out = copy_of(ex, l, h_out);
+  // lean: the update linear is the aggregates' last reader, and takes them from
+  // the copy where there is one
+  float *A = lean && hb ? nullptr : w.A[slot];
+  rc = message_and_aggregate(c, ex, l, wl, hin, ldh, w.PQ[slot], A,
+                             lean ? nullptr : w.args[slot], s, hb, hb ? w.Ab : nullptr);
   if (rc) return rc;
-  w.stored_layer = l;
-  float *A = w.A[slot];
+  w.stored_layer = lean ? -1 : l;
   // u = [h || A] [W_h | W_eff(d)]^T per bucket in the LDS-DMA form where it
   // applies: FP32 on the inputs as they lie, BF16 on their copies
   GemmNTB q{};
@@ -794,7 +815,8 @@ int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_
     q.Ncols = H;
     q.bias = wl + (d.obp - d.off);
     q.relu = 1;
-    q.C = h_out;
+    // between two layers of inference only the copy is read
+    q.C = ex.inference_only && hb && hb_out && l + 1 < c->L ? nullptr : h_out;
     q.ldc = H;
     q.Cb = hb_out;
     q.ldcb = H;
@@ -809,6 +831,7 @@ int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_
     if (e != hipSuccess) return hip_fail(c, e, "update GEMM");
     return HGNN_OK;
   }
+  if (!A) return set_error(HGNN_EDEVICE, "update linear without aggregates");
   GemmNT g{};
   g.Cb = hb_out;
   g.ldcb = H;
@@ -2052,7 +2075,8 @@ int hgnn_forward_multitask(hgnn_ctx *c, const hgnn_batch *b, const float *y_node
     if (rc) return rc;
   } else {
     for (int l = 0; l < c->L; ++l) {
-      rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, c->ex.w.hbuf[l], s);
+      rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, c->ex.w.hbuf[l], s,
+                         /*lean=*/c->recompute && l + 1 < c->L);
       if (rc) return rc;
       h = c->ex.w.hbuf[l];
     }

@@ -24,9 +24,10 @@ struct Work {
   float *xpad = nullptr;                 // [N, F0p] padded layer-0 input
   std::vector<float *> hbuf;             // [L] layer outputs [N, H]
   // BF16 copies of the layer outputs [L][N, H] and of one layer's aggregates
-  // [N, 4H], read by the BF16 linears (gemm_ntb.hip); training batches of
-  // bucketed BF16 PNA models only (empty / null otherwise)
+  // [N, 4H], read by the BF16 linears (gemm_ntb.hip); bucketed BF16 PNA models
+  // only (empty / null otherwise).  Inference: two rotating outputs.
   std::vector<__bf16 *> hbuf_b;
+  bool shared_A = false; // Ab, hbuf[1] and hbuf_b[1] lie in A[0]
   __bf16 *Ab = nullptr;
   std::vector<float *> PQ, A;            // [L] (or 1 with recompute)
   std::vector<uint8_t *> args;
@@ -197,8 +198,11 @@ int check_batch_host(hgnn_ctx *c, const hgnn_batch *b);
 int noalloc_init(int dev);
 void free_work(Exec &ex);
 size_t work_bytes(const hgnn_ctx *c, int B, int N, int E, bool inference_only);
+// lean: nothing reads the layer's aggregates and arg decisions afterwards
+// (inference; recomputation, except for the last layer, whose backward step
+// comes next)
 int layer_forward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_in,
-                  float *h_out, hipStream_t s);
+                  float *h_out, hipStream_t s, bool lean = false);
 // graph heads, node heads (fused path: pred_node/ynode), weighted loss
 int head_forward(hgnn_ctx *c, Exec &ex, const float *wh, const float *h,
                  const float *target, float *pred, float *loss, hipStream_t s,

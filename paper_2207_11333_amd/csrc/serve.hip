@@ -166,7 +166,7 @@ int run_batch(Server &S, Lane &ln, const Bucket &bk) {
   const float *h = x;
   for (int l = 0; l < c->L; ++l) {
     float *out = ex.w.hbuf[l & 1];
-    int rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, out, s);
+    int rc = layer_forward(c, ex, l, c->params + c->ld[l].off, h, out, s, /*lean=*/true);
     if (rc) return rc;
     h = out;
   }
