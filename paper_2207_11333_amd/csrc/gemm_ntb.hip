@@ -37,12 +37,15 @@
 // row tile) BF16 update 9.1 -> 7.8 us.  128 x 128 tiles, whose products
 // are longer, gained nothing (105 us BF16 update at 40k rows).
 //
-// Two tile shapes: 128 x 128 (waves of 64 x 32) for grids that fill the GPU,
-// 64 x 64 (waves of 32 x 16) for smaller ones, whose time is set by how many
-// tiles run at once.  Eight waves in both.  Stages: five for the 64 x 64
-// tiles of the forward pass, which run alone; three where another kernel
-// needs LDS on the same CU (the layer-input gradient, beside the weight
-// gradients) and for 128 x 128 (144 KB in BF16).
+// Three tile shapes: 128 x 128 (waves of 64 x 32) for grids that fill the GPU,
+// 64 x 64 (32 x 16) and 32 x 32 (16 x 16, four waves) for smaller ones, whose
+// time is set by how many tiles run at once (tile_side).  FP32's matrix
+// instructions bound a small grid: a 64 x 64 tile of the update linear (K = 640)
+// is 9 us of them on its CU, whatever the other CUs do.  Stages: three for
+// 128 x 128 (144 KB in BF16), for 32 x 32 (24 or 36 KB: several share a CU; rings
+// of four to ten were slower, 9.2 to 17 us for the BF16 update linear at 4.5k
+// rows) and where another kernel needs LDS on the same CU (the layer-input
+// gradient, beside weight gradients); five for the other 64 x 64 tiles.
 //
 // Products and their order per output are those of the register-staged
 // kernel when it runs unsplit (FP32: per 16 k, four k-slots of
@@ -57,7 +60,8 @@ namespace {
 typedef __attribute__((address_space(3))) void lds_t;
 
 constexpr int kQRow = 128; // bytes per LDS row (one K tile)
-constexpr int kQWGM = 2, kQWGN = 4; // waves of a workgroup
+constexpr int kQWGM = 2; // waves of a workgroup: kQWGM x waves_n
+constexpr int waves_n(int tile) { return tile == 32 ? 2 : 4; }
 
 // PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo.
 // BM x BN tile, WGM x WGN waves, NST LDS stages.
@@ -291,12 +295,22 @@ inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // LDS stages (160 KB of LDS per CU; see the head of this file)
 constexpr int stages(int prec, int tile, int tag) {
-  return tile == 64 ? (tag == 4 ? 3 : 5) : 3;
+  return tile == 64 && tag != 4 ? 5 : 3;
 }
 
-// the large tile when its grid fills every CU at least once
-bool large_tiles(int capM, const GemmNTB &g) {
-  return (long long)(cdiv(capM, 128) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, 128) >= 256;
+// Tile side by the grid it gives: 128 when that fills every CU at least once; 64
+// when its rounds over the 256 CUs are at least 0.8 full; else 32, whose tiles
+// are a quarter of the work (and more of them share a CU), at twice the operand
+// traffic.  Update linear of H = 128, FP32, 64 against 32: 1.1k nodes (23 of 256
+// CUs busy) 11.3 -> 6.8 us, 4.5k (150) 17.9 -> 15.1, 8.9k (290: a second round
+// for 34) 28.9 -> 23.3, but 15.7k (502) 31.5 -> 35.1.
+int tile_side(int capM, const GemmNTB &g) {
+  auto grid = [&](int B) {
+    return (long long)(cdiv(capM, B) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, B);
+  };
+  if (grid(128) >= 256) return 128;
+  const long long n = grid(64), rounds = (n + 255) / 256;
+  return 10 * n >= 8 * 256 * rounds ? 64 : 32;
 }
 
 } // namespace
@@ -322,18 +336,20 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
                            hipStream_t s, int tag, hipEvent_t ev0, hipEvent_t ev1) {
   if (capM <= 0) return hipSuccess;
   if (!gemm_ntb_ok(g, precision)) return hipErrorInvalidValue;
-  const int B = large_tiles(capM, g) ? 128 : 64;
+  const int B = tile_side(capM, g);
   const int nt = cdiv(g.Ncols, B);
   // bucketed rows: each bucket's last tile may be partial
-  const dim3 grid((cdiv(capM, B) + (g.perm ? g.nb : 0)) * nt), block(64 * kQWGM * kQWGN);
+  const dim3 grid((cdiv(capM, B) + (g.perm ? g.nb : 0)) * nt), block(64 * kQWGM * waves_n(B));
   const int key = precision * 1000 + B * 10 + tag;
   switch (key) {
 #define HGNN_NTB(P, BB, T)                                                                     \
   case P * 1000 + BB * 10 + T:                                                                 \
-    hipExtLaunchKernelGGL((k_gemm_ntb<P, BB, BB, kQWGM, kQWGN, stages(P, BB, T), T>), grid, block, \
-                          0, s, ev0, ev1, 0, dims, g, nt);                                     \
+    hipExtLaunchKernelGGL((k_gemm_ntb<P, BB, BB, kQWGM, waves_n(BB), stages(P, BB, T), T>),    \
+                          grid, block, 0, s, ev0, ev1, 0, dims, g, nt);                        \
     break;
 #define HGNN_NTB_TAGS(P, BB) HGNN_NTB(P, BB, 0) HGNN_NTB(P, BB, 1) HGNN_NTB(P, BB, 2) HGNN_NTB(P, BB, 4)
+    HGNN_NTB_TAGS(0, 32)
+    HGNN_NTB_TAGS(1, 32)
     HGNN_NTB_TAGS(0, 64)
     HGNN_NTB_TAGS(0, 128)
     HGNN_NTB_TAGS(1, 64)

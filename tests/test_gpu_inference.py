@@ -59,3 +59,31 @@ def test_recomputation_equals_stored(prec, H, L, graphs):
         m.close()
     assert np.array_equal(got[0][0], got[1][0])
     assert np.array_equal(got[0][1], got[1][1])
+
+
+# BF16 linears sum in one order whatever tile they run on (128, 64 or 32 a side,
+# by the size of the grid), so a graph's prediction does not depend on what else
+# is in its batch
+@pytest.mark.parametrize("H,graphs,lo,hi", [(128, 700, 58, 62), (128, 300, 50, 60),
+                                            (256, 130, 20, 60), (64, 500, 20, 60)])
+def test_prediction_independent_of_the_batch(H, graphs, lo, hi):
+    b = synth.make_batch(51, graphs, lo, hi, 1)
+    m = _hg().Model(3, H, 9, 1, 4, 1, 0, 1.08)
+    m.set_params(synth.init_params(synth.ModelShape(3, H, 9, 1), 52))
+
+    def pred(x):
+        p = torch.empty(x.num_graphs, device="cuda")
+        m.forward(_hg().DeviceBatch.from_host(x), p)
+        return p.cpu().numpy()
+
+    whole = pred(b)
+    at = 0
+    for n in (1, 20, 40, graphs - 61):
+        n0, n1 = b.graph_ptr[at], b.graph_ptr[at + n]
+        e = (b.edge_index[1] >= n0) & (b.edge_index[1] < n1)
+        part = synth.Batch((b.graph_ptr[at:at + n + 1] - n0).astype(np.int32), b.x[n0:n1].copy(),
+                           (b.edge_index[:, e] - n0).astype(np.int32), b.edge_attr[e].copy(),
+                           b.y[at:at + n].copy())
+        assert np.array_equal(pred(part), whole[at:at + n])
+        at += n
+    m.close()
