@@ -136,6 +136,11 @@ struct GemmNTB {
   __bf16 *Cb; // BF16 only: optional BF16 copy of C (the same values rounded), or nullptr
   int ldcb;
   int M_fixed;
+  const float *addend; // as in GemmNT
+  int ld_add;
+  // FP32, > 1: sum K as split-K would, in this many chunks of whole 64-deep
+  // pieces, each from zero, added in the order of reduce.hip
+  int chunks;
 };
 bool gemm_ntb_ok(const GemmNTB &g, int precision);
 hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int precision,

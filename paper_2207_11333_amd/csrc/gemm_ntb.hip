@@ -70,6 +70,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 1)
 k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   using T = typename Prec<PREC>::T;
   constexpr bool SPLIT = PREC == 1;
+  constexpr bool FOLD = PREC == 0 && BM < 128; // chunked sums: small FP32 grids only
   constexpr int ESZ = (int)sizeof(T);
   constexpr int BKE = kQRow / ESZ; // k per K tile
   constexpr int NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
@@ -201,6 +202,29 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  // chunked sums (g.chunks > 1): chunk z holds K tiles [KT z / chunks ..) in
+  // pairs; tot adds the finished ones, with more than four as two halves
+  f4 tot[FOLD ? 2 : 1][TM][TN];
+  int z = 0, z_end = KT, z_half = 0;
+  if constexpr (FOLD) {
+    if (g.chunks > 1) {
+      z_end = 2 * (KT / 2 / g.chunks);
+      z_half = g.chunks > 4 ? (g.chunks + 1) / 2 : g.chunks;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) tot[0][i][j] = tot[1][i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  auto fold = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if (z < z_half) tot[0][i][j] += acc[i][j];
+        else tot[FOLD][i][j] += acc[i][j];
+      }
+  };
   auto mm = [&](const V (&a)[TM], const V (&b)[TN]) { mma_frags<PREC, TM, TN>(a, b, acc); };
   auto next = [](int st) { return st == (NST - 1) * STAGE ? 0 : st + STAGE; };
 
@@ -209,6 +233,17 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   // tile t + 1's fragments; then the last products
   auto step = [&](auto set, int t, int st) {
     constexpr int S = decltype(set)::value;
+    if constexpr (FOLD) {
+      if (t == z_end) { // a chunk is complete
+        fold();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        ++z;
+        z_end = 2 * (KT / 2 * (z + 1) / g.chunks);
+      }
+    }
     mm(fa[S][0], fb[S][0]);
     if constexpr (SPLIT) {
       mm(fa[S][1], fb[S][1]);
@@ -241,6 +276,17 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     st = next(st);
   }
 
+  if constexpr (FOLD) {
+    if (g.chunks > 1) {
+      fold();
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = g.chunks > 4 ? tot[0][i][j] + tot[1][i][j] : tot[0][i][j];
+    }
+  }
+
   // Epilogue (as the register-staged kernel's): lane (cr = 4 (L / 16),
   // cc = L % 16) holds rows wm0 + 16 i + cr + v, columns wn0 + 16 j + cc; the
   // rows' nodes are fetched once, from clamped indices, without a branch.
@@ -267,6 +313,12 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[i][v] = acc[i][j][v] + bias;
+    if (g.addend) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[i][v] += g.addend[(size_t)node[i][v] * g.ld_add + nc];
+    }
     if (g.relu) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -308,7 +360,7 @@ int tile_side(int capM, const GemmNTB &g) {
   auto grid = [&](int B) {
     return (long long)(cdiv(capM, B) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, B);
   };
-  if (grid(128) >= 256) return 128;
+  if (grid(128) >= 256 && g.chunks <= 1) return 128;
   const long long n = grid(64), rounds = (n + 255) / 256;
   return 10 * n >= 8 * 256 * rounds ? 64 : 32;
 }
@@ -327,8 +379,10 @@ bool gemm_ntb_ok(const GemmNTB &g, int precision) {
     const SegB &s = g.seg[q];
     if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esz) % 16 || s.boff != boff)
       return false;
+    if (g.chunks > 1 && s.k % 64) return false;
     boff += s.k;
   }
+  if (g.chunks > 1 && (precision || g.chunks > 8 || boff / 64 < g.chunks)) return false;
   return true;
 }
 

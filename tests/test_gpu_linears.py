@@ -1,0 +1,36 @@
+"""FP32 linears in chunks of K: the LDS-DMA form sums the chunks that split-K
+would launch.  Widths and batches that give one chunk, two to four (one running
+total), five to eight (two halves), and widths it leaves to the other form,
+against the FP64 oracle with the layer kinds' FP32 tolerance."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gclayers as gcl
+from paper_2207_11333_amd import synth
+from test_gpu_gclayers import TAU_FP32, _batch, _run, _tensor_report, rel, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind,H,B,lo,hi", [
+    ("sage", 64, 300, 20, 40),   # one chunk, 64-wide tiles
+    ("sage", 128, 1, 1, 1),      # two chunks, one row
+    ("sage", 192, 3, 20, 30),    # three
+    ("sage", 256, 2, 30, 33),    # four
+    ("sage", 320, 2, 31, 33),    # five
+    ("sage", 448, 2, 31, 32),    # seven
+    ("sage", 512, 4, 15, 17),    # eight
+    ("sage", 96, 20, 10, 30),    # not whole 64-deep pieces
+    ("cgcnn", 256, 3, 20, 30)])  # with an addend
+def test_chunked_sums(kind, H, B, lo, hi):
+    b = _batch(61, B, lo, hi, 1)
+    params = synth.init_gc_params(kind, 2, H, 62, edge_feat=1)
+    m, out = _run(kind, b, params, 2, H, 1)
+    rec = gcl.forward(params, b, kind, 2, H)
+    g_ref, _ = gcl.backward(rec, out["relu"], out["grelu"], None, tau=TAU_FP32)
+    rep = _tensor_report(kind, 2, H, 1, 1, 0, out["grads"], g_ref)
+    say(f"{kind} H={H} N={b.num_nodes}: worst gradient {max(rep.values()):.2e}")
+    assert rel(out["pred"], rec.y[:, 0]) <= 1e-5
+    assert max(rep.values()) <= 1e-5
+    m.close()
