@@ -427,6 +427,12 @@ hipError_t run_nt(const Dims *dims, int capM, const GemmNT &g, bool db, hipStrea
   return e;
 }
 
+// BF16 products of at most this many 64 x 128 tiles take the LDS-DMA form, whose
+// smaller tiles spread over more CUs (layer-input gradient of H = 128 at 4.5k
+// nodes, 71 tiles: 12.8 -> 8.4 us; at 9k, 140: 13.0 -> 12.2; at 12k, 192: 14.7
+// -> 15.6, so it stays here).
+constexpr int kNtSmallBf16 = 144;
+
 // Output tiles are 64 rows x 128 columns: one tile spans the whole hidden
 // width, so each weight tile is staged once per 64 rows.  When the tiles
 // alone cannot cover the 256 CUs, K is split (at least two K tiles per
@@ -483,19 +489,23 @@ hipError_t launch_gemm_nt(const Dims *dims, int capM, GemmNT g, int precision,
   if (g.splits > 1 && !partials) g.splits = 1;
   while (g.splits > 1 && (size_t)g.splits * capM * g.Ncols > nt_partial_floats(0, 0, 0, 0))
     --g.splits;
-  if (precision == 0 && tag != 3) {
+  const long long tiles = (long long)cdiv(capM, kNtBM) * cdiv(g.Ncols, kNtBN);
+  if (tag != 3 && (precision == 0 || tiles <= kNtSmallBf16)) {
     // FP32 operands that whole 32-deep K tiles cover: the LDS-DMA form, with the
     // same chunks of K (one launch, no partial sums in memory).  GraphSAGE of
     // H = 128 at 4.5k nodes: layer 12.5 us and its reduction 4.1 -> 8.4,
     // input gradient 11.8 -> 8.9
     GemmNTB q{};
-    bool plain = g.ileave_n == 0 && !g.Cb;
+    bool plain = g.ileave_n == 0 && (precision || !g.Cb);
     q.nseg = g.nseg;
     for (int k = 0; k < g.nseg; ++k) {
       plain = plain && !g.seg[k].scale;
       q.seg[k] = SegB{g.seg[k].ptr, g.seg[k].ld, g.seg[k].k, g.seg[k].boff};
     }
     q.B = g.B;
+    q.B_lo = g.B_lo;
+    q.Cb = g.Cb;
+    q.ldcb = g.ldcb;
     q.ldb = g.ldb;
     q.bstride = g.bstride;
     q.perm = g.perm;
@@ -511,7 +521,9 @@ hipError_t launch_gemm_nt(const Dims *dims, int capM, GemmNT g, int precision,
     q.addend = g.addend;
     q.ld_add = g.ld_add;
     q.chunks = g.splits;
-    if (plain && gemm_ntb_ok(q, 0)) return launch_gemm_ntb(dims, capM, q, 0, s, tag, ev0, ev1);
+    const int form = precision ? 2 : 0;
+    if (plain && gemm_ntb_ok(q, form))
+      return launch_gemm_ntb(dims, capM, q, form, s, tag, ev0, ev1);
   }
   const long long grid =
       (long long)(cdiv(capM, kNtBM) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, kNtBN) * g.splits;

@@ -3,8 +3,8 @@
 //
 // Every A segment is in the product's own precision in HBM: FP32 as it lies,
 // or for BF16 a copy its producer wrote (RNE-rounded, the rounding the
-// register-staged kernel applies while staging).  A K tile then needs no
-// conversion and goes from HBM to LDS by gfx950's LDS-DMA loads
+// register-staged kernel applies while staging); BF16 products of small grids
+// without a copy take FP32 and round it in registers.  A K tile goes from HBM to LDS by gfx950's LDS-DMA loads
 // (global_load_lds_dwordx4: 16 bytes per lane, written to LDS in lane order),
 // never through registers, which are left to the products.
 //
@@ -63,22 +63,23 @@ constexpr int kQRow = 128; // bytes per LDS row (one K tile)
 constexpr int kQWGM = 2; // waves of a workgroup: kQWGM x waves_n
 constexpr int waves_n(int tile) { return tile == 32 ? 2 : 4; }
 
-// PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo.
+// PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo; 2: as
+// 1 with FP32 operands, rounded when a tile's fragments are used.
 // BM x BN tile, WGM x WGN waves, NST LDS stages.
 template <int PREC, int BM, int BN, int WGM, int WGN, int NST, int TAG>
 __global__ void __launch_bounds__(64 * WGM * WGN, 1)
 k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
-  using T = typename Prec<PREC>::T;
-  constexpr bool SPLIT = PREC == 1;
+  constexpr bool SPLIT = PREC != 0, A32 = PREC == 2;
   constexpr bool FOLD = PREC == 0 && BM < 128; // chunked sums: small FP32 grids only
-  constexpr int ESZ = (int)sizeof(T);
+  constexpr int ESZ = SPLIT ? 2 : 4, ESA = PREC == 1 ? 2 : 4; // bytes of a weight, of an A element
+  constexpr int NAH = A32 ? 2 : 1; // A: rows of 128 bytes per K tile and row
   constexpr int BKE = kQRow / ESZ; // k per K tile
   constexpr int NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int IA = BM / 8, IB = BN / 8; // DMA loads (8 rows each) of A and of one B half
   static_assert(IA % NW == 0 && IB % NW == 0 && TM >= 1 && TN >= 1, "tile shape");
   constexpr int UA = IA / NW, UB = IB / NW; // per wave
-  constexpr int DMA = UA + UB * (SPLIT ? 2 : 1);
-  constexpr int SA = BM * kQRow, SB = BN * kQRow, STAGE = SA + SB * (SPLIT ? 2 : 1);
+  constexpr int DMA = UA * NAH + UB * (SPLIT ? 2 : 1);
+  constexpr int SH = BM * kQRow, SA = SH * NAH, SB = BN * kQRow, STAGE = SA + SB * (SPLIT ? 2 : 1);
   __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];
 
   const int M = g.M_fixed >= 0 ? g.M_fixed : dims->N;
@@ -144,14 +145,15 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
       left = g.seg[q].k / BKE;
       ++q;
 #pragma unroll
-      for (int u = 0; u < UA; ++u) pa[u] = ap + (size_t)rowa[u] * lda * ESZ;
+      for (int u = 0; u < UA; ++u) pa[u] = ap + (size_t)rowa[u] * lda * ESA;
     }
     --left;
     char *d = smem + st + 8 * kQRow * w;
 #pragma unroll
     for (int u = 0; u < UA; ++u) {
-      dma(pa[u], d + 8 * kQRow * NW * u);
-      pa[u] += kQRow;
+#pragma unroll
+      for (int h = 0; h < NAH; ++h) dma(pa[u] + h * kQRow, d + h * SH + 8 * kQRow * NW * u);
+      pa[u] += kQRow * NAH;
     }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
@@ -168,20 +170,33 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   // 16-row block and logical chunk 4 c + L / 16 of the tile's two halves c
   // (BF16: 8 k per lane of a 32-deep MFMA; FP32: 4 k, the k-slots of four
   // 4-deep MFMAs)
-  using V = typename Frag<PREC>::V;
+  // FP32 A of a BF16 product: half c is its own 128-byte row, a lane's 8 k are
+  // logical chunks 2 (L / 16) and the next, rounded (RNE) when the tile begins
+  using V = typename Frag<SPLIT>::V;
   const int fr = L & 15;
   const int p0 = (L >> 4) ^ (fr & 7);
   const int offA0 = (wm0 + fr) * kQRow + 16 * p0, offA1 = (wm0 + fr) * kQRow + 16 * (p0 ^ 4);
   const int offB0 = SA + (wn0 + fr) * kQRow + 16 * p0;
   const int offB1 = SA + (wn0 + fr) * kQRow + 16 * (p0 ^ 4);
-  V fa[2][2][TM], fb[2][2][TN], fl[2][2][SPLIT ? TN : 1]; // [set][half][block]
+  const int q0 = 16 * ((2 * (L >> 4)) ^ (fr & 7)); // A32: the first chunk; the other is 16 bytes off
+  V fa[A32 ? 1 : 2][2][TM], fb[2][2][TN], fl[2][2][SPLIT ? TN : 1]; // [set][half][block]
+  f4 raw[A32 ? 2 : 1][A32 ? TM : 1][2];
   auto read = [&](auto set, int st) {
     constexpr int S = decltype(set)::value;
     const char *base = smem + st;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      fa[S][0][i] = *reinterpret_cast<const V *>(base + offA0 + 16 * i * kQRow);
-      fa[S][1][i] = *reinterpret_cast<const V *>(base + offA1 + 16 * i * kQRow);
+      if constexpr (A32) {
+        const char *row = base + (wm0 + fr + 16 * i) * kQRow;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          raw[h][i][0] = *reinterpret_cast<const f4 *>(row + h * SH + q0);
+          raw[h][i][1] = *reinterpret_cast<const f4 *>(row + h * SH + (q0 ^ 16));
+        }
+      } else {
+        fa[S][0][i] = *reinterpret_cast<const V *>(base + offA0 + 16 * i * kQRow);
+        fa[S][1][i] = *reinterpret_cast<const V *>(base + offA1 + 16 * i * kQRow);
+      }
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -225,7 +240,7 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
         else tot[FOLD][i][j] += acc[i][j];
       }
   };
-  auto mm = [&](const V (&a)[TM], const V (&b)[TN]) { mma_frags<PREC, TM, TN>(a, b, acc); };
+  auto mm = [&](const V (&a)[TM], const V (&b)[TN]) { mma_frags<SPLIT, TM, TN>(a, b, acc); };
   auto next = [](int st) { return st == (NST - 1) * STAGE ? 0 : st + STAGE; };
 
   // tile t (register set S, LDS stage st): its first products; then, if a
@@ -244,10 +259,19 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
         z_end = 2 * (KT / 2 * (z + 1) / g.chunks);
       }
     }
-    mm(fa[S][0], fb[S][0]);
+    constexpr int SF = A32 ? 0 : S;
+    if constexpr (A32) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) fa[0][h][i][e] = (__bf16)raw[h][i][e >> 2][e & 3];
+    }
+    mm(fa[SF][0], fb[S][0]);
     if constexpr (SPLIT) {
-      mm(fa[S][1], fb[S][1]);
-      mm(fa[S][0], fl[S][0]);
+      mm(fa[SF][1], fb[S][1]);
+      mm(fa[SF][0], fl[S][0]);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (t + 1 < KT) {
@@ -258,8 +282,8 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
       read(IC<1 - S>{}, next(st));
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (SPLIT) mm(fa[S][1], fl[S][1]);
-    else mm(fa[S][1], fb[S][1]);
+    if constexpr (SPLIT) mm(fa[SF][1], fl[S][1]);
+    else mm(fa[SF][1], fb[S][1]);
   };
 
   for (int t = 0, st = 0; t < NST && t < KT; ++t, st += STAGE) issue(st);
@@ -347,6 +371,7 @@ inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // LDS stages (160 KB of LDS per CU; see the head of this file)
 constexpr int stages(int prec, int tile, int tag) {
+  if (prec == 2) return 3; // 32 or 16 KB a stage
   return tile == 64 && tag != 4 ? 5 : 3;
 }
 
@@ -368,16 +393,16 @@ int tile_side(int capM, const GemmNTB &g) {
 } // namespace
 
 bool gemm_ntb_ok(const GemmNTB &g, int precision) {
-  const int bke = precision ? 64 : 32, esz = precision ? 2 : 4;
+  const int bke = precision ? 64 : 32, esz = precision ? 2 : 4, esa = precision == 1 ? 2 : 4;
   if (g.nseg < 1 || g.nseg > kMaxSeg || !g.B || !(g.C || g.Cb) || g.Ncols <= 0)
     return false;
-  if ((precision == 1) != (g.B_lo != nullptr) || (precision == 0 && g.Cb)) return false;
+  if ((precision != 0) != (g.B_lo != nullptr) || (precision == 0 && g.Cb)) return false;
   if ((g.ldb * esz) % 16 || !al16(g.B) || (g.B_lo && !al16(g.B_lo))) return false;
   if (g.perm && (!g.brow || g.nb < 1 || (g.bstride * esz) % 16)) return false;
   int boff = 0; // the segments' weight columns follow one another from 0
   for (int q = 0; q < g.nseg; ++q) {
     const SegB &s = g.seg[q];
-    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esz) % 16 || s.boff != boff)
+    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esa) % 16 || s.boff != boff)
       return false;
     if (g.chunks > 1 && s.k % 64) return false;
     boff += s.k;
@@ -408,6 +433,8 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
     HGNN_NTB_TAGS(0, 128)
     HGNN_NTB_TAGS(1, 64)
     HGNN_NTB_TAGS(1, 128)
+    HGNN_NTB_TAGS(2, 32)
+    HGNN_NTB_TAGS(2, 64)
 #undef HGNN_NTB_TAGS
 #undef HGNN_NTB
   default:

@@ -34,3 +34,25 @@ def test_chunked_sums(kind, H, B, lo, hi):
     assert rel(out["pred"], rec.y[:, 0]) <= 1e-5
     assert max(rep.values()) <= 1e-5
     m.close()
+
+
+# BF16 operands rounded in registers (small grids) or while staging (larger ones):
+# the same products in the same order, so a graph's prediction does not depend on
+# the batch it is in.  2300 to 9300 nodes: both sides of the limit of each linear.
+@pytest.mark.parametrize("kind,H,graphs", [("sage", 64, 300), ("sage", 128, 260),
+                                           ("cgcnn", 64, 300), ("cgcnn", 128, 200)])
+def test_bf16_prediction_independent_of_the_batch(kind, H, graphs):
+    from paper_2207_11333_amd import hgnn
+    parts = [synth.make_batch(71 + k, n, 30, 32, 1) for k, n in enumerate((1, graphs // 4, graphs))]
+    m = hgnn.Model(3, H, 9, 1, 4, 1, 0, 1.0, kind=kind)
+    m.set_params(synth.init_gc_params(kind, 3, H, 72, edge_feat=1))
+
+    def pred(b):
+        p = torch.empty(b.num_graphs, device="cuda")
+        m.forward(hgnn.DeviceBatch.from_host(b), p)
+        return p
+
+    whole = pred(synth.concat_batches(parts))
+    assert torch.isfinite(whole).all()
+    assert torch.equal(torch.cat([pred(b) for b in parts]), whole)
+    m.close()
