@@ -199,6 +199,7 @@ struct WgJob {
   float *zscale;
   int sum_from; // rows of P from here on need only column N (M: none)
   int rot;      // XCD of chunk 0 (deals the chunks of a list of jobs evenly)
+  int by_row;   // deal rows of output tiles to the XCDs, not whole chunks
 };
 bool wg_job_ok(const WgJob &j);
 int wg_blocks(const WgJob &j, int tile);

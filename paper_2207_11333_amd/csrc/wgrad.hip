@@ -46,17 +46,20 @@ template <int TW> struct VecOf;
 template <> struct VecOf<4> { using T = f4; };
 template <> struct VecOf<2> { using T = f2; };
 
-// Node rows per step and LDS stages.  FP32 (TW = 2): 24 KB a workgroup; BF16,
-// whose instruction takes 32 rows, 48 KB (TW = 2) or 64 KB (TW = 4: two
-// workgroups a CU; a third stage would leave one).
-template <int PREC> constexpr int wg_rows() { return PREC == 0 ? 16 : 32; }
-template <int PREC, int TW> constexpr int wg_stages() { return TW == 4 ? 2 : 3; }
+// Node rows per step (R) and LDS stages.  FP32 lists: 16 rows, 24 KB a workgroup;
+// BF16, whose instruction takes 32 rows, 48 KB (TW = 2) or 64 KB (TW = 4: two
+// workgroups a CU; a third stage would leave one).  FP32 products launched alone,
+// beside the adjoint on the other stream, keep 32 rows a step in flight (48 KB):
+// at 24k nodes and H = 256 their launches take 231 us in place of 258 (a list at
+// 4.5k nodes 557 us a training step in place of 549).
+template <int TW> constexpr int wg_stages() { return TW == 4 ? 2 : 3; }
 constexpr int kWgChunk = 32; // chunks are multiples of this many rows
 
 // tile counts of a job: full column tiles of the rows before sum_from, one
 // (sum only) of the rest
 struct WgTiles {
   int mfull, nt, tpc;
+  int rows; // rows of nt tiles that hold them (by_row)
 };
 __host__ __device__ inline WgTiles wg_tiles(const WgJob &j, int B) {
   WgTiles t;
@@ -64,6 +67,7 @@ __host__ __device__ inline WgTiles wg_tiles(const WgJob &j, int B) {
   t.mfull = j.sum_from < j.M ? (j.sum_from + B - 1) / B : mt;
   t.nt = (j.N + B - 1) / B;
   t.tpc = t.mfull * t.nt + (mt - t.mfull);
+  t.rows = (t.tpc + t.nt - 1) / t.nt;
   return t;
 }
 
@@ -75,15 +79,14 @@ struct WgPlace {
 
 // FULL: the product and, in the first column tile, the sum column; else the
 // sum column alone.  PERM: rows through j.perm.
-template <int PREC, int TW, bool FULL, bool PERM>
+template <int PREC, int TW, int R, bool FULL, bool PERM>
 __device__ __forceinline__ void wgrad_body(const WgJob &j, const WgPlace &pl, char *smem) {
   using V = typename VecOf<TW>::T;
   constexpr int B = 32 * TW;               // output tile
-  constexpr int R = wg_rows<PREC>();
   constexpr int ROWB = B * 4;              // bytes per LDS row
   constexpr int RPI = 1024 / ROWB;         // rows per DMA load
   constexpr int U = R / RPI / 4;     // DMA loads per wave, operand and step
-  constexpr int NST = wg_stages<PREC, TW>(), OPB = R * ROWB, STAGE = 2 * OPB;
+  constexpr int NST = wg_stages<TW>(), OPB = R * ROWB, STAGE = 2 * OPB;
   constexpr int DMA = FULL ? 2 * U : U;
   const int z = pl.z, i_lo = pl.i_lo, i_hi = pl.i_hi, m0 = pl.m0, n0 = pl.n0;
   const int KT = i_hi > i_lo ? (i_hi - i_lo + R - 1) / R : 0;
@@ -257,17 +260,29 @@ __device__ __forceinline__ void wgrad_body(const WgJob &j, const WgPlace &pl, ch
     }
 }
 
-template <int PREC, int TW>
+template <int PREC, int TW, int R>
 __device__ __forceinline__ void wgrad_tile(const Dims *__restrict__ dims, const WgJob &j, int blk) {
-  constexpr int B = 32 * TW, STAGE = 2 * wg_rows<PREC>() * B * 4;
-  __shared__ __attribute__((aligned(1024))) char smem[wg_stages<PREC, TW>() * STAGE];
+  constexpr int B = 32 * TW, STAGE = 2 * R * B * 4;
+  __shared__ __attribute__((aligned(1024))) char smem[wg_stages<TW>() * STAGE];
   // chunk z and output tile: a chunk's tiles read the same rows and stay on
   // one XCD (the block index's remainder by 8), whose L2 serves the re-reads
   const WgTiles tl = wg_tiles(j, B);
   const int Z = j.splits + (j.perm ? j.nb : 0);
-  const int l = blk >> 3, z = (l / tl.tpc) * 8 + ((blk - j.rot) & 7);
-  if (z >= Z) return;
-  const int jt = l % tl.tpc;
+  // (by_row: a row of them).  The chunks of one product that do not deal evenly
+  // to the XCDs go by rows: 12 chunks of 84 tiles (24k nodes, H = 256) would
+  // give half the XCDs two and the others one (a training step of four layers
+  // 3521 -> 3382 us).
+  const int l = blk >> 3;
+  int z, jt;
+  if (j.by_row) {
+    const int g = (l / tl.nt) * 8 + (blk & 7);
+    z = g / tl.rows;
+    jt = (g % tl.rows) * tl.nt + l % tl.nt;
+  } else {
+    z = (l / tl.tpc) * 8 + ((blk - j.rot) & 7);
+    jt = l % tl.tpc;
+  }
+  if (z >= Z || jt >= tl.tpc) return;
   const bool full = jt < tl.mfull * tl.nt;
   const int mt = full ? jt / tl.nt : tl.mfull + (jt - tl.mfull * tl.nt);
   const int m0 = mt * B, n0 = full ? (jt % tl.nt) * B : 0;
@@ -285,25 +300,25 @@ __device__ __forceinline__ void wgrad_tile(const Dims *__restrict__ dims, const 
       j.zscale[2 * z + 1] = bq >= 0 ? j.table[2 * bq + 1] : 0.f;
     }
     const WgPlace pl{z, bq >= 0 ? r0 : 0, bq >= 0 ? min(r1, r0 + chunk) : 0, m0, n0};
-    wgrad_body<PREC, TW, true, true>(j, pl, smem);
+    wgrad_body<PREC, TW, R, true, true>(j, pl, smem);
     return;
   }
   const int i_lo = min(z * chunk, rows);
   const WgPlace pl{z, i_lo, min(rows, i_lo + chunk), m0, n0};
-  if (full) wgrad_body<PREC, TW, true, false>(j, pl, smem);
-  else wgrad_body<PREC, TW, false, false>(j, pl, smem);
+  if (full) wgrad_body<PREC, TW, R, true, false>(j, pl, smem);
+  else wgrad_body<PREC, TW, R, false, false>(j, pl, smem);
 }
 
 // one FP32 product, on the tile of wg_tile_all
 __global__ void __launch_bounds__(256, 2) k_wgrad(const Dims *__restrict__ dims, const WgJob j) {
-  wgrad_tile<0, 2>(dims, j, blockIdx.x);
+  wgrad_tile<0, 2, 32>(dims, j, blockIdx.x);
 }
 
 // blockIdx.y: the job, in device memory; blocks past a job's have nothing to do
 template <int PREC, int TW>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_all(const Dims *__restrict__ dims, const WgJob *__restrict__ tab) {
-  wgrad_tile<PREC, TW>(dims, tab[blockIdx.y], blockIdx.x);
+  wgrad_tile<PREC, TW, PREC ? 32 : 16>(dims, tab[blockIdx.y], blockIdx.x);
 }
 
 inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
@@ -331,13 +346,17 @@ int wg_tile_all(int blocks128, int precision) { return precision && blocks128 >=
 
 int wg_blocks(const WgJob &j, int tile) {
   const int Z = j.splits + (j.perm ? j.nb : 0);
-  return 8 * ((Z + 7) / 8) * wg_tiles(j, tile).tpc;
+  const WgTiles t = wg_tiles(j, tile);
+  if (j.by_row) return 8 * ((Z * t.rows + 7) / 8) * t.nt;
+  return 8 * ((Z + 7) / 8) * t.tpc;
 }
 
 hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEvent_t ev0,
                         hipEvent_t ev1) {
   if (!wg_job_ok(j)) return hipErrorInvalidValue;
-  hipExtLaunchKernelGGL(k_wgrad, dim3(wg_blocks(j, 64)), dim3(256), 0, s, ev0, ev1, 0, dims, j);
+  WgJob k = j;
+  k.by_row = (j.splits + (j.perm ? j.nb : 0)) % 8 != 0;
+  hipExtLaunchKernelGGL(k_wgrad, dim3(wg_blocks(k, 64)), dim3(256), 0, s, ev0, ev1, 0, dims, k);
   return hipGetLastError();
 }
 
