@@ -211,16 +211,10 @@ __device__ void stage_transposed(const float *__restrict__ Wm, const float *__re
 
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_stage_t_layer(const float *__restrict__ Wm, const float *__restrict__ Wp, int F, int Fp,
-                int H, int Fe, int nb, const float *__restrict__ table, StageOut o) {
-  stage_transposed<T>(Wm, Wp, F, Fp, H, Fe, nb, table, o, blockIdx.x);
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
 k_stage_layer(const float *__restrict__ Wm, const float *__restrict__ Wp, int F, int Fp,
-              int H, int Fe, int nb, const float *__restrict__ table, StageOut o) {
-  stage_row<T>(Wm, Wp, F, Fp, H, Fe, nb, table, o, blockIdx.x);
+              int H, int Fe, int nb, const float *__restrict__ table, StageOut o, int rows) {
+  if ((int)blockIdx.x < rows) stage_row<T>(Wm, Wp, F, Fp, H, Fe, nb, table, o, blockIdx.x);
+  else stage_transposed<T>(Wm, Wp, F, Fp, H, Fe, nb, table, o, blockIdx.x - rows);
 }
 
 // Every layer's copies in one launch (blockIdx.y = layer): the first `rows`
@@ -285,16 +279,12 @@ hipError_t launch_stage_all(const StageDesc *tab, int L, int maxFp, int H, int F
 
 hipError_t launch_stage_layer(const float *Wm, const float *Wp, int F, int Fp, int H,
                               int Fe, int nb, const float *table, const StageOut &o,
-                              int to_bf16, hipStream_t s) {
+                              int to_bf16, bool backward, hipStream_t s) {
   const int rows = stage_rows(H, Fe, nb);
-  const int tiles = stage_t_tiles(Fp, H, nb);
-  if (to_bf16) {
-    k_stage_layer<__bf16><<<rows, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o);
-    k_stage_t_layer<__bf16><<<tiles, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o);
-  } else {
-    k_stage_layer<float><<<rows, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o);
-    k_stage_t_layer<float><<<tiles, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o);
-  }
+  const int grid = rows + (backward ? stage_t_tiles(Fp, H, nb) : 0);
+  if (to_bf16)
+    k_stage_layer<__bf16><<<grid, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o, rows);
+  else k_stage_layer<float><<<grid, 256, 0, s>>>(Wm, Wp, F, Fp, H, Fe, nb, table, o, rows);
   return hipGetLastError();
 }
 

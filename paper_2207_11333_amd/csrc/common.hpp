@@ -208,6 +208,9 @@ hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEven
                         hipEvent_t ev1 = nullptr);
 // n products in device memory in one launch (a whole backward pass's): tile is
 // the output tile side, 128 or 64, most the largest wg_blocks(job, tile).
+// Two products in one launch (a layer's).
+hipError_t launch_wgrad_pair(const Dims *dims, const WgJob &j0, const WgJob &j1, int precision,
+                             hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_wgrad_all(const Dims *dims, const WgJob *tab, int n, int most, int precision,
                             int tile, hipStream_t s, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);
@@ -439,9 +442,9 @@ struct StageDesc {
 hipError_t launch_stage_all(const StageDesc *tab, int L, int maxFp, int H, int Fe,
                             int nb, const float *table, int to_bf16, long long *bump,
                             hipStream_t s);
-hipError_t launch_stage_layer(const float *Wm, const float *Wp, int F, int Fp,
-                              int H, int Fe, int nb, const float *table, const StageOut &o,
-                              int to_bf16, hipStream_t s);
+hipError_t launch_stage_layer(const float *Wm, const float *Wp, int F, int Fp, int H,
+                              int Fe, int nb, const float *table, const StageOut &o,
+                              int to_bf16, bool backward, hipStream_t s);
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t s);
 // p[off + t] for t < n: bound * U[-1, 1) from SplitMix64(seed) at index off + t
 hipError_t launch_init_uniform(float *p, int64_t off, int64_t n, float bound, uint64_t seed,

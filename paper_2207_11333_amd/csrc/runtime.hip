@@ -64,6 +64,8 @@ template <typename T> static hipError_t dalloc(T *&p, size_t count) {
 // measured: a gain at 40k nodes, a loss at 4.5k, where the launches lie on
 // the critical path of the backward pass).
 constexpr int kSplitDeRows = 16384;
+// node rows x hidden width of a layer whose weight gradients share a launch
+constexpr long long kPairElems = 640 << 10;
 // Row chunks of the De column sums (at 40k rows: about 320 rows per chunk;
 // the sums then cost about as much as reading De once)
 constexpr int kColsumChunks = 128;
@@ -592,10 +594,12 @@ int stage_all(hgnn_ctx *c, hipStream_t s) {
   return HGNN_OK;
 }
 
-static int stage_layer_from(hgnn_ctx *c, int l, const float *wl, hipStream_t s) {
+// the transposed copies are the backward pass's
+static int stage_layer_from(hgnn_ctx *c, int l, const float *wl, bool backward, hipStream_t s) {
   const LayerDesc &d = c->ld[l];
   hipError_t e = launch_stage_layer(wl + (d.oWm - d.off), wl + (d.oWp - d.off), d.F, d.Fp,
-                                    c->H, c->Fe, c->nb, c->table, stage_out(c, l), c->prec, s);
+                                    c->H, c->Fe, c->nb, c->table, stage_out(c, l), c->prec,
+                                    backward, s);
   if (e != hipSuccess) return hip_fail(c, e, "stage layer weights");
   c->staged_from_params = false;
   return HGNN_OK;
@@ -932,9 +936,15 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     if (e != hipSuccess) return hip_fail(c, e, "relu mask");
     du = w.du;
   }
-  // fork: the weight gradients run on the aux stream
-  hipStream_t a = c->aux;
-  if (!defer_wg) {
+  // Small layers: both weight gradients in one launch after the adjoint, on s.
+  // Two launches beside the adjoint on the aux stream, and their events, cost
+  // more than they hide: one layer of H = 128 at 4.5k nodes, forward and
+  // backward, 142 -> 111 us on the device and 215 -> 144 with the host.  Larger
+  // ones fork: four recomputed layers of H = 256 at 3.5k nodes (0.9M) took 820
+  // us with the fork and 899 without.
+  const bool pair = !defer_wg && c->nb && (long long)ex.N * H <= kPairElems;
+  hipStream_t a = pair ? s : c->aux;
+  if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);
     if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[0], 0);
     if (e != hipSuccess) return hip_fail(c, e, "fork");
@@ -944,8 +954,10 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // reduction.  Its partial sums stay in part_u until the message weight
   // gradient's are in part too: one launch reduces both.
   ReduceJobs red{};
+  WgJob j_upd{};
   if (c->nb && !defer_wg) {
-    WgJob j = upd_job(c, l, ex.N);
+    WgJob &j = j_upd;
+    j = upd_job(c, l, ex.N);
     j.X = du;
     j.seg[0].ptr = hin;
     j.seg[0].ld = ldh;
@@ -954,7 +966,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     j.perm = w.csr.perm;
     j.brow = w.csr.brow;
     j.zscale = c->zscale;
-    {
+    if (!pair) {
       TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, a, /*manual=*/true);
       e = launch_product(ex.dims, j, c->prec, a, /*tag=*/1, tl.start(), tl.stop());
     }
@@ -1076,9 +1088,11 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   if (e != hipSuccess) return hip_fail(c, e, "aggregation adjoint");
   // second fork: D = [D_in | D_out | De] is ready
   if (!defer_wg) {
-    e = hipEventRecord(c->fork_ev[1], s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[1], 0);
-    if (e != hipSuccess) return hip_fail(c, e, "fork");
+    if (!pair) {
+      e = hipEventRecord(c->fork_ev[1], s);
+      if (e == hipSuccess) e = hipStreamWaitEvent(a, c->fork_ev[1], 0);
+      if (e != hipSuccess) return hip_fail(c, e, "fork");
+    }
     // S8: [dW_dst | dW_src] = [D_in | D_out]^T h, db^m = sum_i D_in, and the
     // edge-feature columns sum_i De_i = sum_k dm_k e_k (the sum column of the
     // De rows; large batches form it by k_colsum)
@@ -1088,7 +1102,10 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     j.seg[0].ptr = hin;
     j.seg[0].ld = ldh;
     j.P = c->part;
-    {
+    if (pair) {
+      TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, a, /*manual=*/true);
+      e = launch_wgrad_pair(ex.dims, j_upd, j, c->prec, a, tl.start(), tl.stop());
+    } else {
       TimedLaunch tl(c, ex, SITE_MESSAGE_WGRAD, a, /*manual=*/true);
       e = launch_product(ex.dims, j, c->prec, a, /*tag=*/2, tl.start(), tl.stop());
     }
@@ -1160,7 +1177,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     }
     if (e != hipSuccess) return hip_fail(c, e, "input gradient GEMM");
   }
-  if (defer_wg) return HGNN_OK;
+  if (defer_wg || pair) return HGNN_OK;
   // join now, or leave it to the launches above of the next layers
   e = hipEventRecord(c->pjoin_ev[l & 1], a);
   if (e == hipSuccess && !defer_join) e = hipStreamWaitEvent(s, c->pjoin_ev[l & 1], 0);
@@ -2250,7 +2267,7 @@ int hgnn_op_layer_forward(hgnn_ctx *c, int32_t l, const float *wl, const float *
   if (l < 0 || l >= c->L) return fail(HGNN_EINVAL, "layer out of range");
   if (!wl || !h_in || !h_out) return fail(HGNN_EINVAL, "NULL buffer");
   hipStream_t s = (hipStream_t)stream;
-  int rc = stage_layer_from(c, l, wl, s);
+  int rc = stage_layer_from(c, l, wl, /*backward=*/false, s);
   if (rc) return rc;
   return layer_forward(c, c->ex, l, wl, h_in, h_out, s);
 }
@@ -2273,7 +2290,7 @@ int hgnn_op_layer_backward(hgnn_ctx *c, int64_t generation, int32_t l, const flo
   if (l < 0 || l >= c->L) return fail(HGNN_EINVAL, "layer out of range");
   if (!wl || !h_in || !h_out || !dh_out || !dwl) return fail(HGNN_EINVAL, "NULL buffer");
   hipStream_t s = (hipStream_t)stream;
-  int rc = stage_layer_from(c, l, wl, s);
+  int rc = stage_layer_from(c, l, wl, /*backward=*/true, s);
   if (rc) return rc;
   return layer_backward(c, c->ex, l, wl, h_in, h_out, dh_out, dh_in, dwl, s);
 }

@@ -314,6 +314,14 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(const Dims *__restrict__ dims,
   wgrad_tile<0, 2, 32>(dims, j, blockIdx.x);
 }
 
+// a layer's two products
+template <int PREC, int TW>
+__global__ void __launch_bounds__(256, 2)
+k_wgrad_pair(const Dims *__restrict__ dims, const WgJob j0, const WgJob j1, int n0) {
+  const bool first = (int)blockIdx.x < n0;
+  wgrad_tile<PREC, TW, PREC ? 32 : 16>(dims, first ? j0 : j1, first ? blockIdx.x : blockIdx.x - n0);
+}
+
 // blockIdx.y: the job, in device memory; blocks past a job's have nothing to do
 template <int PREC, int TW>
 __global__ void __launch_bounds__(256, 2)
@@ -357,6 +365,23 @@ hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEven
   WgJob k = j;
   k.by_row = (j.splits + (j.perm ? j.nb : 0)) % 8 != 0;
   hipExtLaunchKernelGGL(k_wgrad, dim3(wg_blocks(k, 64)), dim3(256), 0, s, ev0, ev1, 0, dims, k);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_pair(const Dims *dims, const WgJob &j0, const WgJob &j1, int precision,
+                             hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  if (!wg_job_ok(j0) || !wg_job_ok(j1)) return hipErrorInvalidValue;
+  WgJob k1 = j1;
+  k1.rot = (j0.splits + j0.nb) % 8;
+  const int tile = wg_tile_all(wg_blocks(j0, 128) + wg_blocks(j1, 128), precision);
+  const int n0 = wg_blocks(j0, tile);
+  const dim3 grid(n0 + wg_blocks(k1, tile));
+#define HGNN_WG(P, W)                                                                          \
+  hipExtLaunchKernelGGL((k_wgrad_pair<P, W>), grid, dim3(256), 0, s, ev0, ev1, 0, dims, j0, k1, n0)
+  if (!precision) HGNN_WG(0, 2);
+  else if (tile == 128) HGNN_WG(1, 4);
+  else HGNN_WG(1, 2);
+#undef HGNN_WG
   return hipGetLastError();
 }
 
