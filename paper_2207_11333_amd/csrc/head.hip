@@ -52,28 +52,41 @@ __device__ float block_sum(float v, float *red) {
 // partial sums are added in order through LDS.  One thread per feature left
 // half of a 256-thread workgroup idle at H = 128 and walked all H rows of W1
 // in one chain.
+// G graphs a workgroup (1, 2 or 4) share each W1 value read: at 1024 graphs and
+// H = 256 one graph a workgroup reads 268 MB of W1 from L2 (23 us, 44 with
+// untransposed rows), four a quarter of it (16.6).  All G are pooled at once, 16
+// bytes a lane.
 constexpr int kHeadFwdThreads = 512;
 
+// four values at p, 16-byte aligned if vec
+__device__ __forceinline__ f4 load4(const float *p, bool vec) {
+  if (vec) return *reinterpret_cast<const f4 *>(p);
+  return f4{p[0], p[1], p[2], p[3]};
+}
+
+template <int G>
 __global__ void __launch_bounds__(kHeadFwdThreads)
 k_head_forward(const Dims *__restrict__ dims, int H, int Tg, const int *__restrict__ gptr,
-               const float *__restrict__ h, const float *__restrict__ wh,
+               const float *__restrict__ h, int vec, const float *__restrict__ wh,
                const float *__restrict__ W1T, float *__restrict__ g, float *__restrict__ q,
                float *__restrict__ pred, float *__restrict__ pred2) {
-  __shared__ float gs[512];
-  __shared__ float red[kHeadFwdThreads];
-  const int b = blockIdx.x, t = blockIdx.y;
+  constexpr int NT = kHeadFwdThreads;
+  __shared__ __attribute__((aligned(16))) float gs[512][G];
+  __shared__ __attribute__((aligned(16))) float red[G * NT];
+  __shared__ float inv_n[G];
+  const int b0 = blockIdx.x * G, t = blockIdx.y;
   const int B = dims->B;
-  if (b >= B) return;
+  if (b0 >= B) return;
   const float *W1 = wh + (size_t)t * (H * H + 2 * H + 1);
   const float *b1 = W1 + H * H, *w2 = b1 + H, *b2 = w2 + H;
-  int lo, hi;
-  graph_range(gptr, b, dims->N, lo, hi);
-  const float inv_n = 1.0f / (float)(hi - lo);
-  const int P = kHeadFwdThreads / H; // H <= 512
+  const int P = NT / H; // H <= 512
   const int tid = threadIdx.x, c = tid % H, p = tid / H;
   const bool act = p < P;
-  // pooling: nodes lo + p R .. of this range
-  {
+  // pooling.  One graph: range p, feature c; several: range pp of graph j,
+  // features 4 cq .. (the divisions that find them cost one graph 1 us)
+  if constexpr (G == 1) {
+    int lo, hi;
+    graph_range(gptr, b0, dims->N, lo, hi);
     const int R = (hi - lo + P - 1) / P;
     const int i0 = min(lo + p * R, hi), i1 = min(i0 + R, hi);
     float s = 0.f;
@@ -82,49 +95,107 @@ k_head_forward(const Dims *__restrict__ dims, int H, int Tg, const int *__restri
       for (int i = i0; i < i1; ++i) s += h[(size_t)i * H + c];
     }
     red[tid] = s;
+    if (tid == 0) inv_n[0] = 1.0f / (float)(hi - lo);
+  } else {
+    const int nq = H / 4, cq = tid % nq, j = tid / nq / P, pp = tid / nq % P;
+    if (j < G) {
+      f4 s = {0.f, 0.f, 0.f, 0.f};
+      int lo = 0, hi = 0;
+      if (b0 + j < B) graph_range(gptr, b0 + j, dims->N, lo, hi);
+      const int R = (hi - lo + P - 1) / P;
+      const int i0 = min(lo + pp * R, hi), i1 = min(i0 + R, hi);
+#pragma unroll 8
+      for (int i = i0; i < i1; ++i) s += load4(h + (size_t)i * H + 4 * cq, vec);
+      *reinterpret_cast<f4 *>(red + (j * P + pp) * H + 4 * cq) = s;
+      if (cq == 0 && pp == 0) inv_n[j] = 1.0f / (float)(hi - lo);
+    }
   }
   __syncthreads();
-  if (p == 0) {
-    float s = red[c];
-    for (int k = 1; k < P; ++k) s += red[k * H + c];
-    const float gv = s * inv_n;
-    gs[c] = gv;
-    if (t == 0) g[(size_t)b * H + c] = gv;
+  for (int e = tid; e < G * H; e += NT) {
+    const int j = G == 1 ? 0 : e / H, cc = G == 1 ? c : e % H; // G = 1: e = tid < H
+    float s = red[j * P * H + cc];
+    for (int k = 1; k < P; ++k) s += red[(j * P + k) * H + cc];
+    const float gv = s * inv_n[j];
+    gs[cc][j] = gv;
+    if (t == 0 && b0 + j < B) g[(size_t)(b0 + j) * H + cc] = gv;
   }
   __syncthreads();
   // the W1 product over k = p RK ..
   {
     const int RK = (H + P - 1) / P;
     const int k0 = min(p * RK, H), k1 = min(k0 + RK, H);
-    float s = 0.f;
-    if (act) {
-      if (W1T) {
-        const float *W1Tt = W1T + (size_t)t * H * H;
+    float s[G] = {};
+    if (G > 1 && !W1T) {
+      // W1 as stored, 16 columns of every range at a time through LDS: its rows
+      // read by the threads' outputs took 44 us, this 26 (transposed rows, where the
+      // context holds them, 17)
+      constexpr int KC = 16, U = KC;
+      __shared__ float tile[G > 1 ? NT : 1][KC + 1];
+      int at[U]; // element u of a chunk: row (range, feature) r, column kk
+      const int kk = tid & (KC - 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = (tid >> 4) + u * (NT / KC), rp = r / H;
+        at[u] = rp < P ? (r - rp * H) * H + min(rp * RK, H) + kk : -1;
+      }
+      for (int d = 0; d < RK; d += KC) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = W1[min(max(at[u], 0) + d, H * H - 1)];
+        __syncthreads(); // the last chunk is read
+#pragma unroll
+        for (int u = 0; u < U; ++u) tile[(tid >> 4) + u * (NT / KC)][kk] = v[u];
+        __syncthreads();
+        if (act)
+          for (int k = 0; k < KC && k0 + d + k < k1; ++k) {
+            const float wv = tile[p * H + c][k];
+#pragma unroll
+            for (int j = 0; j < G; ++j) s[j] += wv * gs[k0 + d + k][j];
+          }
+      }
+    } else if (act) {
+      const float *w = W1T ? W1T + (size_t)t * H * H + c : W1 + (size_t)c * H;
+      const int ld = W1T ? H : 1;
 #pragma unroll 8
-        for (int k = k0; k < k1; ++k) s += W1Tt[(size_t)k * H + c] * gs[k];
-      } else {
-        const float *row = W1 + (size_t)c * H;
-#pragma unroll 8
-        for (int k = k0; k < k1; ++k) s += row[k] * gs[k];
+      for (int k = k0; k < k1; ++k) {
+        const float wv = w[(size_t)k * ld];
+#pragma unroll
+        for (int j = 0; j < G; ++j) s[j] += wv * gs[k][j];
       }
     }
-    __syncthreads(); // every read of red above is done
-    red[tid] = s;
+#pragma unroll
+    for (int j = 0; j < G; ++j) red[j * NT + tid] = s[j]; // the last reads were before a barrier
   }
   __syncthreads();
-  float part = 0.f;
-  if (p == 0) {
-    float s = b1[c];
-    for (int k = 0; k < P; ++k) s += red[k * H + c];
-    const float qv = s > 0.f ? s : 0.f;
-    q[((size_t)t * B + b) * H + c] = qv;
-    part = w2[c] * qv;
+  float part[G];
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    part[j] = 0.f;
+    if (p == 0) {
+      float s = b1[c];
+      for (int k = 0; k < P; ++k) s += red[j * NT + k * H + c];
+      const float qv = s > 0.f ? s : 0.f;
+      if (b0 + j < B) q[((size_t)t * B + b0 + j) * H + c] = qv;
+      part[j] = w2[c] * qv;
+    }
   }
   __syncthreads();
-  const float y = block_sum<kHeadFwdThreads>(part, red) + b2[0];
-  if (threadIdx.x == 0) {
-    pred[(size_t)b * Tg + t] = y;
-    if (pred2) pred2[(size_t)b * Tg + t] = y;
+#pragma unroll
+  for (int j = 0; j < G; ++j) red[j * NT + tid] = part[j];
+  __syncthreads();
+  // block_sum's tree, of the G graphs together
+  for (int lg = 8; lg >= 0; --lg) {
+    static_assert(NT == 2 << 8, "the tree's first level");
+    for (int e = tid; e < G << lg; e += NT) {
+      const int at = (e >> lg) * NT + (e & ((1 << lg) - 1));
+      red[at] += red[at + (1 << lg)];
+    }
+    __syncthreads();
+  }
+  if (tid < G && b0 + tid < B) {
+    const float y = red[tid * NT] + b2[0];
+    pred[(size_t)(b0 + tid) * Tg + t] = y;
+    if (pred2) pred2[(size_t)(b0 + tid) * Tg + t] = y;
   }
 }
 
@@ -162,78 +233,104 @@ k_loss(const Dims *__restrict__ dims, int Tg, const float *__restrict__ pred,
 // masked by relu_of > 0 when given.  The sums over c are split into P
 // contiguous ranges (P = 256 / H threads per output when H < 256) whose
 // partials are added in range order.
+// G graphs a workgroup (more than one with a single head) share each W1 value
+// (1024 graphs, H = 256, 40k nodes: 27 -> 18 us, of which 8 store dh).
+template <int G>
 __global__ void __launch_bounds__(kHeadBwdThreads)
 k_head_bwd_graph(const Dims *__restrict__ dims, int H, int Tg, const int *__restrict__ gptr,
                  const float *__restrict__ wh, const float *__restrict__ q,
                  const float *__restrict__ pred, const float *__restrict__ target,
                  const float *__restrict__ dpred, const float *__restrict__ gw,
                  float *__restrict__ dy, float *__restrict__ dq, float *__restrict__ dh,
-                 const float *__restrict__ relu_of, const float *__restrict__ add) {
-  __shared__ float dqs[kMaxGraphHeads * 512];
-  __shared__ float red[kHeadBwdThreads];
-  __shared__ float dgs[512];
-  const int b = blockIdx.x, tid = threadIdx.x;
+                 const float *__restrict__ relu_of, const float *__restrict__ add, int vec) {
+  constexpr int NT = kHeadBwdThreads;
+  // [head][feature][graph]
+  __shared__ __attribute__((aligned(16))) float dqs[(G == 1 ? kMaxGraphHeads : 1) * 512][G];
+  __shared__ float red[G * NT];
+  __shared__ __attribute__((aligned(16))) float dgs[G][512];
+  const int b0 = blockIdx.x * G, tid = threadIdx.x;
   const int B = dims->B;
-  if (b >= B) return;
+  if (b0 >= B) return;
   const size_t HS = (size_t)H * H + 2 * H + 1;
   for (int t = 0; t < Tg; ++t) {
-    const size_t o = (size_t)b * Tg + t;
-    const float dyb = dpred ? dpred[o]
-                            : (2.0f * (pred[o] - target[o]) / (float)B) * (gw ? gw[t] : 1.0f);
-    if (tid == 0) dy[o] = dyb;
-    const float *w2 = wh + t * HS + H * H + H;
-    const float *qt = q + ((size_t)t * B + b) * H;
-    float *dqt = dq + ((size_t)t * B + b) * H;
-    for (int c = tid; c < H; c += kHeadBwdThreads) {
-      const float v = qt[c] > 0.f ? dyb * w2[c] : 0.f;
-      dqs[t * H + c] = v;
-      dqt[c] = v;
+    for (int e = tid; e < G * H; e += NT) {
+      const int j = G == 1 ? 0 : e / H, c = G == 1 ? e : e % H, b = b0 + j;
+      float v = 0.f;
+      if (b < B) {
+        const size_t o = (size_t)b * Tg + t;
+        const float dyb = dpred ? dpred[o]
+                                : (2.0f * (pred[o] - target[o]) / (float)B) * (gw ? gw[t] : 1.0f);
+        if (c == 0) dy[o] = dyb;
+        const size_t at = ((size_t)t * B + b) * H + c;
+        v = q[at] > 0.f ? dyb * wh[t * HS + H * H + H + c] : 0.f;
+        dq[at] = v;
+      }
+      dqs[t * H + c][j] = v;
     }
   }
   __syncthreads();
-  if (H < kHeadBwdThreads) {
-    const int P = kHeadBwdThreads / H;
-    if (tid < P * H) {
-      const int k = tid % H, p = tid / H;
-      const int c0 = (p * H) / P, c1 = ((p + 1) * H) / P;
-      float s = 0.f;
-      for (int t = 0; t < Tg; ++t) {
-        const float *W1 = wh + t * HS;
-#pragma unroll 8
-        for (int c = c0; c < c1; ++c) s += W1[(size_t)c * H + k] * dqs[t * H + c];
+  const int P = NT / H; // H <= 512
+  const int k = tid % H, p = tid / H;
+  if (p < P) {
+    const int c0 = (p * H) / P, c1 = ((p + 1) * H) / P;
+    float s[G] = {};
+    for (int t = 0; t < Tg; ++t) {
+      const float *W1 = wh + t * HS;
+      auto add = [&](float wv, int c) {
+#pragma unroll
+        for (int j = 0; j < G; ++j) s[j] += wv * dqs[t * H + c][j];
+      };
+      int c = c0;
+      for (; c + 16 <= c1; c += 16) { // 16 loads in flight
+        float wv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) wv[u] = W1[(size_t)(c + u) * H + k];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) add(wv[u], c + u);
       }
-      red[tid] = s;
-    }
-    __syncthreads();
-    if (tid < H) {
-      float s = red[tid];
-      for (int p = 1; p < P; ++p) s += red[p * H + tid];
-      dgs[tid] = s;
-    }
-  } else {
-    for (int k = tid; k < H; k += kHeadBwdThreads) {
-      float s = 0.f;
-      for (int t = 0; t < Tg; ++t) {
-        const float *W1 = wh + t * HS;
 #pragma unroll 8
-        for (int c = 0; c < H; ++c) s += W1[(size_t)c * H + k] * dqs[t * H + c];
-      }
-      dgs[k] = s;
+      for (; c < c1; ++c) add(W1[(size_t)c * H + k], c);
     }
+#pragma unroll
+    for (int j = 0; j < G; ++j) red[j * NT + tid] = s[j];
   }
   __syncthreads();
-  int lo, hi;
-  graph_range(gptr, b, dims->N, lo, hi);
-  const float inv_n = 1.0f / (float)(hi - lo);
-  const long long n = (long long)(hi - lo) * H;
-  for (long long idx = tid; idx < n; idx += kHeadBwdThreads) {
-    const int k = (int)(idx % H);
-    const size_t at = (size_t)lo * H + idx;
-    float o = dgs[k] * inv_n;
-    if (add) o += add[at];
-    // fold in the ReLU adjoint of the layer that produced h
-    if (relu_of && !(relu_of[at] > 0.f)) o = 0.f;
-    dh[at] = o;
+  for (int e = tid; e < G * H; e += NT) {
+    const int j = G == 1 ? 0 : e / H, kk = G == 1 ? e : e % H;
+    float s = red[j * NT + kk];
+    for (int u = 1; u < P; ++u) s += red[j * NT + u * H + kk];
+    dgs[j][kk] = s;
+  }
+  __syncthreads();
+  // dh of the nodes, 16 bytes a lane
+  const int nq = H / 4, kq = tid % nq, row = tid / nq, rows = NT / nq;
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    if (b0 + j >= B) break;
+    int lo, hi;
+    graph_range(gptr, b0 + j, dims->N, lo, hi);
+    const float inv_n = 1.0f / (float)(hi - lo);
+    if (row >= rows) continue;
+    const f4 dg = *reinterpret_cast<const f4 *>(&dgs[j][4 * kq]);
+#pragma unroll 4
+    for (int i = lo + row; i < hi; i += rows) {
+      const size_t at = (size_t)i * H + 4 * kq;
+      f4 o = dg * inv_n;
+      if (add) o += load4(add + at, vec);
+      // fold in the ReLU adjoint of the layer that produced h
+      if (relu_of) {
+        const f4 r = load4(relu_of + at, vec);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!(r[e] > 0.f)) o[e] = 0.f;
+      }
+      if (vec) {
+        *reinterpret_cast<f4 *>(dh + at) = o;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dh[at + e] = o[e];
+      }
+    }
   }
 }
 
@@ -289,7 +386,8 @@ k_head_bwd_weights(const Dims *__restrict__ dims, int H, int Tg, const float *__
 // k_head_w_sum adds the chunks in order.  dW1: a workgroup takes a 16 x 64
 // block of (c, k) and walks its chunk 64 graphs at a time, the rows of dq
 // and g staged in LDS (thread: one c, four k); db1, dw2 and db2 take one more
-// workgroup per chunk (thread: one c, the chunk's graphs in order).  The
+// workgroup per chunk (thread: one c, the chunk's graphs in order,
+// eight loads in flight: one at a time they were the launch's 21 us, now 10).  The
 // one-pass kernel above reads each g and dq value once per output.
 constexpr int kHeadChunks = 16, kHeadTC = 16, kHeadTK = 64, kHeadRows = 64;
 constexpr int kHeadChunkedMinB = 512;
@@ -310,6 +408,7 @@ k_head_w_part(const Dims *__restrict__ dims, int H, int Tg, int Z, const float *
   if ((int)blockIdx.x == tiles) { // db1, dw2, db2 over this chunk
     for (int c = t; c < H; c += 256) {
       float s1 = 0.f, s2 = 0.f;
+#pragma unroll 8
       for (int b = b_lo; b < b_hi; ++b) {
         s1 += dq[(size_t)b * H + c];
         s2 += dyall[(size_t)b * Tg + hd] * q[(size_t)b * H + c];
@@ -319,6 +418,7 @@ k_head_w_part(const Dims *__restrict__ dims, int H, int Tg, int Z, const float *
     }
     if (t == 0) {
       float s3 = 0.f;
+#pragma unroll 8
       for (int b = b_lo; b < b_hi; ++b) s3 += dyall[(size_t)b * Tg + hd];
       P[n1 + 2 * H] = s3;
     }
@@ -489,13 +589,23 @@ hipError_t launch_node_head_small(const Dims *dims, int capN, int H, int Tn, con
   return hipGetLastError();
 }
 
+// Graphs a workgroup of the head takes: as many as leave every CU a workgroup.
+static int graphs_per_group(int capB) { return capB >= 1024 ? 4 : capB >= 512 ? 2 : 1; }
+
 hipError_t launch_head_forward(const Dims *dims, int capB, int H, int Tg, const int *graph_ptr,
                                const float *h, const float *wh, const float *W1T, float *g,
                                float *q, float *pred, float *pred2, hipStream_t s) {
   if (capB <= 0) return hipSuccess;
-  if (Tg < 1 || Tg > kMaxGraphHeads || H < 1 || H > 512) return hipErrorInvalidValue;
-  k_head_forward<<<dim3(capB, Tg), kHeadFwdThreads, 0, s>>>(dims, H, Tg, graph_ptr, h, wh, W1T,
-                                                             g, q, pred, pred2);
+  if (Tg < 1 || Tg > kMaxGraphHeads || H < 4 || H > 512 || H % 4) return hipErrorInvalidValue;
+  const int vec = ((uintptr_t)h & 15) == 0;
+  const int G = graphs_per_group(capB);
+#define HGNN_HEAD(GG)                                                                          \
+  k_head_forward<GG><<<dim3(cdiv(capB, GG), Tg), kHeadFwdThreads, 0, s>>>(                     \
+      dims, H, Tg, graph_ptr, h, vec, wh, W1T, g, q, pred, pred2)
+  if (G == 4) HGNN_HEAD(4);
+  else if (G == 2) HGNN_HEAD(2);
+  else HGNN_HEAD(1);
+#undef HGNN_HEAD
   return hipGetLastError();
 }
 
@@ -539,9 +649,16 @@ hipError_t launch_head_backward(const Dims *dims, int capB, int H, int Tg, const
                                 float *dw_head, const float *relu_of, const float *add,
                                 float *part, hipStream_t s) {
   if (capB <= 0) return hipSuccess;
-  if (Tg < 1 || Tg > kMaxGraphHeads || H > 512) return hipErrorInvalidValue;
-  k_head_bwd_graph<<<capB, kHeadBwdThreads, 0, s>>>(dims, H, Tg, graph_ptr, wh, q, pred, target,
-                                                 dpred, gw, dy, dq, dh, relu_of, add);
+  if (Tg < 1 || Tg > kMaxGraphHeads || H < 4 || H > 512 || H % 4) return hipErrorInvalidValue;
+  const int vec = (((uintptr_t)dh | (uintptr_t)relu_of | (uintptr_t)add) & 15) == 0;
+  const int G = Tg == 1 ? graphs_per_group(capB) : 1;
+#define HGNN_HEAD(GG)                                                                          \
+  k_head_bwd_graph<GG><<<cdiv(capB, GG), kHeadBwdThreads, 0, s>>>(                             \
+      dims, H, Tg, graph_ptr, wh, q, pred, target, dpred, gw, dy, dq, dh, relu_of, add, vec)
+  if (G == 4) HGNN_HEAD(4);
+  else if (G == 2) HGNN_HEAD(2);
+  else HGNN_HEAD(1);
+#undef HGNN_HEAD
   const int n = H * H + 2 * H + 1;
   if (part && capB >= kHeadChunkedMinB && H % 16 == 0) {
     const int Z = std::min(kHeadChunks, cdiv(capB, kHeadRows));
