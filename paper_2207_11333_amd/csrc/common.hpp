@@ -141,6 +141,8 @@ struct GemmNTB {
   // FP32, > 1: sum K as split-K would, in this many chunks of whole 64-deep
   // pieces, each from zero, added in the order of reduce.hip
   int chunks;
+  // FP32 operands: the first segment may be any multiple of 16 up to 64 columns
+  int short0;
 };
 bool gemm_ntb_ok(const GemmNTB &g, int precision);
 hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int precision,

@@ -525,6 +525,10 @@ hipError_t launch_gemm_nt(const Dims *dims, int capM, GemmNT g, int precision,
     q.addend = g.addend;
     q.ld_add = g.ld_add;
     q.chunks = g.splits;
+    // the first layer's input (F columns padded to 16), on small grids: update
+    // linear and its reduction at 4.5k nodes FP32 21.4 -> 14.5 us, BF16 15.3 ->
+    // 10.7, one molecule 13.8 -> 7.4
+    q.short0 = g.seg[0].k % 64 && g.seg[0].k <= 64 && tiles <= kNtSmallBf16;
     const int form = precision ? 2 : 0;
     if (plain && gemm_ntb_ok(q, form))
       return launch_gemm_ntb(dims, capM, q, form, s, tag, ev0, ev1);

@@ -66,7 +66,9 @@ constexpr int waves_n(int tile) { return tile == 32 ? 2 : 4; }
 // PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo; 2: as
 // 1 with FP32 operands, rounded when a tile's fragments are used.
 // BM x BN tile, WGM x WGN waves, NST LDS stages.
-template <int PREC, int BM, int BN, int WGM, int WGN, int NST, int TAG>
+// SHORT: for a short first segment (GemmNTB::short0); instances of their own, as
+// its address selects cost the others 5 to 10 %.
+template <int PREC, int BM, int BN, int WGM, int WGN, int NST, int TAG, bool SHORT>
 __global__ void __launch_bounds__(64 * WGM * WGN, 1)
 k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   constexpr bool SPLIT = PREC != 0, A32 = PREC == 2;
@@ -105,7 +107,12 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   const int wm0 = (w / WGN) * WM, wn0 = (w % WGN) * WN;
 
   int KT = 0;
-  for (int q = 0; q < g.nseg; ++q) KT += g.seg[q].k / BKE;
+  for (int q = 0; q < g.nseg; ++q) KT += (g.seg[q].k + BKE - 1) / BKE;
+  // A short first segment ends in a tile of kv columns, tile t_short: lanes past
+  // the segment or the weight row load the row's first bytes instead, and the
+  // operand there is zeroed when the tile is used.
+  const int kv = SHORT ? g.seg[0].k % BKE : 0;
+  const int t_short = kv ? g.seg[0].k / BKE : -1;
 
   // This wave's DMA loads of a K tile: UA of A rows, UB of weight rows and
   // (BF16) UB of weight low halves, 8 rows each; load u of a kind covers rows
@@ -142,26 +149,34 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     if (left == 0) {
       const char *ap = static_cast<const char *>(g.seg[q].ptr) + db;
       const int lda = g.seg[q].ld;
-      left = g.seg[q].k / BKE;
+      left = (g.seg[q].k + BKE - 1) / BKE;
       ++q;
 #pragma unroll
       for (int u = 0; u < UA; ++u) pa[u] = ap + (size_t)rowa[u] * lda * ESA;
     }
     --left;
     char *d = smem + st + 8 * kQRow * w;
+    // byte offsets from the kept addresses, and the weights' step: one path for
+    // short tiles and others
+    const bool sh = SHORT && kv && q == 1 && left == 0;
+    int oa[NAH], ob = 0;
+    const int bstep = sh ? kv * ESZ : kQRow;
+#pragma unroll
+    for (int h = 0; h < NAH; ++h) oa[h] = sh && h * kQRow + db >= kv * ESA ? -db : h * kQRow;
+    if constexpr (SHORT) ob = sh && t_short * kQRow + db >= g.ldb * ESZ ? -db : 0;
 #pragma unroll
     for (int u = 0; u < UA; ++u) {
 #pragma unroll
-      for (int h = 0; h < NAH; ++h) dma(pa[u] + h * kQRow, d + h * SH + 8 * kQRow * NW * u);
+      for (int h = 0; h < NAH; ++h) dma(pa[u] + oa[h], d + h * SH + 8 * kQRow * NW * u);
       pa[u] += kQRow * NAH;
     }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      dma(pb[u], d + SA + 8 * kQRow * NW * u);
-      pb[u] += kQRow;
+      dma(pb[u] + ob, d + SA + 8 * kQRow * NW * u);
+      pb[u] += bstep;
       if constexpr (SPLIT) {
-        dma(pl[u], d + SA + SB + 8 * kQRow * NW * u);
-        pl[u] += kQRow;
+        dma(pl[u] + ob, d + SA + SB + 8 * kQRow * NW * u);
+        pl[u] += bstep;
       }
     }
   };
@@ -221,9 +236,10 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   // pairs; tot adds the finished ones, with more than four as two halves
   f4 tot[FOLD ? 2 : 1][TM][TN];
   int z = 0, z_end = KT, z_half = 0;
+  const int adj = KT & 1, KT64 = (KT + adj) / 2; // a short segment of one tile is a 64-deep piece
   if constexpr (FOLD) {
     if (g.chunks > 1) {
-      z_end = 2 * (KT / 2 / g.chunks);
+      z_end = 2 * (KT64 / g.chunks) - adj;
       z_half = g.chunks > 4 ? (g.chunks + 1) / 2 : g.chunks;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -256,7 +272,7 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 #pragma unroll
           for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
         ++z;
-        z_end = 2 * (KT / 2 * (z + 1) / g.chunks);
+        z_end = 2 * (KT64 * (z + 1) / g.chunks) - adj;
       }
     }
     constexpr int SF = A32 ? 0 : S;
@@ -267,6 +283,15 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int e = 0; e < 8; ++e) fa[0][h][i][e] = (__bf16)raw[h][i][e >> 2][e & 3];
+    }
+    if constexpr (SHORT) {
+      if (t == t_short) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            if ((BKE / 2) * h + (BKE / 8) * (L >> 4) >= kv) fa[SF][h][i] = V{};
+      }
     }
     mm(fa[SF][0], fb[S][0]);
     if constexpr (SPLIT) {
@@ -385,7 +410,7 @@ int tile_side(int capM, const GemmNTB &g) {
   auto grid = [&](int B) {
     return (long long)(cdiv(capM, B) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, B);
   };
-  if (grid(128) >= 256 && g.chunks <= 1) return 128;
+  if (grid(128) >= 256 && g.chunks <= 1 && !g.short0) return 128;
   const long long n = grid(64), rounds = (n + 255) / 256;
   return 10 * n >= 8 * 256 * rounds ? 64 : 32;
 }
@@ -399,15 +424,20 @@ bool gemm_ntb_ok(const GemmNTB &g, int precision) {
   if ((precision != 0) != (g.B_lo != nullptr) || (precision == 0 && g.Cb)) return false;
   if ((g.ldb * esz) % 16 || !al16(g.B) || (g.B_lo && !al16(g.B_lo))) return false;
   if (g.perm && (!g.brow || g.nb < 1 || (g.bstride * esz) % 16)) return false;
-  int boff = 0; // the segments' weight columns follow one another from 0
+  int boff = 0, pieces = 0; // the segments' weight columns follow one another from 0
+  if (g.short0 && precision == 1) return false;
   for (int q = 0; q < g.nseg; ++q) {
     const SegB &s = g.seg[q];
-    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || s.k % bke || (s.ld * esa) % 16 || s.boff != boff)
+    if (!s.ptr || !al16(s.ptr) || s.k <= 0 || (s.ld * esa) % 16 || s.boff != boff) return false;
+    if (g.short0 && q == 0) {
+      if (s.k % 16 || s.k > 64) return false;
+    } else if (s.k % bke || (g.chunks > 1 && s.k % 64)) {
       return false;
-    if (g.chunks > 1 && s.k % 64) return false;
+    }
     boff += s.k;
+    pieces += (s.k + 63) / 64;
   }
-  if (g.chunks > 1 && (precision || g.chunks > 8 || boff / 64 < g.chunks)) return false;
+  if (g.chunks > 1 && (precision || g.chunks > 8 || pieces < g.chunks)) return false;
   return true;
 }
 
@@ -419,14 +449,19 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
   const int nt = cdiv(g.Ncols, B);
   // bucketed rows: each bucket's last tile may be partial
   const dim3 grid((cdiv(capM, B) + (g.perm ? g.nb : 0)) * nt), block(64 * kQWGM * waves_n(B));
-  const int key = precision * 1000 + B * 10 + tag;
+  const int key = precision * 10000 + B * 10 + tag + (g.short0 ? 5 : 0);
   switch (key) {
-#define HGNN_NTB(P, BB, T)                                                                     \
-  case P * 1000 + BB * 10 + T:                                                                 \
-    hipExtLaunchKernelGGL((k_gemm_ntb<P, BB, BB, kQWGM, waves_n(BB), stages(P, BB, T), T>),    \
-                          grid, block, 0, s, ev0, ev1, 0, dims, g, nt);                        \
+#define HGNN_NTB(P, BB, T, SH)                                                                 \
+  case P * 10000 + BB * 10 + T + (SH ? 5 : 0):                                                 \
+    hipExtLaunchKernelGGL(                                                                     \
+        (k_gemm_ntb<P, BB, BB, kQWGM, waves_n(BB), stages(P, BB, T), T, SH>), grid, block, 0, s, \
+        ev0, ev1, 0, dims, g, nt);                                                             \
     break;
-#define HGNN_NTB_TAGS(P, BB) HGNN_NTB(P, BB, 0) HGNN_NTB(P, BB, 1) HGNN_NTB(P, BB, 2) HGNN_NTB(P, BB, 4)
+#define HGNN_NTB_TAGS(P, BB)                                                                   \
+  HGNN_NTB(P, BB, 0, false) HGNN_NTB(P, BB, 1, false) HGNN_NTB(P, BB, 2, false)                \
+  HGNN_NTB(P, BB, 4, false)
+#define HGNN_NTB_SHORT(P, BB)                                                                  \
+  HGNN_NTB(P, BB, 0, true) HGNN_NTB(P, BB, 1, true) HGNN_NTB(P, BB, 2, true) HGNN_NTB(P, BB, 4, true)
     HGNN_NTB_TAGS(0, 32)
     HGNN_NTB_TAGS(1, 32)
     HGNN_NTB_TAGS(0, 64)
@@ -435,6 +470,11 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
     HGNN_NTB_TAGS(1, 128)
     HGNN_NTB_TAGS(2, 32)
     HGNN_NTB_TAGS(2, 64)
+    HGNN_NTB_SHORT(0, 32)
+    HGNN_NTB_SHORT(0, 64)
+    HGNN_NTB_SHORT(2, 32)
+    HGNN_NTB_SHORT(2, 64)
+#undef HGNN_NTB_SHORT
 #undef HGNN_NTB_TAGS
 #undef HGNN_NTB
   default:

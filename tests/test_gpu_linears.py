@@ -2,6 +2,7 @@
 would launch.  Widths and batches that give one chunk, two to four (one running
 total), five to eight (two halves), and widths it leaves to the other form,
 against the FP64 oracle with the layer kinds' FP32 tolerance."""
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -55,4 +56,33 @@ def test_bf16_prediction_independent_of_the_batch(kind, H, graphs):
     whole = pred(synth.concat_batches(parts))
     assert torch.isfinite(whole).all()
     assert torch.equal(torch.cat([pred(b) for b in parts]), whole)
+    m.close()
+
+
+# The first layer's input is padded to 16 columns: K tiles of 16, 32 (none left
+# over in FP32), 48 and 64 columns on small grids, the staged form on large ones.
+# BF16 sums in one order; FP32 splits K by the size of the batch.
+@pytest.mark.parametrize("prec,tol", [(0, 1e-5), (1, 0.0)])
+@pytest.mark.parametrize("F", [9, 20, 40, 60])
+@pytest.mark.parametrize("H", [64, 128, 80])
+def test_first_layer(prec, tol, F, H):
+    from paper_2207_11333_amd import hgnn
+    rng = np.random.default_rng(F + H)
+    parts = []
+    for k, n in enumerate((1, 9, 120, 700)):
+        b = synth.make_batch(81 + k, n, 12, 16 if n < 700 else 32, 1)
+        parts.append(synth.Batch(b.graph_ptr, rng.standard_normal((b.num_nodes, F)).astype(np.float32),
+                                 b.edge_index, b.edge_attr, b.y))
+    m = hgnn.Model(2, H, F, 1, 4, prec, 0, 1.0)
+    m.set_params(synth.init_params(synth.ModelShape(2, H, F, 1), 82))
+
+    def pred(b):
+        p = torch.empty(b.num_graphs, device="cuda")
+        m.forward(hgnn.DeviceBatch.from_host(b), p)
+        return p
+
+    whole = pred(synth.concat_batches(parts))
+    got = torch.cat([pred(b) for b in parts])
+    assert torch.isfinite(whole).all()
+    assert float((got - whole).norm()) <= tol * float(whole.norm())
     m.close()
