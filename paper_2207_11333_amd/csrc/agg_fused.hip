@@ -17,11 +17,16 @@
 // j * 32 + f is dA column j H + c0 + f (wave column j holds aggregator j).
 // The adjoint is node_adjoint's (agg_msg.hpp), as in k_aggregate_bwd, with
 // its loads split off: the node id is fetched with the product's first
-// operand tiles, and after the product the CSR bounds, source ids and the
-// rows they gather are loaded before the dA block goes through LDS, so they
-// are in flight meanwhile.  The CSR bounds and source ids are not fetched
-// earlier: held over the K loop they raise the register count past what two
-// workgroups per CU allow, which costs more than they save.
+// operand tiles and its CSR bounds during the product; after it the source ids
+// and the rows they gather are loaded before the dA block goes through LDS, so
+// they are in flight meanwhile.
+//
+// What bounds it: dependent latencies, covered by two workgroups a CU (128
+// registers).  Ids or gathered rows fetched before the product take 144 to 180
+// registers and leave one workgroup: 18.3 -> 22.8 us (FP32, 4.5k nodes, H = 128),
+// 242 -> 321 (BF16, 40k, H = 256).  Three (80 registers, 20 spilled): 20.8 and
+// 298.  One register stage of operands rather than two, and the bounds early:
+// 18.4 -> 18.2, BF16 at 4.5k nodes 12.4 -> 11.9, 241 -> 238.
 #include "mfma_tile.hpp"
 #include "agg_msg.hpp"
 
@@ -98,72 +103,63 @@ k_agg_bwd_fused(const AggBwdFused a) {
     b_row[j] = (tc / kFusedFC) * H + c0 + tc % kFusedFC;
     b_col[j] = (v % (BK / BVEC)) * BVEC;
   }
+  const int lo = a.rowptr[node], deg = a.rowptr[node + 1] - lo;
   const int KT = (K + BK - 1) / BK;
-  // two register stages keeping raw loads; masks applied when stashed (the
-  // NT GEMM's scheme: loads stay in flight over the step's products)
-  f4 ra[2][NA], rb[2][NB], rl[2][SPLIT ? NB : 1];
-  unsigned am[2], bmk[2];
-  auto dload = [&](auto st, int t) {
-    constexpr int S = decltype(st)::value;
+  // a register stage keeping raw loads; masks applied when stashed (loads stay in
+  // flight over the step's products)
+  f4 ra[NA], rb[NB], rl[SPLIT ? NB : 1];
+  unsigned am, bmk;
+  auto dload = [&](int t) {
     const int k0 = min(t, KT - 1) * BK;
     unsigned mk = 0;
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int k = k0 + a_col[j];
-      ra[S][j] = *reinterpret_cast<const f4 *>(a.du + (size_t)a_row[j] * H + min(k, K - 4));
+      ra[j] = *reinterpret_cast<const f4 *>(a.du + (size_t)a_row[j] * H + min(k, K - 4));
       mk |= (a_ok[j] && k < K) ? 1u << j : 0u;
     }
-    am[S] = mk;
+    am = mk;
     mk = 0;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int k = k0 + b_col[j];
       const size_t off = (size_t)b_row[j] * K + min(k, K - BVEC);
-      rb[S][j] = *reinterpret_cast<const f4 *>(Bg + off);
-      if constexpr (SPLIT) rl[S][j] = *reinterpret_cast<const f4 *>(Blg + off);
+      rb[j] = *reinterpret_cast<const f4 *>(Bg + off);
+      if constexpr (SPLIT) rl[j] = *reinterpret_cast<const f4 *>(Blg + off);
       mk |= (k < K) ? 1u << j : 0u;
     }
-    bmk[S] = mk;
+    bmk = mk;
   };
-  auto stash = [&](auto st) {
-    constexpr int S = decltype(st)::value;
+  auto stash = [&]() {
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int v = tid + j * NTH;
       const int r = v / (BK / 4), c = (v % (BK / 4)) * 4;
-      store4(As + r * LDA + c, (am[S] >> j & 1u) ? ra[S][j] : zero);
+      store4(As + r * LDA + c, (am >> j & 1u) ? ra[j] : zero);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int v = tid + j * NTH;
       const int r = v / (BK / BVEC), c = (v % (BK / BVEC)) * BVEC;
-      const bool ok = bmk[S] >> j & 1u;
-      *reinterpret_cast<f4 *>(Bs + r * LDA + c) = ok ? rb[S][j] : zero; // 16 raw bytes
-      if constexpr (SPLIT) *reinterpret_cast<f4 *>(Bl + r * LDA + c) = ok ? rl[S][j] : zero;
+      const bool ok = bmk >> j & 1u;
+      *reinterpret_cast<f4 *>(Bs + r * LDA + c) = ok ? rb[j] : zero; // 16 raw bytes
+      if constexpr (SPLIT) *reinterpret_cast<f4 *>(Bl + r * LDA + c) = ok ? rl[j] : zero;
     }
   };
-  auto step = [&](auto st, int t) {
+  dload(0);
+  __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): see the TN GEMMs
+  for (int t = 0; t < KT; ++t) {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
-    stash(st);
+    stash();
     __syncthreads();
-    if (t + 2 < KT) dload(st, t + 2);
+    if (t + 1 < KT) dload(t + 1);
     mma_tile<PREC, TM, TN, LDA, BK>(As, Bs, wm0, wn0, acc);
     if constexpr (SPLIT) mma_tile<PREC, TM, TN, LDA, BK>(As, Bl, wm0, wn0, acc);
-  };
-  dload(IC<0>{}, 0);
-  if (KT > 1) dload(IC<1>{}, 1);
-  __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): see the TN GEMMs
-  int t = 0;
-  for (; t + 1 < KT; t += 2) {
-    step(IC<0>{}, t);
-    step(IC<1>{}, t + 1);
   }
-  if (t < KT) step(IC<0>{}, t);
   // the adjoint's operands that do not depend on dA are in flight while the
   // block goes through LDS
-  const int lo = a.rowptr[node], deg = a.rowptr[node + 1] - lo;
   int src[kCache];
   if (deg > 0) fetch_sources(a.csr_src, lo, deg, src);
   AdjIn in;
