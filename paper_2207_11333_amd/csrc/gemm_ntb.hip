@@ -41,11 +41,11 @@
 // 64 x 64 (32 x 16) and 32 x 32 (16 x 16, four waves) for smaller ones, whose
 // time is set by how many tiles run at once (tile_side).  FP32's matrix
 // instructions bound a small grid: a 64 x 64 tile of the update linear (K = 640)
-// is 9 us of them on its CU, whatever the other CUs do.  Stages: three for
-// 128 x 128 (144 KB in BF16), for 32 x 32 (24 or 36 KB: several share a CU; rings
-// of four to ten were slower, 9.2 to 17 us for the BF16 update linear at 4.5k
-// rows) and where another kernel needs LDS on the same CU (the layer-input
-// gradient, beside weight gradients); five for the other 64 x 64 tiles.
+// is 9 us of them on its CU, whatever the other CUs do.  Three stages: 144 KB for
+// 128 x 128 in BF16, 24 to 96 KB for the others, so that several workgroups share
+// a CU.  Five for 64 x 64 in BF16 (120 KB, one workgroup): 28k nodes, H = 64,
+// message linear 9.6 -> 12.6 us, a training step 1161 -> 1210; four to ten for
+// 32 x 32: BF16 update linear at 4.5k nodes 9.2 -> 9.5 to 17 us.
 //
 // Products and their order per output are those of the register-staged
 // kernel when it runs unsplit (FP32: per 16 k, four k-slots of
@@ -62,6 +62,7 @@ typedef __attribute__((address_space(3))) void lds_t;
 constexpr int kQRow = 128; // bytes per LDS row (one K tile)
 constexpr int kQWGM = 2; // waves of a workgroup: kQWGM x waves_n
 constexpr int waves_n(int tile) { return tile == 32 ? 2 : 4; }
+constexpr int kStages = 3; // LDS stages
 
 // PREC 0: FP32 operands and weights; 1: BF16 operands, weights as hi + lo; 2: as
 // 1 with FP32 operands, rounded when a tile's fragments are used.
@@ -394,12 +395,6 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 
 inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
-// LDS stages (160 KB of LDS per CU; see the head of this file)
-constexpr int stages(int prec, int tile, int tag) {
-  if (prec == 2) return 3; // 32 or 16 KB a stage
-  return tile == 64 && tag != 4 ? 5 : 3;
-}
-
 // Tile side by the grid it gives: 128 when that fills every CU at least once; 64
 // when its rounds over the 256 CUs are at least 0.8 full; else 32, whose tiles
 // are a quarter of the work (and more of them share a CU), at twice the operand
@@ -454,7 +449,7 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
 #define HGNN_NTB(P, BB, T, SH)                                                                 \
   case P * 10000 + BB * 10 + T + (SH ? 5 : 0):                                                 \
     hipExtLaunchKernelGGL(                                                                     \
-        (k_gemm_ntb<P, BB, BB, kQWGM, waves_n(BB), stages(P, BB, T), T, SH>), grid, block, 0, s, \
+        (k_gemm_ntb<P, BB, BB, kQWGM, waves_n(BB), kStages, T, SH>), grid, block, 0, s, \
         ev0, ev1, 0, dims, g, nt);                                                             \
     break;
 #define HGNN_NTB_TAGS(P, BB)                                                                   \
