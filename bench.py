@@ -79,10 +79,10 @@ def measured_traffic(name, sources):
 # large batches) run k_wgrad in FP32 and k_gemm_tn_tr in BF16.
 SITES = {
     "message_gemm": ("S1 message linear",
-                     "k_gemm_nt<P, 64, 128, *, 2, 4, *> | k_gemm_ntb<P, *, *, 2, 4, 2>", "mfma"),
+                     "k_gemm_ntb<P, *, *, 2, *, 3, 2, *> | k_gemm_nt<P, 64, 128, *, 2, 4, *>", "mfma"),
     "aggregate": ("S2 aggregation", "k_aggregate<1>", "hbm"),
     "update_gemm": ("S3 update linear",
-                    "k_gemm_nt<P, 64, 128, *, 1, 4, *> | k_gemm_ntb<P, *, *, 2, 4, 1>", "mfma"),
+                    "k_gemm_ntb<P, *, *, 2, *, 3, 1, *> | k_gemm_nt<P, 64, 128, *, 1, 4, *>", "mfma"),
     "update_wgrad": ("S6 update weight gradient", "k_wgrad | k_gemm_tn_tr<1, *>",
                      "mfma"),
     "agg_input_gemm": ("S6 aggregate-input gradient", "k_gemm_nt<P, 64, 128, *, 3, 4, *>", "mfma"),
@@ -90,7 +90,7 @@ SITES = {
     # not stored) and the S6 aggregate-input GEMM site has no launches
     "aggregate_bwd": ("S6 dA + S7 aggregation adjoint, fused", "k_agg_bwd_fused<P, 1, *>", "hbm"),
     "input_gemm": ("S6+S8 layer-input gradient",
-                   "k_gemm_nt<P, 64, 128, *, 4, 4, *> | k_gemm_ntb<0, 64, 64, 2, 4, 4>", "mfma"),
+                   "k_gemm_ntb<P, *, *, 2, *, 3, 4, *> | k_gemm_nt<P, 64, 128, *, 4, 4, *>", "mfma"),
     "message_wgrad": ("S8 message weight gradient", "k_wgrad | k_gemm_tn_tr<2, *>",
                       "mfma"),
 }
@@ -105,9 +105,9 @@ def site_work(site, w, N, E):
     weight per degree), F = 9 real input features in layer 0 and H after."""
     H, L, Fe = w.hidden, w.num_layers, w.edge_feat
     Fs = [9] + [H] * (L - 1)
-    rec = 2 if w.recompute else 1
+    runs = 2 * L - 1 if w.recompute else L  # S1 and S2; the last layer's are kept
     if site == "message_gemm":
-        return sum(2.0 * N * F * 2 * H for F in Fs) / L, rec * L
+        return sum(2.0 * N * F * 2 * H for F in Fs) / L, runs
     if site == "update_gemm":
         return sum(2.0 * N * (F + 4 * H) * H for F in Fs) / L, L
     if site == "update_wgrad":
@@ -119,7 +119,15 @@ def site_work(site, w, N, E):
     if site == "message_wgrad":
         return sum(2.0 * N * 2 * H * F for F in Fs) / L, L
     if site == "aggregate":
-        return float(aggregate_bytes(N, E, H, Fe)), rec * L
+        nbytes = float(aggregate_bytes(N, E, H, Fe))
+        if w.recompute:
+            # the forward pass's launches before the last layer write no arg
+            # decisions, and in BF16 those after the first A as BF16 alone
+            less = (L - 1) * 2 * H * N
+            if w.precision == 1 and H % 64 == 0:
+                less += (L - 2) * 8 * H * N
+            nbytes -= less / runs
+        return nbytes, runs
     if site == "aggregate_bwd":
         return float(aggregate_bwd_bytes(N, E, H, Fe, fused=True)), L
     raise KeyError(site)
