@@ -105,9 +105,9 @@ def site_work(site, w, N, E):
     weight per degree), F = 9 real input features in layer 0 and H after."""
     H, L, Fe = w.hidden, w.num_layers, w.edge_feat
     Fs = [9] + [H] * (L - 1)
-    runs = 2 * L - 1 if w.recompute else L  # S1 and S2; the last layer's are kept
+    rec = 2 if w.recompute else 1
     if site == "message_gemm":
-        return sum(2.0 * N * F * 2 * H for F in Fs) / L, runs
+        return sum(2.0 * N * F * 2 * H for F in Fs) / L, rec * L
     if site == "update_gemm":
         return sum(2.0 * N * (F + 4 * H) * H for F in Fs) / L, L
     if site == "update_wgrad":
@@ -119,8 +119,9 @@ def site_work(site, w, N, E):
     if site == "message_wgrad":
         return sum(2.0 * N * 2 * H * F for F in Fs) / L, L
     if site == "aggregate":
-        nbytes = float(aggregate_bytes(N, E, H, Fe))
+        nbytes, runs = float(aggregate_bytes(N, E, H, Fe)), L
         if w.recompute:
+            runs = 2 * L - 1  # the last layer's are kept
             # the forward pass's launches before the last layer write no arg
             # decisions, and in BF16 those after the first A as BF16 alone
             less = (L - 1) * 2 * H * N
