@@ -219,6 +219,7 @@ k_loss(const Dims *__restrict__ dims, int Tg, const float *__restrict__ pred,
   }
   for (int k = 0; k < Tn; ++k) {
     float s = 0.f;
+#pragma unroll 8
     for (int i = threadIdx.x; i < N; i += kHeadThreads) {
       const float d = z[(size_t)i * Tn + k] - zt[(size_t)i * Tn + k];
       s += d * d;
@@ -489,7 +490,11 @@ k_node_head_out(const Dims *__restrict__ dims, int H, int Tn, size_t capN,
   const float *q = Qn + (size_t)sh * capN * H + (size_t)i * H;
   float acc = w2[H];
 #pragma unroll 8
-  for (int c = 0; c < H; ++c) acc += w2[c] * q[c];
+  for (int c = 0; c < H; c += 4) { // H is a multiple of 16
+    const f4 v = *reinterpret_cast<const f4 *>(q + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc += w2[c + e] * v[e];
+  }
   z[t] = acc;
   if (z2) z2[t] = acc;
 }
@@ -516,7 +521,9 @@ k_node_head_err(const Dims *__restrict__ dims, int H, int Tn, size_t capN,
 // dw2_s[c] = sum_i e[i, s] Q_s[i, c] and db2_s = sum_i e[i, s] (column c = H),
 // in a fixed order: the nodes are cut into kNodeChunks contiguous chunks
 // (blockIdx.x), each chunk's sum goes to part[s][chunk][c], and
-// k_node_head_small_sum adds the chunks in order.
+// k_node_head_small_sum adds the chunks in order.  Both are chains of loads:
+// 12 and 32 in flight (4.5k nodes, two heads: 10.3 -> 5.9 us and 5.6 -> 3.1; the
+// node heads' part of k_loss with 8, 14.7 -> 8.5 for the launch).
 constexpr int kNodeChunks = 128;
 
 __global__ void __launch_bounds__(256)
@@ -532,8 +539,10 @@ k_node_head_small(const Dims *__restrict__ dims, int H, int Tn, size_t capN,
   for (int c = threadIdx.x; c <= H; c += 256) {
     float s = 0.f;
     if (c < H)
+#pragma unroll 12
       for (int i = i0; i < i1; ++i) s += e[(size_t)i * Tn + sh] * Q[(size_t)i * H + c];
     else
+#pragma unroll 12
       for (int i = i0; i < i1; ++i) s += e[(size_t)i * Tn + sh];
     out[c] = s;
   }
@@ -546,6 +555,7 @@ k_node_head_small_sum(int H, const float *__restrict__ part, float *__restrict__
   float *dw2 = gwn + (size_t)sh * (H * H + 2 * H + 1) + H * H + H;
   for (int c = threadIdx.x; c <= H; c += 256) {
     float s = 0.f;
+#pragma unroll 32
     for (int r = 0; r < kNodeChunks; ++r) s += p[(size_t)r * (H + 1) + c];
     dw2[c] = s;
   }
