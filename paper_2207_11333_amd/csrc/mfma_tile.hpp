@@ -117,6 +117,10 @@ inline int xcd_group_grid(int ngroups, int gsize) { return 8 * ((ngroups + 7) / 
 // than a dependent load per bucket.  total() is the tile count; find() gives,
 // for tile `want`, the bucket bq (-1 past the last tile), the tile's first
 // row r0 and the bucket's end r1, the same in every lane.
+// It stands before every load of its workgroup: the scan in DPP row shifts and
+// the results by readlane instead of ten trips through the LDS crossbar took
+// the FP32 training step at 4.5k nodes, H=128, from 549 to 545 us and inference
+// over 128 graphs from 156 to 154.5.
 struct BucketWalk {
   int lo, hi, nt, incl, T;
   __device__ __forceinline__ BucketWalk(const int *__restrict__ brow, int nb, int T_) : T(T_) {
@@ -125,25 +129,25 @@ struct BucketWalk {
     lo = brow[min(q, nb)];
     hi = brow[min(q + 1, nb)];
     nt = lane < kMaxBuckets ? (hi - lo + T - 1) / T : 0;
+    // the first row of 16 lanes holds every bucket: a scan by DPP row shifts
+    static_assert(kMaxBuckets == 16, "one DPP row");
     incl = nt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += t;
-    }
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
   }
   __device__ __forceinline__ void find(int want, int &bq, int &r0, int &r1) const {
     const int first = incl - nt;
     const unsigned long long hit = __ballot(nt > 0 && want >= first && want < incl);
-    bq = hit ? __ffsll((long long)hit) - 1 : -1;
+    bq = __builtin_amdgcn_readfirstlane(hit ? __ffsll((long long)hit) - 1 : -1);
     const int src = bq < 0 ? 0 : bq;
-    // wave-uniform results: keep them in scalar registers
-    r0 = __builtin_amdgcn_readfirstlane(__shfl(lo, src, 64) + (want - __shfl(first, src, 64)) * T);
-    r1 = __builtin_amdgcn_readfirstlane(__shfl(hi, src, 64));
-    bq = __builtin_amdgcn_readfirstlane(bq);
+    // wave-uniform results, in scalar registers
+    r0 = __builtin_amdgcn_readlane(lo, src) + (want - __builtin_amdgcn_readlane(first, src)) * T;
+    r1 = __builtin_amdgcn_readlane(hi, src);
   }
   __device__ __forceinline__ int total() const {
-    return __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+    return __builtin_amdgcn_readlane(incl, 15);
   }
 };
 
