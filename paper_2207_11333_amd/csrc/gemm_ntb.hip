@@ -110,8 +110,8 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
   int KT = 0;
   for (int q = 0; q < g.nseg; ++q) KT += (g.seg[q].k + BKE - 1) / BKE;
   // A short first segment ends in a tile of kv columns, tile t_short: lanes past
-  // the segment or the weight row load the row's first bytes instead, and the
-  // operand there is zeroed when the tile is used.
+  // the segment or the weight row load the row's first bytes instead, and both
+  // operands there are zeroed when the tile is used.
   const int kv = SHORT ? g.seg[0].k % BKE : 0;
   const int t_short = kv ? g.seg[0].k / BKE : -1;
 
@@ -157,8 +157,10 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     }
     --left;
     char *d = smem + st + 8 * kQRow * w;
-    // byte offsets from the kept addresses, and the weights' step: one path for
-    // short tiles and others
+    // Byte offsets from the kept addresses, and the weights' step: selected, on one
+    // path for short tiles and others.  With a branch for the short tile that
+    // returned early the compiler moved the kept addresses' additions so that one
+    // of the copies of this code loaded from an address never written.
     const bool sh = SHORT && kv && q == 1 && left == 0;
     int oa[NAH], ob = 0;
     const int bstep = sh ? kv * ESZ : kQRow;
@@ -287,11 +289,18 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
     }
     if constexpr (SHORT) {
       if (t == t_short) {
+        // both operands: the weights there may be infinite
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+          const bool past = (BKE / 2) * h + (BKE / 8) * (L >> 4) >= kv;
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-            if ((BKE / 2) * h + (BKE / 8) * (L >> 4) >= kv) fa[SF][h][i] = V{};
+          for (int i = 0; i < TM; ++i) fa[SF][h][i] = past ? V{} : fa[SF][h][i];
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            fb[S][h][j] = past ? V{} : fb[S][h][j];
+            if constexpr (SPLIT) fl[S][h][j] = past ? V{} : fl[S][h][j];
+          }
+        }
       }
     }
     mm(fa[SF][0], fb[S][0]);
