@@ -922,6 +922,15 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   }
   float *PQ = w.PQ[slot], *A = w.A[slot];
   const uint8_t *args = w.args[slot];
+  // The weight gradients' LDS-DMA loads take 16-byte aligned rows: a caller's
+  // input off that grid (its recomputation above reads it as the forward did)
+  // is copied to a du buffer that the per-operation path leaves unused.
+  if ((uintptr_t)hin & 15) {
+    float *copy = w.duL ? w.duL : w.dh0;
+    if (hipError_t e = launch_pad_copy(ex.dims, ex.N, hin, H, copy, H, s); e != hipSuccess)
+      return hip_fail(c, e, "layer input");
+    hin = copy;
+  }
   // D of this layer: odd layers use the second buffer when it exists (no
   // recomputation), so that writing it need not wait for the previous
   // layer's weight gradients, which read the other one
