@@ -621,8 +621,8 @@ __global__ void __launch_bounds__(T) k_csr_small(const CsrSmall a) {
     const bool in = s >= 0 && s < N && d >= 0 && d < N;
     bool live = k < E;
     if (live && !in) bad |= ERR_EDGE_RANGE;
-    live = live && in;
-    if (live && (!ok || s_graph[s] != s_graph[d])) {
+    live = live && in && ok;
+    if (live && s_graph[s] != s_graph[d]) {
       bad |= ERR_EDGE_CROSS;
       live = false;
     }
