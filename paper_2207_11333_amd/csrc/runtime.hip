@@ -71,7 +71,9 @@ constexpr long long kPairElems = 640 << 10;
 constexpr int kColsumChunks = 128;
 
 // Batches below this many nodes keep every layer's du and D and run all
-// weight gradients in one launch at the end of the backward pass.
+// weight gradients in one launch at the end of the backward pass: the batch
+// counts, not the context's capacity (six layers of H = 128 at 4.5k nodes in a
+// context that has seen 20k: XXX).
 constexpr int kDeferNodes = 16384;
 constexpr size_t kDeferPartBytes = size_t(1) << 30; // and partial sums up to this
 
@@ -116,7 +118,8 @@ void free_work(Exec &ex) {
   for (void **p : ptrs) dfree(*p);
   for (auto &p : w.gcA) dfree(reinterpret_cast<void *&>(p));
   w.gcA.clear();
-  w.wg_n = 0;
+  w.wg_n = w.deferN = 0;
+  w.no_defer = false;
   for (auto &p : w.hbuf) dfree(reinterpret_cast<void *&>(p));
   for (auto &p : w.hbuf_b) dfree(reinterpret_cast<void *&>(p));
   w.hbuf_b.clear();
@@ -341,6 +344,22 @@ static size_t defer_table_bytes(const hgnn_ctx *c) {
   return wg_count(c) * (sizeof(WgJob) + sizeof(ReduceJob));
 }
 
+// The buffers of that pass, for batches of up to n nodes and `part` floats of
+// partial sums.  PNA and GraphSAGE products read every layer's du, PNA and CGCNN
+// ones every layer's D.
+template <typename F>
+static bool for_each_defer_buffer(const hgnn_ctx *c, Work &w, int n, size_t part, F &&f) {
+  const bool pna = c->kind == HGNN_GC_PNA;
+  const size_t LN = (size_t)c->L * n, H = c->H;
+  const size_t ldD = pna ? (2 + c->Fe) * H : (4 + 2 * c->Fe) * H;
+  bool ok = true;
+  if (c->kind != HGNN_GC_CGCNN) ok = ok && f(w.duL, LN * H);
+  if (c->kind != HGNN_GC_SAGE) ok = ok && f(w.DL, LN * ldD);
+  ok = ok && f(w.wg_part, part) && f(w.wg_tab, defer_table_bytes(c));
+  if (pna) ok = ok && f(w.wg_zscale, (size_t)2 * c->L * (kMaxTnSplits + c->nb));
+  return ok;
+}
+
 // Every capacity-sized buffer of an Exec, with its element count: the one
 // table used both to allocate and to price a batch for HBM admission.
 template <typename F>
@@ -410,17 +429,9 @@ static bool for_each_buffer(const hgnn_ctx *c, Work &w, int capB, int capN, int 
     if (Tn > 0)
       ok = ok && f(w.dQn, (size_t)Tn * capN * H) && f(w.en, (size_t)capN * Tn) &&
            f(w.dhn, (size_t)capN * H);
-    const size_t defer = defer_floats(c, capN);
+    const size_t defer = w.no_defer ? 0 : defer_floats(c, capN);
     ok = ok && f(w.du, (size_t)capN * H);
-    if (defer) {
-      // PNA and GraphSAGE products read every layer's du, PNA and CGCNN ones
-      // every layer's D
-      const size_t ldD = pna ? (2 + c->Fe) * H : (4 + 2 * c->Fe) * H;
-      if (c->kind != HGNN_GC_CGCNN) ok = ok && f(w.duL, (size_t)L * capN * H);
-      if (c->kind != HGNN_GC_SAGE) ok = ok && f(w.DL, (size_t)L * capN * ldD);
-      ok = ok && f(w.wg_part, defer) && f(w.wg_tab, defer_table_bytes(c));
-      if (pna) ok = ok && f(w.wg_zscale, (size_t)2 * L * (kMaxTnSplits + c->nb));
-    }
+    if (defer) ok = ok && for_each_defer_buffer(c, w, capN, defer, f);
     if (!defer || c->kind == HGNN_GC_CGCNN)
       ok = ok && f(w.dh0, (size_t)capN * H) && f(w.dh1, (size_t)capN * H);
     if (pna) {
@@ -473,12 +484,13 @@ size_t carve_work(const hgnn_ctx *c, Exec &ex, int B, int N, int E, char *base,
   return off;
 }
 
-// The device tables of the deferred weight gradients and their reduction:
-// every address in them belongs to the context or to this workspace.
-static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int capN) {
+// The device tables of the deferred weight gradients and their reduction, for
+// batches of up to nodes: every address in them belongs to the context or to this
+// workspace.  Written in s's order; waits for it.
+static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int nodes, hipStream_t s) {
   w.wg_n = 0;
   if (!w.wg_tab) return hipSuccess;
-  auto v = wg_jobs(c, capN);
+  auto v = wg_jobs(c, nodes);
   const int n = (int)v.size(), H = c->H, L = c->L;
   if (n != wg_count(c)) return hipErrorInvalidValue;
   std::vector<uint8_t> tab(defer_table_bytes(c));
@@ -498,7 +510,7 @@ static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int capN) {
     j.seg[0].ptr = l > 0 ? w.hbuf[l - 1] : c->kind == HGNN_GC_CGCNN && l == 0 ? w.h0 : w.xpad;
     red[k] = ReduceJob{};
     if (c->kind == HGNN_GC_PNA && upd) {
-      j.X = w.duL + (size_t)l * capN * H;
+      j.X = w.duL + (size_t)l * nodes * H;
       j.seg[1].ptr = w.A[l];
       j.perm = w.csr.perm;
       j.brow = w.csr.brow;
@@ -507,14 +519,14 @@ static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int capN) {
       red[k].upd = 1;
       red[k].u = upd_reduce(c, l, j, c->grads + c->ld[l].off);
     } else if (c->kind == HGNN_GC_PNA) {
-      j.X = w.DL + (size_t)l * capN * j.ldx;
+      j.X = w.DL + (size_t)l * nodes * j.ldx;
       red[k].m = msg_reduce(c, l, j, c->grads + c->ld[l].off);
     } else if (c->kind == HGNN_GC_SAGE) {
-      j.X = w.duL + (size_t)l * capN * H;
+      j.X = w.duL + (size_t)l * nodes * H;
       j.seg[1].ptr = w.gcA[l];
       red[k].m = sage_reduce(c, l, j);
     } else if (l >= 0) {
-      j.X = w.DL + (size_t)l * capN * j.ldx;
+      j.X = w.DL + (size_t)l * nodes * j.ldx;
       red[k].m = cgcnn_reduce(c, l, j);
     } else { // the embedding's, from where L steps between the two buffers end
       j.X = L % 2 ? w.dh1 : w.dh0;
@@ -527,9 +539,46 @@ static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int capN) {
     jobs[k] = j;
   }
   w.red_most = reduce_layout(red, n);
-  hipError_t e = hipMemcpy(w.wg_tab, tab.data(), tab.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess) w.wg_n = n;
-  return e;
+  hipError_t e = hipMemcpyAsync(w.wg_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return e;
+  w.wg_n = n;
+  w.deferN = nodes;
+  return hipSuccess;
+}
+
+// Whether the backward pass of the prepared batch runs its weight gradients in
+// one launch.  A context whose capacity is past kDeferNodes gets the buffers at
+// its first backward pass over a batch below (unless s is being captured: that
+// pass goes layer by layer).  Without the memory for them it does so too, and
+// nothing fails.
+static bool defer_wgrads(hgnn_ctx *c, Exec &ex, hipStream_t s) {
+  Work &w = ex.w;
+  if (w.wg_n > 0) return ex.N <= w.deferN;
+  if (w.no_defer || ex.N >= kDeferNodes) return false;
+  const int nodes = std::min(w.capN, kDeferNodes - 1);
+  const size_t part = defer_floats(c, nodes);
+  if (!part) return !(w.no_defer = true);
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  // (allowed while another thread captures)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const bool ok = for_each_defer_buffer(c, w, nodes, part,
+                                        [&](auto &p, size_t n) { return dalloc(p, n) == hipSuccess; }) &&
+                  build_wg_tables(c, w, nodes, s) == hipSuccess;
+  if (!ok) {
+    for (void **p : {(void **)&w.duL, (void **)&w.DL, (void **)&w.wg_part, (void **)&w.wg_tab,
+                     (void **)&w.wg_zscale})
+      dfree(*p);
+    (void)hipGetLastError(); // not the next launch's error
+    w.no_defer = true;
+  }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return ok;
 }
 
 int ensure_work(hgnn_ctx *c, Exec &ex, int B, int N, int E) {
@@ -547,7 +596,7 @@ int ensure_work(hgnn_ctx *c, Exec &ex, int B, int N, int E) {
     free_work(ex);
     return fail(HGNN_ENOMEM, "hipMalloc failed for the batch workspace");
   }
-  if (hipError_t et = build_wg_tables(c, w, capN); et != hipSuccess) {
+  if (hipError_t et = build_wg_tables(c, w, capN, nullptr); et != hipSuccess) {
     free_work(ex);
     return hip_fail(c, et, "weight-gradient tables");
   }
@@ -900,8 +949,8 @@ static hipError_t launch_deferred_wgrads(hgnn_ctx *c, Exec &ex, hipStream_t s) {
 // aggregation adjoint two layers on (with one D buffer, the next one's).
 // Not with recomputation, which rewrites the stored A and PQ at the start of
 // the next layer.
-// defer_wg: leave the weight gradients to the caller (deferred_wgrads), who
-// has given this layer a du and a D of its own; everything runs on s then.
+// defer_wg: leave the weight gradients to the caller (launch_deferred_wgrads), who
+// has given this layer a du of its own (its D is too); everything runs on s then.
 int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h_in,
                    const float *h_out, const float *dh_out, float *dh_in, float *dwl,
                    hipStream_t s, bool dh_out_masked = false, bool mask_dh_in = false,
@@ -924,9 +973,10 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const uint8_t *args = w.args[slot];
   // The weight gradients' LDS-DMA loads take 16-byte aligned rows: a caller's
   // input off that grid (its recomputation above reads it as the forward did)
-  // is copied to a du buffer that the per-operation path leaves unused.
+  // is copied to a du buffer that the per-operation path leaves unused (duL holds
+  // the whole capacity where there is no dh0).
   if ((uintptr_t)hin & 15) {
-    float *copy = w.duL ? w.duL : w.dh0;
+    float *copy = w.dh0 ? w.dh0 : w.duL;
     if (hipError_t e = launch_pad_copy(ex.dims, ex.N, hin, H, copy, H, s); e != hipSuccess)
       return hip_fail(c, e, "layer input");
     hin = copy;
@@ -934,9 +984,9 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // D of this layer: odd layers use the second buffer when it exists (no
   // recomputation), so that writing it need not wait for the previous
   // layer's weight gradients, which read the other one
-  float *Dl = w.D;
-  if (w.DL) Dl = w.DL + (defer_wg ? (size_t)l * w.capN * ldD : 0);
-  else if ((l & 1) && w.D2) Dl = w.D2;
+  float *Dl = (l & 1) && w.D2 ? w.D2 : w.D;
+  if (defer_wg) Dl = w.DL + (size_t)l * w.deferN * ldD;
+  else if (!Dl) Dl = w.DL;
   const float *bm = wl + (d.obm - d.off);
   hipError_t e = hipSuccess;
   const float *du = dh_out;
@@ -950,8 +1000,12 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // more than they hide: one layer of H = 128 at 4.5k nodes, forward and
   // backward, 142 -> 111 us on the device and 215 -> 144 with the host.  Larger
   // ones fork: four recomputed layers of H = 256 at 3.5k nodes (0.9M) took 820
-  // us with the fork and 899 without.
-  const bool pair = !defer_wg && c->nb && (long long)ex.N * H <= kPairElems;
+  // us with the fork and 899 without.  A whole pass that keeps its activations
+  // forks too: its launches lie on the chain (six layers of H = 128 at 4.5k nodes,
+  // without the one launch at its end: FP32 588 us with the fork and 687 without, BF16
+  // 492 and 547).
+  const bool pair = !defer_wg && c->nb && (long long)ex.N * H <= kPairElems &&
+                    (c->recompute || !dh_out_masked);
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);
@@ -1443,10 +1497,9 @@ static void wait_pending_join(hgnn_ctx *c, hipStream_t s, hipError_t &e) {
   }
 }
 
-static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_t s) {
+static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, bool defer, hipStream_t s) {
   Work &w = ex.w;
   const int H = c->H, Fe = c->Fe;
-  const bool defer = w.wg_n > 0; // all weight gradients at the end, everything on s
   hipError_t e = hipSuccess;
   wait_pending_join(c, s, e); // left by a backward that failed part-way
   if (e != hipSuccess) return hip_fail(c, e, "join");
@@ -1493,7 +1546,7 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
       }
     } else {
       const int ldD = (4 + 2 * Fe) * H;
-      float *gcD = defer ? w.DL + (size_t)l * w.capN * ldD : (l & 1) ? w.gcD1 : w.gcD;
+      float *gcD = defer ? w.DL + (size_t)l * w.deferN * ldD : (l & 1) ? w.gcD1 : w.gcD;
       {
         TimedLaunch tl(c, ex, SITE_AGGREGATE_BWD, s);
         e = launch_cg_aggregate_bwd(ex.dims, ex.N, H, Fe, w.csr.rowptr, w.csr.csr_src,
@@ -1547,8 +1600,8 @@ static int gc_backward(hgnn_ctx *c, Exec &ex, float *cur, float *nxt, hipStream_
     }
     if (defer) {
       if (c->kind == HGNN_GC_SAGE) { // every layer's du stays
-        cur = l ? w.duL + (size_t)(l - 1) * w.capN * H : cur;
-        nxt = l > 1 ? w.duL + (size_t)(l - 2) * w.capN * H : nullptr;
+        cur = l ? w.duL + (size_t)(l - 1) * w.deferN * H : cur;
+        nxt = l > 1 ? w.duL + (size_t)(l - 2) * w.deferN * H : nullptr;
       } else {
         std::swap(cur, nxt);
       }
@@ -2121,10 +2174,10 @@ int hgnn_backward(hgnn_ctx *c, const float *dpred, void *stream) {
   if (!c->staged_from_params) return fail(HGNN_EINVAL, "weights changed since the forward");
   hipStream_t s = (hipStream_t)stream;
   Work &w = c->ex.w;
-  const bool defer = w.wg_n > 0;
-  const size_t NH = (size_t)w.capN * c->H;
+  const bool defer = defer_wgrads(c, c->ex, s);
+  const size_t NH = (size_t)w.deferN * c->H;
   float *cur = w.dh0, *nxt = w.dh1;
-  if (w.duL) {
+  if (defer && w.duL) {
     cur = w.duL + (c->L - 1) * NH;
     nxt = c->L > 1 ? cur - NH : nullptr;
   }
@@ -2133,7 +2186,7 @@ int hgnn_backward(hgnn_ctx *c, const float *dpred, void *stream) {
   int rc = head_backward(c, c->ex, c->params + c->off_head, c->ex.target, dpred, cur,
                          c->grads + c->off_head, s, w.hbuf[c->L - 1], w.hbuf[c->L - 1]);
   if (rc) return rc;
-  if (c->kind != HGNN_GC_PNA) return gc_backward(c, c->ex, cur, nxt, s);
+  if (c->kind != HGNN_GC_PNA) return gc_backward(c, c->ex, cur, nxt, defer, s);
   if (c->join_pending) { // left by a backward that failed part-way
     c->join_pending = false;
     if (hipError_t e = hipStreamWaitEvent(s, c->join_ev, 0); e != hipSuccess)

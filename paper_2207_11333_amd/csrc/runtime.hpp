@@ -39,8 +39,11 @@ struct Work {
   float *dh0 = nullptr, *dh1 = nullptr;
   // Small batches keep every layer's du and D (and partial sums) until the
   // end of the backward pass, whose weight gradients then run in one launch
-  // (empty / null otherwise: one layer's at a time)
-  float *duL = nullptr, *DL = nullptr;   // [L][N, H], [L][N, (2 + Fe) H]
+  // (empty / null otherwise: one layer's at a time).  deferN: the nodes a batch
+  // may have for that, the row stride of the two; no_defer: not to be allocated.
+  int deferN = 0;
+  bool no_defer = false;
+  float *duL = nullptr, *DL = nullptr;   // [L][deferN, H], [L][deferN, (2 + Fe) H]
   float *wg_part = nullptr, *wg_zscale = nullptr;
   uint8_t *wg_tab = nullptr;             // products [wg_n], then reductions [wg_n]
   int wg_n = 0, wg_tile = 0, wg_most = 0, red_most = 0;
