@@ -184,6 +184,9 @@ int hgnn_param_views(hgnn_ctx *ctx, float **params_dev, float **grads_dev);
  * failed launch would, and the context stays in HGNN_ESTATE until
  * hgnn_set_state.  n = 0 disables it.  For tests of callers' recovery. */
 int hgnn_debug_fail_after(hgnn_ctx *ctx, int32_t n);
+/* Test hook: the n-th allocation of a batch workspace from now on fails as
+ * without memory.  n = 0 disables it. */
+int hgnn_debug_fail_alloc(hgnn_ctx *ctx, int32_t n);
 /* Synchronise the stream and report the device error word (EINVAL with a
  * message naming the first failed check) or a sticky ESTATE. */
 int hgnn_check(hgnn_ctx *ctx, void *stream);

@@ -547,6 +547,12 @@ static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int nodes, hipStream_t s
   return hipSuccess;
 }
 
+// One workspace allocation (hgnn_debug_fail_alloc can make it fail).
+template <typename T> static bool work_alloc(hgnn_ctx *c, T *&p, size_t n) {
+  if (c->fail_alloc > 0 && --c->fail_alloc == 0) return false;
+  return dalloc(p, n) == hipSuccess;
+}
+
 // Whether the backward pass of the prepared batch runs its weight gradients in
 // one launch.  A context whose capacity is past kDeferNodes gets the buffers at
 // its first backward pass over a batch below (unless s is being captured: that
@@ -568,7 +574,7 @@ static bool defer_wgrads(hgnn_ctx *c, Exec &ex, hipStream_t s) {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   const bool ok = for_each_defer_buffer(c, w, nodes, part,
-                                        [&](auto &p, size_t n) { return dalloc(p, n) == hipSuccess; }) &&
+                                        [&](auto &p, size_t n) { return work_alloc(c, p, n); }) &&
                   build_wg_tables(c, w, nodes, s) == hipSuccess;
   if (!ok) {
     for (void **p : {(void **)&w.duL, (void **)&w.DL, (void **)&w.wg_part, (void **)&w.wg_tab,
@@ -589,9 +595,17 @@ int ensure_work(hgnn_ctx *c, Exec &ex, int B, int N, int E) {
   const int capB = B > w.capB ? B : w.capB;
   const int capN = N > w.capN ? N : w.capN;
   const int capE = E > w.capE ? E : w.capE;
-  free_work(ex);
-  const bool ok = for_each_buffer(c, w, capB, capN, capE, ex.inference_only,
-                                  [&](auto &p, size_t n) { return dalloc(p, n) == hipSuccess; });
+  // without the memory for the one-launch weight gradients, the buffers of a
+  // pass layer by layer
+  const bool defer = !ex.inference_only && defer_floats(c, capN) > 0;
+  bool ok = false;
+  for (int k = defer ? 0 : 1; k < 2 && !ok; ++k) {
+    free_work(ex);
+    w.no_defer = k == 1 && defer;
+    ok = for_each_buffer(c, w, capB, capN, capE, ex.inference_only,
+                         [&](auto &p, size_t n) { return work_alloc(c, p, n); });
+    if (!ok) (void)hipGetLastError(); // not the next launch's error
+  }
   if (!ok) {
     free_work(ex);
     return fail(HGNN_ENOMEM, "hipMalloc failed for the batch workspace");
@@ -2076,6 +2090,12 @@ int hgnn_op_generation(const hgnn_ctx *c, int64_t *out) {
 int hgnn_debug_fail_after(hgnn_ctx *c, int32_t n) {
   if (!c || n < 0) return fail(HGNN_EINVAL, "context is NULL or n < 0");
   c->fail_after = n;
+  return HGNN_OK;
+}
+
+int hgnn_debug_fail_alloc(hgnn_ctx *c, int32_t n) {
+  if (!c || n < 0) return fail(HGNN_EINVAL, "context is NULL or n < 0");
+  c->fail_alloc = n;
   return HGNN_OK;
 }
 

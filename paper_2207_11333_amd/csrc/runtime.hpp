@@ -158,6 +158,7 @@ struct hgnn_ctx {
   hgnn::Exec na;
   int sticky = 0;
   int fail_after = 0; // test-only failure injection (hgnn_debug_fail_after)
+  int fail_alloc = 0; // and of workspace allocations (hgnn_debug_fail_alloc)
   hgnn::Server *server = nullptr;
   hgnn::SiteTimer timer;
   // The backward pass runs the weight-gradient GEMMs on this stream,

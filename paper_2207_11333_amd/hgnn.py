@@ -87,6 +87,7 @@ _SIGS = {
                         ctypes.POINTER(_P)], _I),
     "hgnn_param_views": ([_P, ctypes.POINTER(_P), ctypes.POINTER(_P)], _I),
     "hgnn_debug_fail_after": ([_P, _I], _I),
+    "hgnn_debug_fail_alloc": ([_P, _I], _I),
     "hgnn_destroy": ([_P], None),
     "hgnn_num_params": ([_P, ctypes.POINTER(ctypes.c_int64)], _I),
     "hgnn_set_params": ([_P, _P, _P], _I),
@@ -389,6 +390,10 @@ class Model:
     def debug_fail_after(self, n: int):
         """Test hook: the n-th layer call from now fails as a launch would."""
         _check(lib().hgnn_debug_fail_after(self.handle, n))
+
+    def debug_fail_alloc(self, n: int):
+        """Test hook: the n-th workspace allocation from now fails as without memory."""
+        _check(lib().hgnn_debug_fail_alloc(self.handle, n))
 
     def check(self):
         _check(lib().hgnn_check(self.handle, _stream()))

@@ -1,7 +1,7 @@
 """Small batches in a context that has seen a large one: their backward pass forms
 the weight gradients in one launch as in a fresh context, adds the buffers for that
-at its first such pass, and does without them under stream capture.  The gradients
-are the same bits on every route."""
+at its first such pass, and does without them under stream capture or where their
+allocation fails.  The gradients are the same bits on every route."""
 import numpy as np
 import pytest
 
@@ -99,3 +99,26 @@ def test_captured_before_any_eager_pass(kind, prec):
         assert torch.equal(la.grads(), big)
         assert torch.equal(sm.grads(), want)
     m.close()
+
+
+# a small context's first workspace, and the buffers added to a grown one
+@pytest.mark.parametrize("grown", [False, True])
+@pytest.mark.parametrize("kind,prec", KINDS)
+def test_without_memory_for_the_one_launch(kind, prec, grown):
+    small, large = _batches()
+    want = _Step(_model(kind, prec), small).grads()
+    for n in (1, 2, 3, 4, 30):
+        m = _model(kind, prec)
+        sm = _Step(m, small)
+        if grown:
+            big = _Step(m, large).grads()
+        m.debug_fail_alloc(n)
+        assert torch.equal(sm.grads(), want)
+        m.debug_fail_alloc(0)
+        buffers = 5 if kind == "pna" else 3  # of the one launch; a workspace has over 30
+        assert (_launches(m, sm) == 1) == (grown and n > buffers)
+        if grown:
+            assert torch.equal(_Step(m, large).grads(), big)
+        assert torch.equal(sm.grads(), want)
+        m.check()
+        m.close()
