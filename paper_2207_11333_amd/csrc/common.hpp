@@ -200,10 +200,12 @@ struct WgJob {
   const float *table;
   float *zscale;
   int sum_from; // rows of P from here on need only column N (M: none)
-  int rot;      // XCD of chunk 0 (deals the chunks of a list of jobs evenly)
+  int rot;      // XCD of chunk or row 0 (deals those of a list of jobs evenly)
   int by_row;   // deal rows of output tiles to the XCDs, not whole chunks
 };
 bool wg_job_ok(const WgJob &j);
+bool wg_by_row(const WgJob &j, bool alone); // FP32
+int wg_groups(const WgJob &j, int tile);    // chunks or rows dealt
 int wg_blocks(const WgJob &j, int tile);
 // One FP32 product by itself.
 hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEvent_t ev0 = nullptr,

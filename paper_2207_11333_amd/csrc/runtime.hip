@@ -532,8 +532,9 @@ static hipError_t build_wg_tables(hgnn_ctx *c, Work &w, int nodes, hipStream_t s
       j.X = L % 2 ? w.dh1 : w.dh0;
       red[k].m = emb_reduce(c, j);
     }
-    j.rot = rot; // go on where the last job's chunks ended
-    rot = (rot + j.splits + j.nb) % 8;
+    j.by_row = !c->prec && wg_by_row(j, false);
+    j.rot = rot; // go on where the last job's chunks or rows ended
+    rot = (rot + wg_groups(j, w.wg_tile)) % 8;
     if (!wg_job_ok(j)) return hipErrorInvalidValue;
     w.wg_most = std::max(w.wg_most, wg_blocks(j, w.wg_tile));
     jobs[k] = j;

@@ -268,18 +268,15 @@ __device__ __forceinline__ void wgrad_tile(const Dims *__restrict__ dims, const 
   // one XCD (the block index's remainder by 8), whose L2 serves the re-reads
   const WgTiles tl = wg_tiles(j, B);
   const int Z = j.splits + (j.perm ? j.nb : 0);
-  // (by_row: a row of them).  The chunks of one product that do not deal evenly
-  // to the XCDs go by rows: 12 chunks of 84 tiles (24k nodes, H = 256) would
-  // give half the XCDs two and the others one (a training step of four layers
-  // 3521 -> 3382 us).
-  const int l = blk >> 3;
+  // (by_row: a row of them; see wg_by_row)
+  const int l = blk >> 3, x = (blk - j.rot) & 7;
   int z, jt;
   if (j.by_row) {
-    const int g = (l / tl.nt) * 8 + (blk & 7);
+    const int g = (l / tl.nt) * 8 + x;
     z = g / tl.rows;
     jt = (g % tl.rows) * tl.nt + l % tl.nt;
   } else {
-    z = (l / tl.tpc) * 8 + ((blk - j.rot) & 7);
+    z = (l / tl.tpc) * 8 + x;
     jt = l % tl.tpc;
   }
   if (z >= Z || jt >= tl.tpc) return;
@@ -352,18 +349,37 @@ bool wg_job_ok(const WgJob &j) {
 // operands are read half as often, where that gives every CU two workgroups.
 int wg_tile_all(int blocks128, int precision) { return precision && blocks128 >= 512 ? 128 : 64; }
 
-int wg_blocks(const WgJob &j, int tile) {
+int wg_groups(const WgJob &j, int tile) {
   const int Z = j.splits + (j.perm ? j.nb : 0);
+  return j.by_row ? Z * wg_tiles(j, tile).rows : Z;
+}
+
+int wg_blocks(const WgJob &j, int tile) {
   const WgTiles t = wg_tiles(j, tile);
-  if (j.by_row) return 8 * ((Z * t.rows + 7) / 8) * t.nt;
-  return 8 * ((Z + 7) / 8) * t.tpc;
+  return 8 * ((wg_groups(j, tile) + 7) / 8) * (j.by_row ? t.nt : t.tpc);
+}
+
+// Which FP32 products deal rows of tiles to the XCDs.  Whole chunks keep a chunk's
+// rows in one L2, but few chunks leave XCDs idle, the more so where they are unequal
+// (bucketed ones).  In a list, by chunks and by rows (a training step): H = 512,
+// with 7 and 3 chunks a layer, one layer at 14k nodes 1920 and 1402 us, two 3847 and
+// 3124; one CGCNN layer 2275 and 1323; H = 256, with 12 and 9, one layer 562 and
+// 511, four 2090 and 1961; H = 192, with 16 and 15, six layers 1938 and 1897 but one
+// 365 and 370; H = 128, with 29 each, single layers at 1k to 5k nodes up to 3 % slower
+// by rows.  BF16 products too: GraphSAGE and CGCNN of H = 256 at 14k nodes 4 and 2 %.
+// Launched alone (24k nodes): three layers of H = 384, 8 chunks, 5770 and 4869 us; of
+// H = 192 1692 and 1645; and rows where the chunks do not deal evenly: 12 of H = 256,
+// four layers, 3521 and 3382.
+bool wg_by_row(const WgJob &j, bool alone) {
+  const int Z = j.splits + (j.perm ? j.nb : 0);
+  return Z < 14 || (alone && (Z <= 16 || Z % 8));
 }
 
 hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEvent_t ev0,
                         hipEvent_t ev1) {
   if (!wg_job_ok(j)) return hipErrorInvalidValue;
   WgJob k = j;
-  k.by_row = (j.splits + (j.perm ? j.nb : 0)) % 8 != 0;
+  k.by_row = wg_by_row(j, true);
   hipExtLaunchKernelGGL(k_wgrad, dim3(wg_blocks(k, 64)), dim3(256), 0, s, ev0, ev1, 0, dims, k);
   return hipGetLastError();
 }
@@ -371,13 +387,15 @@ hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEven
 hipError_t launch_wgrad_pair(const Dims *dims, const WgJob &j0, const WgJob &j1, int precision,
                              hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   if (!wg_job_ok(j0) || !wg_job_ok(j1)) return hipErrorInvalidValue;
-  WgJob k1 = j1;
-  k1.rot = (j0.splits + j0.nb) % 8;
   const int tile = wg_tile_all(wg_blocks(j0, 128) + wg_blocks(j1, 128), precision);
-  const int n0 = wg_blocks(j0, tile);
+  WgJob k0 = j0, k1 = j1;
+  k0.by_row = !precision && wg_by_row(j0, false);
+  k1.by_row = !precision && wg_by_row(j1, false);
+  k1.rot = wg_groups(k0, tile) % 8;
+  const int n0 = wg_blocks(k0, tile);
   const dim3 grid(n0 + wg_blocks(k1, tile));
 #define HGNN_WG(P, W)                                                                          \
-  hipExtLaunchKernelGGL((k_wgrad_pair<P, W>), grid, dim3(256), 0, s, ev0, ev1, 0, dims, j0, k1, n0)
+  hipExtLaunchKernelGGL((k_wgrad_pair<P, W>), grid, dim3(256), 0, s, ev0, ev1, 0, dims, k0, k1, n0)
   if (!precision) HGNN_WG(0, 2);
   else if (tile == 128) HGNN_WG(1, 4);
   else HGNN_WG(1, 2);

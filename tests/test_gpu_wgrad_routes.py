@@ -1,0 +1,60 @@
+"""The routes of the weight gradients against one another: every layer's in one
+launch, a layer's two products on the second stream (FP32 k_wgrad, BF16
+k_gemm_tn_tr) and both in one launch.  All sum the same chunks in the same order,
+so the gradients are equal bit for bit."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2207_11333_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _hg():
+    from paper_2207_11333_amd import hgnn
+    return hgnn
+
+
+def _grads(b, params, L, H, prec, recompute=0, maxd=4, kind="pna", fail=0):
+    hg = _hg()
+    m = hg.Model(L, H, 9, 1, maxd, prec, recompute, 1.08, kind=kind)
+    m.set_params(params)
+    m.debug_fail_alloc(fail)  # 1: without the buffers of the one launch
+    db = hg.DeviceBatch.from_host(b)
+    pred, loss = torch.empty(b.num_graphs, device="cuda"), torch.empty(1, device="cuda")
+    m.forward(db, pred, loss, validate=True)
+    m.backward()
+    g = m.grads().cpu().numpy()
+    m.close()
+    return g
+
+
+# hidden widths from 29 chunks a product down to 2 (dealt to the XCDs by whole
+# chunks and, the few FP32 ones of the wide layers, by rows of tiles), batches on
+# both sides of the limit of two products in one launch, and from a few nodes (one
+# row chunk) up; degrees up to 12 (13 buckets)
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("H,graphs,lo,hi,maxd", [
+    (64, 2, 5, 9, 4), (128, 200, 30, 40, 4), (176, 100, 30, 40, 4), (192, 40, 30, 40, 12),
+    (240, 100, 30, 40, 4), (256, 30, 30, 40, 4), (256, 140, 30, 40, 4), (320, 60, 30, 40, 4),
+    (384, 50, 30, 40, 4), (512, 1, 40, 40, 4), (512, 20, 30, 40, 4), (512, 60, 30, 40, 4)])
+def test_routes_agree(prec, H, graphs, lo, hi, maxd):
+    b = synth.make_batch(11, graphs, lo, hi, 1)
+    p = synth.init_params(synth.ModelShape(2, H, 9, 1), 12)
+    one = _grads(b, p, 2, H, prec, maxd=maxd)
+    assert np.isfinite(one).all() and np.abs(one).max() > 0
+    assert np.array_equal(one, _grads(b, p, 2, H, prec, maxd=maxd, fail=1))
+    assert np.array_equal(one, _grads(b, p, 2, H, prec, recompute=1, maxd=maxd))
+
+
+@pytest.mark.parametrize("kind", ["sage", "cgcnn"])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("H,graphs", [(256, 40), (384, 20), (512, 3), (512, 60)])
+def test_other_layer_kinds(kind, prec, H, graphs):
+    b = synth.make_batch(13, graphs, 30, 40, 1)
+    p = synth.init_gc_params(kind, 2, H, 14, edge_feat=1)
+    one = _grads(b, p, 2, H, prec, kind=kind)
+    assert np.isfinite(one).all() and np.abs(one).max() > 0
+    assert np.array_equal(one, _grads(b, p, 2, H, prec, kind=kind, fail=1))
