@@ -76,6 +76,12 @@ constexpr int kColsumChunks = 128;
 // context that has seen 20k: XXX).
 constexpr int kDeferNodes = 16384;
 constexpr size_t kDeferPartBytes = size_t(1) << 30; // and partial sums up to this
+// FP32 PNA products of up to this many node rows a chunk: longer ones hide better
+// beside the adjoint.  H = 512 (two chunks), layer by layer against one launch: one
+// layer at 6.1k nodes 718 and 727 us, at 9.2k 996 and 1018, at 14k 1338 and 1402, two
+// layers 1523 and 1611, 2242 and 2427, 3016 and 3113; H = 384 (three) at 9.2k 1354
+// and 1331, at 14k 1988 and 2028.
+constexpr int kDeferChunkRows = 4096;
 
 // Chunks of a weight-gradient product (product and ordered reduction timed
 // together at 4.5k and 40k nodes): FP32 about 512 workgroups of 64 x 64
@@ -330,8 +336,13 @@ static std::vector<std::pair<WgJob, int>> wg_jobs(const hgnn_ctx *c, int capN) {
 // when layers go one at a time (recomputation, which keeps one layer's
 // aggregates; unbucketed models; large batches, whose products fill the GPU by
 // themselves).
+static int defer_limit(const hgnn_ctx *c) { // nodes, exclusive
+  if (c->kind != HGNN_GC_PNA || c->prec) return kDeferNodes;
+  const int widest = c->ld[c->L - 1].Fp + 4 * c->H + 4;
+  return std::min(kDeferNodes, kDeferChunkRows * tn_splits(c->H, widest, 0));
+}
 static size_t defer_floats(const hgnn_ctx *c, int capN) {
-  if ((c->kind == HGNN_GC_PNA && !c->nb) || c->recompute || capN >= kDeferNodes) return 0;
+  if ((c->kind == HGNN_GC_PNA && !c->nb) || c->recompute || capN >= defer_limit(c)) return 0;
   size_t n = 0;
   for (const auto &j : wg_jobs(c, capN)) n += wg_part_floats(j.first, j.first.nb);
   return n * sizeof(float) <= kDeferPartBytes ? n : 0;
@@ -555,15 +566,16 @@ template <typename T> static bool work_alloc(hgnn_ctx *c, T *&p, size_t n) {
 }
 
 // Whether the backward pass of the prepared batch runs its weight gradients in
-// one launch.  A context whose capacity is past kDeferNodes gets the buffers at
+// one launch.  A context whose capacity is past defer_limit gets the buffers at
 // its first backward pass over a batch below (unless s is being captured: that
 // pass goes layer by layer).  Without the memory for them it does so too, and
 // nothing fails.
 static bool defer_wgrads(hgnn_ctx *c, Exec &ex, hipStream_t s) {
   Work &w = ex.w;
   if (w.wg_n > 0) return ex.N <= w.deferN;
-  if (w.no_defer || ex.N >= kDeferNodes) return false;
-  const int nodes = std::min(w.capN, kDeferNodes - 1);
+  const int limit = defer_limit(c);
+  if (w.no_defer || ex.N >= limit) return false;
+  const int nodes = std::min(w.capN, limit - 1);
   const size_t part = defer_floats(c, nodes);
   if (!part) return !(w.no_defer = true);
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

@@ -58,3 +58,29 @@ def test_other_layer_kinds(kind, prec, H, graphs):
     one = _grads(b, p, 2, H, prec, kind=kind)
     assert np.isfinite(one).all() and np.abs(one).max() > 0
     assert np.array_equal(one, _grads(b, p, 2, H, prec, kind=kind, fail=1))
+
+
+# FP32 products of H = 512 come in two chunks of half the nodes each: above 8192
+# nodes the layers go one at a time
+@pytest.mark.parametrize("graphs,launches", [(225, 1), (245, 2)])
+def test_long_chunks_go_layer_by_layer(graphs, launches):
+    hg = _hg()
+    b = synth.make_batch(15, graphs, 33, 37, 1)
+    assert (b.num_nodes < 8192) == (launches == 1)
+    p = synth.init_params(synth.ModelShape(1, 512, 9, 1), 16)
+    m = hg.Model(1, 512, 9, 1, 4, 0, 0, 1.08)
+    m.set_params(p)
+    db = hg.DeviceBatch.from_host(b)
+    pred, loss = torch.empty(b.num_graphs, device="cuda"), torch.empty(1, device="cuda")
+    n = 0
+    for site in ("update_wgrad", "message_wgrad"):
+        m.timer_start(site, 8)
+        m.forward(db, pred, loss)
+        m.backward()
+        n += m.timer_read()[1]
+    assert n == launches
+    got = m.grads().cpu().numpy()
+    m.close()
+    if launches == 1:  # else a failed allocation of the workspace is an error
+        assert np.array_equal(got, _grads(b, p, 1, 512, 0, fail=1))
+    assert np.array_equal(got, _grads(b, p, 1, 512, 0, recompute=1))
