@@ -64,7 +64,15 @@ template <typename T> static hipError_t dalloc(T *&p, size_t count) {
 // measured: a gain at 40k nodes, a loss at 4.5k, where the launches lie on
 // the critical path of the backward pass).
 constexpr int kSplitDeRows = 16384;
-// node rows x hidden width of a layer whose weight gradients share a launch
+// Node rows x hidden width up to which a layer's two weight gradients share a launch
+// (layer_backward); for FP32 layers wider than 128 times 128 / width.  Single layers,
+// forward and backward, in two launches beside the adjoint and in one after it:
+// BF16 H = 64, 643k 101 and 81 us; H = 128, 622k 99 and 89, 1148k 121 and 114;
+// H = 256, 596k 127 and 119, 881k 137 and 127; H = 512, 596k 184 and 188.
+// FP32 H = 64, 643k 101 and 86; H = 128, 622k 111 and 110, 1148k 155 and 151; H = 192,
+// 313k 106 and 106, 567k 127 and 138; H = 256, 302k 119 and 122, 596k 148 and 163;
+// H = 512, 270k 180 and 207, 596k 240 and 291.  Four recomputed layers, 561k (H = 128)
+// BF16 422 and 417, FP32 495 and 517; 881k (H = 256) 582 and 570, 806 and 868.
 constexpr long long kPairElems = 640 << 10;
 // Row chunks of the De column sums (at 40k rows: about 320 rows per chunk;
 // the sums then cost about as much as reading De once)
@@ -1024,14 +1032,12 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   }
   // Small layers: both weight gradients in one launch after the adjoint, on s.
   // Two launches beside the adjoint on the aux stream, and their events, cost
-  // more than they hide: one layer of H = 128 at 4.5k nodes, forward and
-  // backward, 142 -> 111 us on the device and 215 -> 144 with the host.  Larger
-  // ones fork: four recomputed layers of H = 256 at 3.5k nodes (0.9M) took 820
-  // us with the fork and 899 without.  A whole pass that keeps its activations
-  // forks too: its launches lie on the chain (six layers of H = 128 at 4.5k nodes,
+  // more than they hide (kPairElems).  A whole pass that keeps its activations
+  // forks: its launches lie on the chain (six layers of H = 128 at 4.5k nodes,
   // without the one launch at its end: FP32 588 us with the fork and 687 without, BF16
   // 492 and 547).
-  const bool pair = !defer_wg && c->nb && (long long)ex.N * H <= kPairElems &&
+  const long long elems = (long long)ex.N * H, wide = std::max(H, 128);
+  const bool pair = !defer_wg && c->nb && (c->prec ? elems : elems * wide / 128) <= kPairElems &&
                     (c->recompute || !dh_out_masked);
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
