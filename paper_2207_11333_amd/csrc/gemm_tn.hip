@@ -1,6 +1,7 @@
 // TN-form MFMA GEMMs of the weight gradients that wgrad.hip leaves out: the
 // concatenated update weight gradient with row scales (models without degree
-// buckets), and in BF16 every product launched by itself.  Split-K over node
+// buckets), the FP32 ones of large batches beside register-staged linears, and in
+// BF16 every product launched by itself.  Split-K over node
 // chunks; reduce.hip adds the splits in order and scatters the result into the
 // packed gradient.  Shared tile code: mfma_tile.hpp.
 #include "mfma_tile.hpp"
@@ -12,7 +13,18 @@ namespace {
 // --------------------------------------------------------------------------
 // TN form (split-K weight gradients)
 // --------------------------------------------------------------------------
-template <int BM, int BN>
+// FP32.  PERM: bucketed chunks (g.perm non-null), a template parameter so that the
+// row lookups add no branch to the loop.  SCALE: some segment has row scales
+// (the concatenated update input); without it no scale is loaded at all.
+//
+// Its 17 KB of LDS leave a CU to the register-staged linears of the chain beside it
+// (the aggregate-input and layer-input gradients of layers whose width is no multiple
+// of 32), where wgrad.hip's 48 KB, faster by itself, hold them up: four layers of
+// H = 176 at 24k nodes, a training step 2279 us with wgrad.hip's kernel, 2142 with this
+// one; at 40k 3515 and 3396, H = 240 5379 and 5163.  At 18k H = 144 takes 1630 and 1626,
+// H = 176 1828 and 1842, H = 240 2624 and 2649, at 9k (recomputed) H = 144 1109 and
+// 1122: kStagedRows lies between.
+template <int BM, int BN, bool PERM, bool SCALE>
 __global__ void __launch_bounds__(256)
 k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
   using T = float;
@@ -32,7 +44,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 
   const int rows = dims->N;
   const int mtiles = (g.M + BM - 1) / BM;
-  const int zc = g.splits, gm = tn_group_rows(zc, mtiles);
+  const int zc = g.splits + (PERM ? g.nb : 0), gm = tn_group_rows(zc, mtiles);
   int grp, jt;
   xcd_group(blockIdx.x, zc * (mtiles / gm), gm * ntiles_n, grp, jt);
   if (grp < 0) return;
@@ -40,8 +52,21 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
   const int m0 = ((grp % (mtiles / gm)) * gm + jt / ntiles_n) * BM, n0 = (jt % ntiles_n) * BN;
   int chunk = (rows + g.splits - 1) / g.splits;
   chunk = (chunk + BK - 1) / BK * BK;
-  const int i_lo = z * chunk;
-  const int i_hi = min(rows, i_lo + chunk);
+  int i_lo = z * chunk;
+  int i_hi = min(rows, i_lo + chunk);
+  if constexpr (PERM) {
+    // bucket-pure chunks over the permuted rows: bucket q holds
+    // ceil(n_q / chunk) chunks, in bucket order; the chunks past the last
+    // are empty and write zero partials
+    int bq, r0, r1;
+    BucketWalk(g.brow, g.nb, chunk).find(z, bq, r0, r1);
+    i_lo = bq >= 0 ? r0 : 0;
+    i_hi = bq >= 0 ? min(r1, r0 + chunk) : 0;
+    if (m0 == 0 && n0 == 0 && threadIdx.x == 0) {
+      g.zscale[2 * z] = bq >= 0 ? g.table[2 * bq] : 0.f;
+      g.zscale[2 * z + 1] = bq >= 0 ? g.table[2 * bq + 1] : 0.f;
+    }
+  }
   const int KT = i_hi > i_lo ? (i_hi - i_lo + BK - 1) / BK : 0;
   const int tid = threadIdx.x, wid = tid >> 6;
   const int wm0 = (wid >> 1) * WM, wn0 = (wid & 1) * WN;
@@ -94,7 +119,10 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
     b_sstride[j] = b_has_scale[j] ? 1 : b_ld[j];
   }
   const int i_last = max(i_hi - 1, 0);
-  // Rows (clamped to the chunk) of tile t's vectors into slot Q.
+  // Row ids (nodes, clamped to the chunk) of tile t's vectors into slot Q.  With
+  // bucketed chunks each is a load of the permutation: they are fetched one step
+  // before the data loads that use them and issued ahead of that step's data
+  // loads, so waiting for them never waits for data still in flight.
   int prow[2][NA];
   auto fetch_rows = [&](auto slot, int t) {
     constexpr int Q = decltype(slot)::value;
@@ -102,7 +130,8 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int ic = min(i0 + a_il[j], i_last);
-      prow[Q][j] = ic;
+      if constexpr (PERM) prow[Q][j] = g.perm[ic];
+      else prow[Q][j] = ic;
     }
   };
   // data loads of tile t into stage S, from the row ids in slot S
@@ -116,7 +145,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
     for (int j = 0; j < NB; ++j) {
       const int ic = prow[S][j];
       rb[S][j] = *reinterpret_cast<const f4 *>(b_ptr[j] + (size_t)ic * b_ld[j]);
-      rsc[S][j] = b_sptr[j][(size_t)ic * b_sstride[j]];
+      if constexpr (SCALE) rsc[S][j] = b_sptr[j][(size_t)ic * b_sstride[j]];
     }
   };
   // (a uniform branch: only a chunk's last, partial step pays for masks)
@@ -136,7 +165,7 @@ k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
       const int v = tid + j * 256;
       const int il = v / (BN / 4), nc = (v % (BN / 4)) * 4;
       f4 val = b_ones[j] ? f4{1.f, 0.f, 0.f, 0.f} : rb[S][j];
-      val = val * (b_has_scale[j] ? rsc[S][j] : 1.0f);
+      if constexpr (SCALE) val = val * (b_has_scale[j] ? rsc[S][j] : 1.0f);
       if constexpr (MASK) val = b_il[j] < rlim[S] ? val : zero;
       store4(Bs + il * LDKB + nc, val);
     }
@@ -426,16 +455,16 @@ k_gemm_tn_tr(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {
 
 } // namespace
 
-// FP32: the concatenated update weight gradient of unbucketed models
-// (max_degree above 15; row scales), 64 x 64 tiles (k_gemm_tn).  BF16: that
-// one and every weight gradient launched by itself, 128 x 128 tiles read
-// through the transposing LDS loads (k_gemm_tn_tr).
+// The concatenated update weight gradient of unbucketed models (max_degree above
+// 15; row scales) and products launched by themselves (tag 1 the update's, 2 the
+// message's).  FP32: 64 x 64 tiles (k_gemm_tn); BF16: 128 x 128 tiles read through
+// the transposing LDS loads (k_gemm_tn_tr).
 hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision, hipStream_t s,
                           int tag, hipEvent_t ev0, hipEvent_t ev1) {
   if (g.M <= 0 || g.Ncols <= 0) return hipSuccess;
   bool scaled = false;
   for (int q = 0; q < g.nseg; ++q) scaled = scaled || g.seg[q].scale != nullptr;
-  if ((g.perm && (scaled || tag != 1)) || (precision == 0 && g.perm)) return hipErrorInvalidValue;
+  if (g.perm && (scaled || tag != 1)) return hipErrorInvalidValue;
   const int T = precision ? 128 : 64;
   const int nt = cdiv(g.Ncols, T);
   const int zc = g.splits + (g.perm ? g.nb : 0), mt = cdiv(g.M, T), gm = tn_group_rows(zc, mt);
@@ -444,8 +473,15 @@ hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision, hipS
 #define HGNN_TR(TAG, PERM, SCALE)                                                               \
   hipExtLaunchKernelGGL((k_gemm_tn_tr<TAG, PERM, SCALE>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0, \
                         dims, g, nt)
-  if (!precision)
-    hipExtLaunchKernelGGL((k_gemm_tn<64, 64>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0, dims, g, nt);
+#define HGNN_TN(PERM, SCALE)                                                                    \
+  hipExtLaunchKernelGGL((k_gemm_tn<64, 64, PERM, SCALE>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0, \
+                        dims, g, nt)
+  if (!precision && g.perm)
+    HGNN_TN(true, false);
+  else if (!precision && scaled)
+    HGNN_TN(false, true);
+  else if (!precision)
+    HGNN_TN(false, false);
   else if (tag == 1 && g.perm)
     HGNN_TR(1, true, false);
   else if (tag == 1)
@@ -454,6 +490,7 @@ hipError_t launch_gemm_tn(const Dims *dims, const GemmTN &g, int precision, hipS
     HGNN_TR(2, false, false);
   else
     HGNN_TR(0, false, true);
+#undef HGNN_TN
 #undef HGNN_TR
   return hipGetLastError();
 }

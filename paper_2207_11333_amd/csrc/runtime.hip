@@ -225,14 +225,20 @@ static WgJob cgcnn_job(const hgnn_ctx *c, int capN) {
 static size_t wg_part_floats(const WgJob &j, int nb) {
   return (size_t)(j.splits + nb) * j.M * (j.N + 4);
 }
-// One product by itself: FP32 in wgrad.hip; BF16 in gemm_tn.hip, whose kernel
+// From this many nodes on the FP32 products of PNA layers that are no multiple of 32
+// wide run in gemm_tn.hip's kernel (its comment has both sides).
+constexpr int kStagedRows = 20480;
+
+// One product by itself: FP32 in wgrad.hip, or (staged) in gemm_tn.hip's k_gemm_tn
+// beside register-staged linears; BF16 in gemm_tn.hip, whose kernel
 // keeps two steps of operands in registers and so covers the memory latency of
 // a large batch better (40k nodes, H = 256: update 157 us against 220, message
 // 91 against 100); in one launch over every layer of a small batch wgrad.hip is
 // the faster one (128 molecules, H = 128, six layers: 36 us against 132).
 static hipError_t launch_product(const Dims *dims, const WgJob &j, int prec, hipStream_t s,
-                                 int tag = 0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-  if (prec == 0) return launch_wgrad(dims, j, s, ev0, ev1);
+                                 int tag = 0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                                 bool staged = false) {
+  if (prec == 0 && !staged) return launch_wgrad(dims, j, s, ev0, ev1);
   GemmTN t{};
   t.X = j.X;
   t.ldx = j.ldx;
@@ -1039,6 +1045,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const long long elems = (long long)ex.N * H, wide = std::max(H, 128);
   const bool pair = !defer_wg && c->nb && (c->prec ? elems : elems * wide / 128) <= kPairElems &&
                     (c->recompute || !dh_out_masked);
+  const bool staged = H % 32 != 0 && ex.N >= kStagedRows;
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);
@@ -1064,7 +1071,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
     j.zscale = c->zscale;
     if (!pair) {
       TimedLaunch tl(c, ex, SITE_UPDATE_WGRAD, a, /*manual=*/true);
-      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/1, tl.start(), tl.stop());
+      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/1, tl.start(), tl.stop(), staged);
     }
     if (e != hipSuccess) return hip_fail(c, e, "update weight gradient");
     red.upd[0] = true;
@@ -1203,7 +1210,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
       e = launch_wgrad_pair(ex.dims, j_upd, j, c->prec, a, tl.start(), tl.stop());
     } else {
       TimedLaunch tl(c, ex, SITE_MESSAGE_WGRAD, a, /*manual=*/true);
-      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/2, tl.start(), tl.stop());
+      e = launch_product(ex.dims, j, c->prec, a, /*tag=*/2, tl.start(), tl.stop(), staged);
     }
     red.m[red.njobs++] = msg_reduce(c, l, j, dwl);
     // column sums of De over kColsumChunks row chunks, after the product's

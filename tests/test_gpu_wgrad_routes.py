@@ -84,3 +84,31 @@ def test_long_chunks_go_layer_by_layer(graphs, launches):
     if launches == 1:  # else a failed allocation of the workspace is an error
         assert np.array_equal(got, _grads(b, p, 1, 512, 0, fail=1))
     assert np.array_equal(got, _grads(b, p, 1, 512, 0, recompute=1))
+
+
+# Batches of 20,480 nodes or more: the products by themselves on the second stream,
+# the De rows left to their column sums.  H = 64 runs k_wgrad, widths that are no
+# multiple of 32 k_gemm_tn (bucketed and plain chunks); no other route takes such a
+# batch, so against the FP64 oracle (decision replay, the FP32 path's tolerances).
+@pytest.mark.parametrize("H,Fe,maxd", [(64, 1, 4), (48, 1, 4), (80, 2, 4), (48, 0, 4), (48, 1, 20)])
+def test_large_fp32_against_the_oracle(H, Fe, maxd):
+    import oracle
+    from test_gpu_parity import (ELEM_FP32, TAU_FP32, gpu_decisions, grad_report, make_model, maxrel,
+                                 rel, run_train_step)
+    b = synth.make_batch(17 + Fe, 620, 20, 50, Fe)
+    assert b.num_nodes >= 20480
+    L, delta = 2, 1.3
+    shape = synth.ModelShape(L, H, 9, Fe)
+    params = synth.init_params(shape, 18 + Fe)
+    m = make_model(L, H, Fe, 0, 0, delta, maxd)
+    out = run_train_step(m, b, params)
+    rec = oracle.forward(params, b, L, H, delta)
+    g_ref, _, _ = oracle.backward(rec, hint=gpu_decisions(m, L, H, b.num_nodes, b.num_graphs),
+                                  tau=TAU_FP32)
+    g = out["grads"].cpu().numpy()
+    assert rel(out["pred"].cpu().numpy(), rec.y) <= 1e-5
+    rep, erep = grad_report(m, g, g_ref, shape), grad_report(m, g, g_ref, shape, elementwise=True)
+    print(f"H={H} Fe={Fe}: worst gradient {max(rep.values()):.2e}, element-wise {max(erep.values()):.2e}")
+    assert max(rep.values()) <= 1e-5
+    assert max(erep.values()) <= ELEM_FP32
+    m.close()
