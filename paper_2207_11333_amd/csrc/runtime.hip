@@ -65,15 +65,24 @@ template <typename T> static hipError_t dalloc(T *&p, size_t count) {
 // the critical path of the backward pass).
 constexpr int kSplitDeRows = 16384;
 // Node rows x hidden width up to which a layer's two weight gradients share a launch
-// (layer_backward); for FP32 layers wider than 128 times 128 / width.  Single layers,
+// (layer_backward); in FP32, whose products are the longer, also the rows x width^2
+// of fp32_pair_limit.  Single layers,
 // forward and backward, in two launches beside the adjoint and in one after it:
 // BF16 H = 64, 643k 101 and 81 us; H = 128, 622k 99 and 89, 1148k 121 and 114;
 // H = 256, 596k 127 and 119, 881k 137 and 127; H = 512, 596k 184 and 188.
 // FP32 H = 64, 643k 101 and 86; H = 128, 622k 111 and 110, 1148k 155 and 151; H = 192,
 // 313k 106 and 106, 567k 127 and 138; H = 256, 302k 119 and 122, 596k 148 and 163;
-// H = 512, 270k 180 and 207, 596k 240 and 291.  Four recomputed layers, 561k (H = 128)
-// BF16 422 and 417, FP32 495 and 517; 881k (H = 256) 582 and 570, 806 and 868.
+// H = 512, 270k 180 and 207, 596k 240 and 291.  Four recomputed layers, BF16 H = 128,
+// 568k 422 and 417; H = 256, 881k 582 and 570; FP32 H = 64, 509k (32M) 427 and 402,
+// 772k (48M) 511 and 499; H = 128, 382k (48M) 429 and 432, 568k (71M) 495 and 517.
+// Beside an adjoint that does not form dA itself, single FP32 layers H = 80, 388k (30M)
+// 118 and 118, 520k (41M) 129 and 136; H = 144, 275k (39M) 130 and 133; four recomputed
+// ones H = 48, 430k (20M) 464 and 447; H = 80, 76k (6M) 447 and 458, 520k 573 and 621.
 constexpr long long kPairElems = 640 << 10;
+static long long fp32_pair_limit(int H, bool fused, bool recompute) {
+  if (fused) return recompute ? 48ll << 20 : 80ll << 20;
+  return recompute && H > 64 ? 0 : 32ll << 20;
+}
 // Row chunks of the De column sums (at 40k rows: about 320 rows per chunk;
 // the sums then cost about as much as reading De once)
 constexpr int kColsumChunks = 128;
@@ -1042,8 +1051,10 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // forks: its launches lie on the chain (six layers of H = 128 at 4.5k nodes,
   // without the one launch at its end: FP32 588 us with the fork and 687 without, BF16
   // 492 and 547).
-  const long long elems = (long long)ex.N * H, wide = std::max(H, 128);
-  const bool pair = !defer_wg && c->nb && (c->prec ? elems : elems * wide / 128) <= kPairElems &&
+  const bool fused = c->nb && agg_bwd_fused_ok(H, c->nb);
+  const long long elems = (long long)ex.N * H;
+  const bool pair = !defer_wg && c->nb && elems <= kPairElems &&
+                    (c->prec || elems * H <= fp32_pair_limit(H, fused, c->recompute)) &&
                     (c->recompute || !dh_out_masked);
   const bool staged = H % 32 != 0 && ex.N >= kStagedRows;
   hipStream_t a = pair ? s : c->aux;
@@ -1113,7 +1124,6 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   // feature block inside the aggregation adjoint (one launch, dA not
   // stored).  Otherwise dA = [du || s+ du || s- du] [W0; W+; W-] by the NT
   // GEMM, then the adjoint.
-  const bool fused = c->nb && agg_bwd_fused_ok(H, c->nb);
   if (!fused) {
     GemmNT g{};
     if (c->nb) {
