@@ -32,9 +32,12 @@ k_gemm_nt(const Dims *__restrict__ dims, const GemmNT g, int ntiles_n) {
   using P = Prec<PREC>;
   using T = typename P::T;
   // FP32 backward products are the chain that a weight gradient on the other
-  // stream runs beside: their waves go first (24k nodes, H = 208: a training step
-  // 2683 -> 2557 us; BF16, not bound by the matrix cores, gains nothing)
-  if (PREC == 0 && (TAG == 3 || TAG == 4)) __builtin_amdgcn_s_setprio(2);
+  // stream runs beside: their waves go first (24k nodes, four layers of H = 176, a
+  // training step 2227 -> 2136 us, H = 208 2976 -> 2917; BF16, not bound by the matrix
+  // cores, gains nothing).  Narrower than 48 the weight gradients are the longer side: six
+  // layers of H = 16 at 96k nodes 1702 us so, 1588 without; H = 48 at 18k, recomputed, 998
+  // and 1033, at 31k 1048 and 1064, at 96k 2349 and 2307.
+  if (PREC == 0 && (TAG == 3 || TAG == 4) && g.seg[0].k >= 48) __builtin_amdgcn_s_setprio(2);
   constexpr int NTH = 128 * WGN;
   constexpr int BK = P::BK, LDA = BK + P::PAD;
   constexpr int WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
