@@ -23,7 +23,8 @@ namespace {
 // H = 176 at 24k nodes, a training step 2279 us with wgrad.hip's kernel, 2142 with this
 // one; at 40k 3515 and 3396, H = 240 5379 and 5163.  At 18k H = 144 takes 1630 and 1626,
 // H = 176 1828 and 1842, H = 240 2624 and 2649, at 9k (recomputed) H = 144 1109 and
-// 1122: kStagedRows lies between.
+// 1122: kStagedRows lies between.  Narrow layers, whose product is one row of tiles
+// and waits for memory: six of H = 32 at 31k nodes 738 and 699, at 96k 1739 and 1559.
 template <int BM, int BN, bool PERM, bool SCALE>
 __global__ void __launch_bounds__(256)
 k_gemm_tn(const Dims *__restrict__ dims, const GemmTN g, int ntiles_n) {

@@ -235,7 +235,8 @@ static size_t wg_part_floats(const WgJob &j, int nb) {
   return (size_t)(j.splits + nb) * j.M * (j.N + 4);
 }
 // From this many nodes on the FP32 products of PNA layers that are no multiple of 32
-// wide run in gemm_tn.hip's kernel (its comment has both sides).
+// wide, or bucketed and narrower than 64, run in gemm_tn.hip's kernel (its comment has
+// both sides).
 constexpr int kStagedRows = 20480;
 
 // One product by itself: FP32 in wgrad.hip, or (staged) in gemm_tn.hip's k_gemm_tn
@@ -1056,7 +1057,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const bool pair = !defer_wg && c->nb && elems <= kPairElems &&
                     (c->prec || elems * H <= fp32_pair_limit(H, fused, c->recompute)) &&
                     (c->recompute || !dh_out_masked);
-  const bool staged = H % 32 != 0 && ex.N >= kStagedRows;
+  const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows;
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);
