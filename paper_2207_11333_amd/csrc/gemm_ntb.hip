@@ -409,13 +409,18 @@ inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 // are a quarter of the work (and more of them share a CU), at twice the operand
 // traffic.  Update linear of H = 128, FP32, 64 against 32: 1.1k nodes (23 of 256
 // CUs busy) 11.3 -> 6.8 us, 4.5k (150) 17.9 -> 15.1, 8.9k (290: a second round
-// for 34) 28.9 -> 23.3, but 15.7k (502) 31.5 -> 35.1.
-int tile_side(int capM, const GemmNTB &g) {
+// for 34) 28.9 -> 23.3, but 15.7k (502) 31.5 -> 35.1.  BF16's products are a quarter
+// as long or less, so that a second round costs less than that traffic: inference of
+// four layers, 64 against 32, H = 384 at 2.5k nodes (264) 169 and 190 us, H = 448 at
+// 4.5k (525) 331 and 369, H = 256 at 6.3k (416) 200 and 209.  Not where the operands
+// are FP32, twice the traffic again (training of H = 256 at 4.5k, whose layer-input
+// gradient has 304 tiles, 583 and 575).
+int tile_side(int capM, const GemmNTB &g, int precision) {
   auto grid = [&](int B) {
     return (long long)(cdiv(capM, B) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, B);
   };
   if (grid(128) >= 256 && g.chunks <= 1 && !g.short0) return 128;
-  const long long n = grid(64), rounds = (n + 255) / 256;
+  const long long n = grid(64), rounds = precision == 1 ? 1 : (n + 255) / 256;
   return 10 * n >= 8 * 256 * rounds ? 64 : 32;
 }
 
@@ -449,7 +454,7 @@ hipError_t launch_gemm_ntb(const Dims *dims, int capM, const GemmNTB &g, int pre
                            hipStream_t s, int tag, hipEvent_t ev0, hipEvent_t ev1) {
   if (capM <= 0) return hipSuccess;
   if (!gemm_ntb_ok(g, precision)) return hipErrorInvalidValue;
-  const int B = tile_side(capM, g);
+  const int B = tile_side(capM, g, precision);
   const int nt = cdiv(g.Ncols, B);
   // bucketed rows: each bucket's last tile may be partial
   const dim3 grid((cdiv(capM, B) + (g.perm ? g.nb : 0)) * nt), block(64 * kQWGM * waves_n(B));
