@@ -236,7 +236,9 @@ static size_t wg_part_floats(const WgJob &j, int nb) {
 }
 // From this many nodes on the FP32 products of PNA layers that are no multiple of 32
 // wide, or bucketed and narrower than 64, run in gemm_tn.hip's kernel (its comment has
-// both sides).
+// both sides).  Not those of a multiple of eight chunks, which that kernel deals whole
+// to the XCDs however unequal they are: three layers of H = 400 (3 + 5 chunks) at 19k
+// nodes 6150 us in it, 5088 in wgrad.hip's.
 constexpr int kStagedRows = 20480;
 
 // One product by itself: FP32 in wgrad.hip, or (staged) in gemm_tn.hip's k_gemm_tn
@@ -1057,7 +1059,8 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const bool pair = !defer_wg && c->nb && elems <= kPairElems &&
                     (c->prec || elems * H <= fp32_pair_limit(H, fused, c->recompute)) &&
                     (c->recompute || !dh_out_masked);
-  const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows;
+  const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows &&
+                      (tn_splits(H, d.Fp + 4 * H + 4, 0) + c->nb) % 8 != 0;
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);
