@@ -65,8 +65,8 @@ template <typename T> static hipError_t dalloc(T *&p, size_t count) {
 // the critical path of the backward pass).
 constexpr int kSplitDeRows = 16384;
 // Node rows x hidden width up to which a layer's two weight gradients share a launch
-// (layer_backward); in FP32, whose products are the longer, also the rows x width^2
-// of fp32_pair_limit.  Single layers,
+// (layer_backward), and the rows x width^2: in FP32, whose products are the longer, and
+// in BF16 layers of 448 and more, whose partial sums are.  Single layers,
 // forward and backward, in two launches beside the adjoint and in one after it:
 // BF16 H = 64, 643k 101 and 81 us; H = 128, 622k 99 and 89, 1148k 121 and 114;
 // H = 256, 596k 127 and 119, 881k 137 and 127; H = 512, 596k 184 and 188.
@@ -78,8 +78,11 @@ constexpr int kSplitDeRows = 16384;
 // Beside an adjoint that does not form dA itself, single FP32 layers H = 80, 388k (30M)
 // 118 and 118, 520k (41M) 129 and 136; H = 144, 275k (39M) 130 and 133; four recomputed
 // ones H = 48, 430k (20M) 464 and 447; H = 80, 76k (6M) 447 and 458, 520k 573 and 621.
+// Four recomputed BF16 ones of 245 nodes, 5 and 16 buckets: H = 384 560 and 546, 715 and
+// 708; H = 448 651 and 658, 846 and 871; H = 480 830 and 900, 1107 and 1191.
 constexpr long long kPairElems = 640 << 10;
-static long long fp32_pair_limit(int H, bool fused, bool recompute) {
+static long long pair_limit(int H, int prec, bool fused, bool recompute) {
+  if (prec) return H < 448 ? kPairElems * H : 0;
   if (fused) return recompute ? 48ll << 20 : 80ll << 20;
   return recompute && H > 64 ? 0 : 32ll << 20;
 }
@@ -1057,7 +1060,7 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const bool fused = c->nb && agg_bwd_fused_ok(H, c->nb);
   const long long elems = (long long)ex.N * H;
   const bool pair = !defer_wg && c->nb && elems <= kPairElems &&
-                    (c->prec || elems * H <= fp32_pair_limit(H, fused, c->recompute)) &&
+                    elems * H <= pair_limit(H, c->prec, fused, c->recompute) &&
                     (c->recompute || !dh_out_masked);
   const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows &&
                       (tn_splits(H, d.Fp + 4 * H + 4, 0) + c->nb) % 8 != 0;
