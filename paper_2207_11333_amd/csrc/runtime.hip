@@ -66,7 +66,7 @@ template <typename T> static hipError_t dalloc(T *&p, size_t count) {
 constexpr int kSplitDeRows = 16384;
 // Node rows x hidden width up to which a layer's two weight gradients share a launch
 // (layer_backward), and the rows x width^2: in FP32, whose products are the longer, and
-// in BF16 layers of 448 and more, whose partial sums are.  Single layers,
+// in wide BF16 layers, whose partial sums are.  Single layers,
 // forward and backward, in two launches beside the adjoint and in one after it:
 // BF16 H = 64, 643k 101 and 81 us; H = 128, 622k 99 and 89, 1148k 121 and 114;
 // H = 256, 596k 127 and 119, 881k 137 and 127; H = 512, 596k 184 and 188.
@@ -79,10 +79,12 @@ constexpr int kSplitDeRows = 16384;
 // 118 and 118, 520k (41M) 129 and 136; H = 144, 275k (39M) 130 and 133; four recomputed
 // ones H = 48, 430k (20M) 464 and 447; H = 80, 76k (6M) 447 and 458, 520k 573 and 621.
 // Four recomputed BF16 ones of 245 nodes, 5 and 16 buckets: H = 384 560 and 546, 715 and
-// 708; H = 448 651 and 658, 846 and 871; H = 480 830 and 900, 1107 and 1191.
+// 708; H = 448 651 and 658, 846 and 871; H = 480 830 and 900, 1107 and 1191; and where
+// the adjoint does not form dA H = 176 464 and 466, 498 and 513; H = 208 498 and 529, 547
+// and 590; H = 336 640 and 673, 787 and 836 (single ones H = 240, 541 nodes 125 and 121).
 constexpr long long kPairElems = 640 << 10;
 static long long pair_limit(int H, int prec, bool fused, bool recompute) {
-  if (prec) return H < 448 ? kPairElems * H : 0;
+  if (prec) return H < (fused ? 448 : recompute ? 192 : 256) ? kPairElems * H : 0;
   if (fused) return recompute ? 48ll << 20 : 80ll << 20;
   return recompute && H > 64 ? 0 : 32ll << 20;
 }
