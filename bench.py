@@ -75,24 +75,25 @@ def measured_traffic(name, sources):
 # Layers after the first run the message and update linears in the LDS-DMA
 # form (k_gemm_ntb: FP32 on the inputs, BF16 on operand copies), FP32 also the
 # layer-input gradient; the first layer and the other BF16 sites the
-# register-staged kernel.  Weight gradients launched layer by layer (recomputation,
-# large batches) run k_wgrad in FP32 and k_gemm_tn_tr in BF16.
+# register-staged kernel.  Weight gradients launched by themselves (recomputation,
+# large batches) run k_wgrad or, beside register-staged linears, k_gemm_tn in FP32 and
+# k_gemm_tn_tr in BF16; time_sites names the launches that hold several.
 SITES = {
     "message_gemm": ("S1 message linear",
                      "k_gemm_ntb<P, *, *, 2, *, 3, 2, *> | k_gemm_nt<P, 64, 128, *, 2, 4, *>", "mfma"),
     "aggregate": ("S2 aggregation", "k_aggregate<1>", "hbm"),
     "update_gemm": ("S3 update linear",
                     "k_gemm_ntb<P, *, *, 2, *, 3, 1, *> | k_gemm_nt<P, 64, 128, *, 1, 4, *>", "mfma"),
-    "update_wgrad": ("S6 update weight gradient", "k_wgrad | k_gemm_tn_tr<1, *>",
-                     "mfma"),
+    "update_wgrad": ("S6 update weight gradient",
+                     "k_wgrad | k_gemm_tn<64, 64, *, *> | k_gemm_tn_tr<1, *>", "mfma"),
     "agg_input_gemm": ("S6 aggregate-input gradient", "k_gemm_nt<P, 64, 128, *, 3, 4, *>", "mfma"),
     # by degree bucket dA is formed inside the adjoint (one fused kernel, dA
     # not stored) and the S6 aggregate-input GEMM site has no launches
     "aggregate_bwd": ("S6 dA + S7 aggregation adjoint, fused", "k_agg_bwd_fused<P, 1, *>", "hbm"),
     "input_gemm": ("S6+S8 layer-input gradient",
                    "k_gemm_ntb<P, *, *, 2, *, 3, 4, *> | k_gemm_nt<P, 64, 128, *, 4, 4, *>", "mfma"),
-    "message_wgrad": ("S8 message weight gradient", "k_wgrad | k_gemm_tn_tr<2, *>",
-                      "mfma"),
+    "message_wgrad": ("S8 message weight gradient",
+                      "k_wgrad | k_gemm_tn<64, 64, *, *> | k_gemm_tn_tr<2, *>", "mfma"),
 }
 
 
@@ -139,24 +140,27 @@ def time_sites(m, step, steps, w, N, E, sites=tuple(SITES)):
     the roofline figures."""
     import torch
     bf16 = w.precision == 1
-    out = {}
+    out, times = {}, {}
     for site in sites:
         m.timer_start(site, steps * 2 * w.num_layers + 16)
         torch.cuda.synchronize()
         for _ in range(steps):
             step()
         torch.cuda.synchronize()
-        ms, n = m.timer_read()
+        times[site] = m.timer_read()
+    for site, (ms, n) in times.items():
         if n == 0:
             continue
         work, per_step = site_work(site, w, N, E)
         avg = ms / 1e3 / n
         what, kern, bound = SITES[site]
-        if site == "update_wgrad" and n == steps and w.num_layers > 1:
-            # small batches: every layer's weight gradients in one launch
-            work = w.num_layers * (work + site_work("message_wgrad", w, N, E)[0])
-            per_step = 1
-            what, kern = "S6 + S8 weight gradients, all layers", "k_wgrad_all<P, *>"
+        if site == "update_wgrad" and "message_wgrad" in times and not times["message_wgrad"][1]:
+            # small batches: these launches hold the message products too, a layer's
+            # (recomputation) or every layer's
+            per_step = n // steps
+            work = w.num_layers * (work + site_work("message_wgrad", w, N, E)[0]) / per_step
+            what, kern = (("S6 + S8 weight gradients, a layer", "k_wgrad_pair<P, *>") if w.recompute
+                          else ("S6 + S8 weight gradients, all layers", "k_wgrad_all<P, *>"))
         if bound == "hbm":
             ach, peak, unit = work / avg / 1e9, HBM_PEAK_GBS, "GB/s"
         else:

@@ -318,10 +318,13 @@ int hgnn_op_fetch(hgnn_ctx *ctx, int32_t which, int32_t layer, void *dst_dev,
  * weight-gradient GEMM, 5 aggregate-gradient GEMM, 6 aggregation adjoint,
  * 7 input-gradient GEMM, 8 message weight-gradient GEMM (these time the
  * kernel alone, not a split-K reduction after it), 9 the CSR build of a
- * training-path forward (all of its launches).  Where a backward pass forms
- * the weight gradients of all layers in one launch (contexts of fewer than
- * 16384 nodes that keep their activations), that launch is site 4 and site 8
- * has none.  For GraphSAGE models site 3 is the layer GEMM and 4 its weight
+ * training-path forward (all of its launches).  Where one launch holds both
+ * weight gradients of a layer (small layers of recomputing contexts and of the
+ * per-operation entries) or those of all layers (batches of fewer than 16384
+ * nodes in contexts that keep their activations, PNA ones with max_degree up to
+ * 15; 4096 nodes times the chunks of the update product in FP32; up to 1 GiB of
+ * partial sums, and where the memory for them is there), that launch is site 4
+ * and site 8 has none.  For GraphSAGE models site 3 is the layer GEMM and 4 its weight
  * gradient; for CGCNN models 2 is the gated aggregation, 4 the layer weight
  * gradient, 6 the aggregation adjoint and 7 the input-gradient GEMM.
  * Synchronises the device. */
