@@ -112,3 +112,39 @@ def test_large_fp32_against_the_oracle(H, Fe, maxd):
     assert max(rep.values()) <= 1e-5
     assert max(erep.values()) <= ELEM_FP32
     m.close()
+
+
+# A batch too large for the one launch: the fused backward leaves each layer's
+# second-stream products to be joined two layers on, the per-operation entries join
+# every layer at once.  Several steps back to back, so that a step's products still run
+# while the next one's chain begins.  (The loss gradient is formed by torch on one side
+# and by the head kernel on the other, as in test_deferred_joins_match_per_layer_joins,
+# whose batch is below the limit, and with that test's tolerances.)
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("H", [64, 80])
+def test_deferred_joins_of_a_large_batch(prec, H):
+    hg = _hg()
+    from test_gpu_parity import rel
+    b = synth.make_batch(19, 500, 30, 50, 1)
+    assert b.num_nodes >= 16384 and b.num_nodes * H > 640 * 1024
+    L = 5
+    p = synth.init_params(synth.ModelShape(L, H, 9, 1), 20)
+    m = hg.Model(L, H, 9, 1, 4, prec, 0, 1.08)
+    m.set_params(p)
+    db = hg.DeviceBatch.from_host(b)
+    pred, loss = torch.empty(b.num_graphs, device="cuda"), torch.empty(1, device="cuda")
+    for _ in range(3):
+        m.forward(db, pred, loss)
+        m.backward()
+    fused = m.grads()
+    net = hg.PNANet(m, p)
+    for _ in range(3):
+        net.zero_grad()
+        out = net(db)
+        ((out - db.y) ** 2).mean().backward()
+    torch.cuda.synchronize()
+    assert torch.equal(out.detach(), pred)
+    r = rel(net.packed_grad().cpu().numpy(), fused.cpu().numpy())
+    print(f"H={H} prec={prec}: gradient rel {r:.2e}")
+    assert r <= (1e-5 if prec else 1e-6)
+    m.close()
