@@ -106,17 +106,18 @@ struct GemmNT {
   int ldcb;
 };
 
-// LDS-DMA NT form (gemm_ntb.hip): C = act(sum_seg A_seg B_seg^T + bias) with
-// every A segment in the product's precision in HBM (FP32 as it lies, BF16 as
-// a copy written by its producer) and every segment length a multiple of the
-// K tile (32 FP32 or 64 BF16), so that whole K tiles are copied from HBM to
-// LDS without passing through registers.  Same products, in the same order,
-// as GemmNT's unsplit form on the same values: the outputs are bitwise equal.
-// No split-K, row scales, interleave or addend.
+// LDS-DMA NT form (gemm_ntb.hip): C = act(sum_seg A_seg B_seg^T + bias + addend)
+// with every A segment as it lies in HBM: FP32, or BF16 copies written by their
+// producers (precision 1), or FP32 rounded to BF16 when used (precision 2).  Every
+// segment length is a multiple of the K tile (32 FP32 or 64 BF16), but for a short
+// first one (short0), so that whole K tiles are copied from HBM to LDS without
+// passing through registers.  Same products, in the same order, as GemmNT's on the
+// same values, unsplit or (chunks) with that many K splits: the outputs are bitwise
+// equal.  No row scales or interleave.
 struct SegB {
   const void *ptr; // [rows, ld] row-major, k-contiguous, 16-byte aligned rows
   int ld;          // leading dimension (elements; rows 16-byte multiples)
-  int k;           // segment length (multiple of the K tile)
+  int k;           // segment length (multiple of the K tile; see short0)
   int boff;        // column of this segment in the B rows: the sum of the k before it
 };
 struct GemmNTB {
@@ -210,11 +211,11 @@ int wg_blocks(const WgJob &j, int tile);
 // One FP32 product by itself.
 hipError_t launch_wgrad(const Dims *dims, const WgJob &j, hipStream_t s, hipEvent_t ev0 = nullptr,
                         hipEvent_t ev1 = nullptr);
-// n products in device memory in one launch (a whole backward pass's): tile is
-// the output tile side, 128 or 64, most the largest wg_blocks(job, tile).
 // Two products in one launch (a layer's).
 hipError_t launch_wgrad_pair(const Dims *dims, const WgJob &j0, const WgJob &j1, int precision,
                              hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// n products in device memory in one launch (a whole backward pass's): tile is
+// the output tile side, 128 or 64, most the largest wg_blocks(job, tile).
 hipError_t launch_wgrad_all(const Dims *dims, const WgJob *tab, int n, int most, int precision,
                             int tile, hipStream_t s, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);

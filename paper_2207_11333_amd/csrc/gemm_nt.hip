@@ -498,9 +498,10 @@ hipError_t launch_gemm_nt(const Dims *dims, int capM, GemmNT g, int precision,
     --g.splits;
   const long long tiles = (long long)cdiv(capM, kNtBM) * cdiv(g.Ncols, kNtBN);
   if (tag != 3 && (precision == 0 || tiles <= kNtSmallBf16)) {
-    // FP32 operands that whole 32-deep K tiles cover: the LDS-DMA form, with the
-    // same chunks of K (one launch, no partial sums in memory).  GraphSAGE of
-    // H = 128 at 4.5k nodes: layer 12.5 us and its reduction 4.1 -> 8.4,
+    // Operands that whole K tiles cover: the LDS-DMA form, in FP32 with the same
+    // chunks of K (one launch, no partial sums in memory), in BF16 on small grids with
+    // FP32 operands rounded when used (kNtSmallBf16).  GraphSAGE of
+    // H = 128 at 4.5k nodes, FP32: layer 12.5 us and its reduction 4.1 -> 8.4,
     // input gradient 11.8 -> 8.9
     GemmNTB q{};
     bool plain = g.ileave_n == 0 && (precision || !g.Cb);

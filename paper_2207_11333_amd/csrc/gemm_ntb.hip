@@ -50,7 +50,8 @@
 // Products and their order per output are those of the register-staged
 // kernel when it runs unsplit (FP32: per 16 k, four k-slots of
 // v_mfma_f32_16x16x4_f32; BF16: per 64 k, weight hi over k 0-31 and 32-63,
-// then lo over the same), so outputs are bitwise equal to its unsplit form.
+// then lo over the same), so outputs are bitwise equal to its unsplit form; with
+// chunks above one (FP32) the sums are those of its split-K form and its reduction.
 #include "mfma_tile.hpp"
 
 namespace hgnn {

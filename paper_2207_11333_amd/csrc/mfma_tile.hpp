@@ -1,12 +1,12 @@
-// Shared pieces of the MFMA GEMMs (gemm_nt.hip, gemm_tn.hip): operand types
-// per precision, the XCD-aware tile order and the LDS tile multiply-accumulate
-// (whole, or as per-chunk fragment reads and products for loops pipelined
-// by hand).
+// Shared pieces of the MFMA GEMMs (gemm_nt.hip, gemm_ntb.hip, gemm_tn.hip, wgrad.hip)
+// and of the fused adjoint: operand types per precision, the XCD-aware tile order
+// and the LDS tile multiply-accumulate (whole, or as per-chunk fragment reads and
+// products for loops pipelined by hand).
 //
 // MFMA GEMMs of the message, update and head-free linears (steps S1, S3 and
 // their adjoints S6, S8).
 //
-// Two forms:
+// Three forms:
 //  * gemm_nt:  C = act(sum_seg diag(scale_seg) A_seg B_seg^T + bias).  The
 //    K dimension is a list of segments so that the update input
 //    [h || A || s+ A || s- A] and the adjoint input [du || s+ du || s- du]
@@ -14,11 +14,14 @@
 //    512-thread workgroups (8 wave64s in a 2x4 grid) on 64 x 128 tiles,
 //    operands staged through LDS in [row][k] order (k contiguous); small
 //    grids with long K ranges double-buffer the LDS tiles.
-//  * gemm_tn:  P[z] = X^T Yv over a fixed chunk z of the node rows (split-K),
+//  * gemm_ntb: the same without row scales, whole K tiles copied from HBM to LDS
+//    by LDS-DMA loads.
+//  * wgrad, gemm_tn:  P[z] = X^T Yv over a fixed chunk z of the node rows,
 //    reduced afterwards in the fixed order z = 0, 1, ...: weight gradients
 //    are deterministic and need no atomics.  256-thread workgroups (4
-//    wave64s in a 2x2 grid) on 64 x 64 tiles; FP32 keeps the node-row tiles
-//    k-major in LDS, BF16 transposes them to [row][k] while staging.
+//    wave64s in a 2x2 grid) on 64 x 64 or 128 x 128 tiles, the node-row tiles
+//    k-major in LDS: by LDS-DMA loads (wgrad) or through registers (gemm_tn, whose
+//    BF16 kernel rounds there and reads LDS transposing).
 // Precision 0 runs v_mfma_f32_16x16x4_f32 on FP32 operands; precision 1
 // rounds operands to BF16 (RNE, v_cvt_pk_bf16_f32) while staging and runs
 // v_mfma_f32_16x16x32_bf16 with FP32 accumulation.  Weights in BF16 mode come

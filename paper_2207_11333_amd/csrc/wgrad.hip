@@ -5,10 +5,10 @@
 //
 // A workgroup (4 wave64 in a 2 x 2 grid) owns one output tile of one chunk.
 // Both operand tiles go from HBM to LDS by LDS-DMA loads as they lie in
-// memory, node row after node row ([k][columns], FP32), 16 (FP32) or 32 (BF16)
-// rows a step.  Rows
-// past the chunk repeat its last one; the last step zeroes them in LDS, so no
-// product is masked.
+// memory, node row after node row ([k][columns], FP32), 16 rows a step in FP32
+// lists and pairs, 32 in FP32 products by themselves and in BF16.  Rows past the
+// chunk repeat its last one; the last step zeroes them in LDS, so no product is
+// masked.
 //
 // MFMA operands: a wave's tile is 16 TW x 16 TW (TW = 4 or 2 blocks a side).
 // The 16 rows of block i are the tile's columns TW r + i, r = 0..15, so one
