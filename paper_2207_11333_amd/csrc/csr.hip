@@ -530,7 +530,6 @@ __device__ __forceinline__ unsigned wave_add_scan(unsigned v) {
   v += dpp0<0x143, 0xc>(v); // lane 31 into rows 2 and 3
   return v;
 }
-typedef int i4 __attribute__((ext_vector_type(4)));
 
 template <int T, int CAPN, int CAPE>
 __global__ void __launch_bounds__(T) k_csr_small(const CsrSmall a) {

@@ -1,6 +1,7 @@
-"""The CSR build at the edges of its size classes (one workgroup up to 6144
-nodes and 12288 edges, a chain of kernels above) against the host build, and
-the errors each class reports."""
+"""The CSR build at the edges of its size classes (one launch up to 6144 nodes and
+12288 edges, of one workgroup up to 1024 edges and of one per 512 above; a chain of
+kernels for larger batches) against the host build, and the errors each class
+reports."""
 import numpy as np
 import pytest
 
