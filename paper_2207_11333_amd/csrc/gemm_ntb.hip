@@ -405,10 +405,13 @@ k_gemm_ntb(const Dims *__restrict__ dims, const GemmNTB g, int ntiles_n) {
 
 inline bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
-// Tile side by the grid it gives: 128 when that fills every CU at least once; 64
-// when its rounds over the 256 CUs are at least 0.8 full; else 32, whose tiles
-// are a quarter of the work (and more of them share a CU), at twice the operand
-// traffic.  Update linear of H = 128, FP32, 64 against 32: 1.1k nodes (23 of 256
+// Tile side by the grid it gives: 128 when that fills every CU at least once and its
+// rounds over the 256 CUs are at least 0.8 full; 64 when its own rounds are; else 32.
+// Each is a quarter of the work of the one before (and more of them share a CU), at
+// twice the operand traffic.  128 against 64, four layers, FP32 inference of SAGE
+// H = 256: 17.9k nodes (280: a second round for 24) 323 and 259 us, 23.9k (374) 341
+// and 298, 40.4k (632: three rounds, 0.82 full) 488 and 488; H = 128 at 50.3k (393,
+// 0.77 full) 252 and 242.  Update linear of H = 128, FP32, 64 against 32: 1.1k nodes (23 of 256
 // CUs busy) 11.3 -> 6.8 us, 4.5k (150) 17.9 -> 15.1, 8.9k (290: a second round
 // for 34) 28.9 -> 23.3, but 15.7k (502) 31.5 -> 35.1.  BF16's products are a quarter
 // as long or less, so that a second round costs less than that traffic: inference of
@@ -420,9 +423,10 @@ int tile_side(int capM, const GemmNTB &g, int precision) {
   auto grid = [&](int B) {
     return (long long)(cdiv(capM, B) + (g.perm ? g.nb : 0)) * cdiv(g.Ncols, B);
   };
-  if (grid(128) >= 256 && g.chunks <= 1 && !g.short0) return 128;
-  const long long n = grid(64), rounds = precision == 1 ? 1 : (n + 255) / 256;
-  return 10 * n >= 8 * 256 * rounds ? 64 : 32;
+  auto full = [](long long n, long long rounds) { return 10 * n >= 8 * 256 * rounds; };
+  const long long l = grid(128), n = grid(64);
+  if (l >= 256 && full(l, (l + 255) / 256) && g.chunks <= 1 && !g.short0) return 128;
+  return full(n, precision == 1 ? 1 : (n + 255) / 256) ? 64 : 32;
 }
 
 } // namespace
