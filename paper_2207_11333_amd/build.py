@@ -15,7 +15,7 @@ OUT = os.path.join(HERE, "libhgnn.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["csr.hip", "gemm_nt.hip", "gemm_ntb.hip", "gemm_tn.hip", "wgrad.hip", "reduce.hip", "aggregate.hip",
            "agg_fused.hip", "head.hip", "adam.hip", "gc.hip", "runtime.hip", "serve.hip",
-           "store.hip", "noalloc.hip"]
+           "store.hip", "noalloc.hip", "streams.hip"]
 ARCH = os.environ.get("HGNN_OFFLOAD_ARCH", "gfx950")
 
 

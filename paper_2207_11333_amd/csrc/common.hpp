@@ -485,4 +485,9 @@ struct GcStageJob {
 hipError_t launch_gc_stage(const GcStageJob *jobs, int njobs, long long max_elems,
                            long long *bump, hipStream_t s);
 
+// ---- streams.hip ----
+// A non-blocking stream of the current device, to be given back when it is idle
+hipError_t stream_acquire(hipStream_t *out);
+void stream_release(hipStream_t s);
+
 } // namespace hgnn

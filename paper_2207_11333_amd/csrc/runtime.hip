@@ -2048,7 +2048,7 @@ static int create_ctx(const hgnn_config *cfg, int kind, const hgnn_heads *heads,
     hgnn_destroy(c);
     return fail(HGNN_EDEVICE, std::string("context init: ") + hipGetErrorString(e));
   }
-  if (hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) != hipSuccess ||
+  if (stream_acquire(&c->aux) != hipSuccess ||
       hipEventCreateWithFlags(&c->fork_ev[0], hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->fork_ev[1], hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming) != hipSuccess ||
@@ -2081,7 +2081,7 @@ void hgnn_destroy(hgnn_ctx *c) {
   for (hipEvent_t ev : {c->fork_ev[0], c->fork_ev[1], c->join_ev, c->stage_ev, c->pjoin_ev[0],
                         c->pjoin_ev[1]})
     if (ev) (void)hipEventDestroy(ev);
-  if (c->aux) (void)hipStreamDestroy(c->aux);
+  stream_release(c->aux);
   void **ptrs[] = {(void **)&c->params, (void **)&c->grads, (void **)&c->adam_m,
                    (void **)&c->adam_v, (void **)&c->step_dev, (void **)&c->stage_tab,
                    (void **)&c->gw_dev, (void **)&c->nw_dev, (void **)&c->W1n,

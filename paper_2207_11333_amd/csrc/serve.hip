@@ -375,7 +375,7 @@ void destroy_lane(Lane &ln) {
   if (ln.h_stage) (void)hipHostFree(ln.h_stage);
   if (ln.h_out) (void)hipHostFree(ln.h_out);
   if (ln.done) (void)hipEventDestroy(ln.done);
-  if (ln.stream) (void)hipStreamDestroy(ln.stream);
+  stream_release(ln.stream);
 }
 
 // Host-side validation of one request (Table 1 layout, request-local ids).
@@ -472,7 +472,7 @@ int hgnn_serve_start(hgnn_ctx *c, const hgnn_serve_config *cfg) {
   for (int i = 0; i < fit; ++i) {
     std::unique_ptr<Lane> ln(new Lane());
     ln->ex.inference_only = true;
-    bool ok = hipStreamCreateWithFlags(&ln->stream, hipStreamNonBlocking) == hipSuccess &&
+    bool ok = stream_acquire(&ln->stream) == hipSuccess &&
               hipEventCreateWithFlags(&ln->done, hipEventDisableTiming) == hipSuccess &&
               hipMalloc((void **)&ln->ex.dims, sizeof(Dims)) == hipSuccess &&
               hipMalloc((void **)&ln->ex.w.csr.err, kErrWords * sizeof(int)) == hipSuccess &&

@@ -196,7 +196,7 @@ void shutdown(hgnn_store *s) {
     if (d.copied) (void)hipEventDestroy(d.copied);
     if (d.released) (void)hipEventDestroy(d.released);
   }
-  if (s->copy) (void)hipStreamDestroy(s->copy);
+  hgnn::stream_release(s->copy);
   if (s->fd >= 0) close(s->fd);
 }
 
@@ -242,7 +242,7 @@ int hgnn_store_open(const char *path, int32_t io_threads, int32_t host_slots,
     s->max_E = std::max(s->max_E, en.E);
   }
   hipError_t e = hipGetDevice(&s->dev);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hgnn::stream_acquire(&s->copy);
   s->host.resize(host_slots);
   for (int i = 0; i < host_slots && e == hipSuccess; ++i) {
     s->host[i].expect = i;
