@@ -241,9 +241,10 @@ static size_t wg_part_floats(const WgJob &j, int nb) {
 }
 // From this many nodes on the FP32 products of PNA layers that are no multiple of 32
 // wide, or bucketed and narrower than 64, run in gemm_tn.hip's kernel (its comment has
-// both sides).  Not those of a multiple of eight chunks, which that kernel deals whole
-// to the XCDs however unequal they are: three layers of H = 400 (3 + 5 chunks) at 19k
-// nodes 6150 us in it, 5088 in wgrad.hip's.
+// both sides).  Not those of 8 or 16 chunks, which that kernel deals whole to the XCDs
+// however unequal they are and wgrad.hip's by rows: three layers of H = 400 (3 + 5
+// chunks) at 19k nodes 6150 us in it, 5088 in wgrad.hip's; two of H = 208 at 45k with
+// 8 + 8 chunks 2595 and 2488.  From 24 on both deal them whole: with 8 + 16 2606 and 2672.
 constexpr int kStagedRows = 20480;
 
 // One product by itself: FP32 in wgrad.hip, or (staged) in gemm_tn.hip's k_gemm_tn
@@ -1064,8 +1065,9 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
   const bool pair = !defer_wg && c->nb && elems <= kPairElems &&
                     elems * H <= pair_limit(H, c->prec, fused, c->recompute) &&
                     (c->recompute || !dh_out_masked);
+  const int chunks = tn_splits(H, d.Fp + 4 * H + 4, 0) + c->nb;
   const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows &&
-                      (tn_splits(H, d.Fp + 4 * H + 4, 0) + c->nb) % 8 != 0;
+                      (chunks % 8 != 0 || chunks > 16);
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);

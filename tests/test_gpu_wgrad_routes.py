@@ -88,9 +88,10 @@ def test_long_chunks_go_layer_by_layer(graphs, launches):
 
 # Batches of 20,480 nodes or more: the products by themselves on the second stream,
 # the De rows left to their column sums.  H = 64 runs k_wgrad, widths that are no
-# multiple of 32, and 32, k_gemm_tn (bucketed and plain chunks); no other route takes such a
-# batch, so against the FP64 oracle (decision replay, the FP32 path's tolerances).
-@pytest.mark.parametrize("H,Fe,maxd", [(64, 1, 4), (32, 1, 4), (48, 1, 4), (80, 2, 4), (48, 0, 4), (48, 1, 20)])
+# multiple of 32, and 32, k_gemm_tn (bucketed and plain chunks; 72 and 24 of them whole to an
+# XCD), except H = 208 with 16 chunks; no other route takes such a batch, so against the FP64 oracle (decision replay, the FP32 path's tolerances).
+@pytest.mark.parametrize("H,Fe,maxd", [(64, 1, 4), (32, 1, 4), (48, 1, 4), (80, 2, 4), (48, 0, 4), (48, 1, 20),
+                                       (48, 1, 7), (208, 1, 7), (208, 1, 15)])
 def test_large_fp32_against_the_oracle(H, Fe, maxd):
     import oracle
     from test_gpu_parity import (ELEM_FP32, TAU_FP32, gpu_decisions, grad_report, make_model, maxrel,
