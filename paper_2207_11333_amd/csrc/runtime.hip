@@ -245,6 +245,9 @@ static size_t wg_part_floats(const WgJob &j, int nb) {
 // however unequal they are and wgrad.hip's by rows: three layers of H = 400 (3 + 5
 // chunks) at 19k nodes 6150 us in it, 5088 in wgrad.hip's; two of H = 208 at 45k with
 // 8 + 8 chunks 2595 and 2488.  From 24 on both deal them whole: with 8 + 16 2606 and 2672.
+// Without buckets the widths between 288 and 384 do at every size: six layers of H = 368
+// at 3.5k nodes 3872 and 4070, of H = 336 at 5.5k 5725 and 5934, of H = 304 4891 and 5036;
+// H = 272 at 4.2k 3189 and 3174, H = 400 at 2.8k 4241 and 4132.
 constexpr int kStagedRows = 20480;
 
 // One product by itself: FP32 in wgrad.hip, or (staged) in gemm_tn.hip's k_gemm_tn
@@ -1066,8 +1069,9 @@ int layer_backward(hgnn_ctx *c, Exec &ex, int l, const float *wl, const float *h
                     elems * H <= pair_limit(H, c->prec, fused, c->recompute) &&
                     (c->recompute || !dh_out_masked);
   const int chunks = tn_splits(H, d.Fp + 4 * H + 4, 0) + c->nb;
-  const bool staged = (H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows &&
-                      (chunks % 8 != 0 || chunks > 16);
+  const bool staged = (!c->nb && H % 32 != 0 && H > 288 && H < 384) ||
+                      ((H % 32 != 0 || (c->nb && H < 64)) && ex.N >= kStagedRows &&
+                       (chunks % 8 != 0 || chunks > 16));
   hipStream_t a = pair ? s : c->aux;
   if (!defer_wg && !pair) {
     e = hipEventRecord(c->fork_ev[0], s);

@@ -86,18 +86,10 @@ def test_long_chunks_go_layer_by_layer(graphs, launches):
     assert np.array_equal(got, _grads(b, p, 1, 512, 0, recompute=1))
 
 
-# Batches of 20,480 nodes or more: the products by themselves on the second stream,
-# the De rows left to their column sums.  H = 64 runs k_wgrad, widths that are no
-# multiple of 32, and 32, k_gemm_tn (bucketed and plain chunks; 72 and 24 of them whole to an
-# XCD), except H = 208 with 16 chunks; no other route takes such a batch, so against the FP64 oracle (decision replay, the FP32 path's tolerances).
-@pytest.mark.parametrize("H,Fe,maxd", [(64, 1, 4), (32, 1, 4), (48, 1, 4), (80, 2, 4), (48, 0, 4), (48, 1, 20),
-                                       (48, 1, 7), (208, 1, 7), (208, 1, 15)])
-def test_large_fp32_against_the_oracle(H, Fe, maxd):
+def _against_the_oracle(b, H, Fe, maxd):
     import oracle
     from test_gpu_parity import (ELEM_FP32, TAU_FP32, gpu_decisions, grad_report, make_model, maxrel,
                                  rel, run_train_step)
-    b = synth.make_batch(17 + Fe, 620, 20, 50, Fe)
-    assert b.num_nodes >= 20480
     L, delta = 2, 1.3
     shape = synth.ModelShape(L, H, 9, Fe)
     params = synth.init_params(shape, 18 + Fe)
@@ -149,3 +141,23 @@ def test_deferred_joins_of_a_large_batch(prec, H):
     print(f"H={H} prec={prec}: gradient rel {r:.2e}")
     assert r <= (1e-5 if prec else 1e-6)
     m.close()
+
+
+# Batches of 20,480 nodes or more: the products by themselves on the second stream,
+# the De rows left to their column sums.  H = 64 runs k_wgrad, widths that are no
+# multiple of 32, and 32, k_gemm_tn (bucketed and plain chunks; 72 and 24 of them whole to an
+# XCD), except H = 208 with 16 chunks; no other route takes such a batch, so against the
+# FP64 oracle (decision replay, the FP32 path's tolerances).
+@pytest.mark.parametrize("H,Fe,maxd", [(64, 1, 4), (32, 1, 4), (48, 1, 4), (80, 2, 4), (48, 0, 4), (48, 1, 20),
+                                       (48, 1, 7), (208, 1, 7), (208, 1, 15)])
+def test_large_fp32_against_the_oracle(H, Fe, maxd):
+    b = synth.make_batch(17 + Fe, 620, 20, 50, Fe)
+    assert b.num_nodes >= 20480
+    _against_the_oracle(b, H, Fe, maxd)
+
+
+# Without buckets the widths between 288 and 384 run k_gemm_tn at every size: one
+# node, one row chunk, several
+@pytest.mark.parametrize("H,graphs,lo,hi", [(304, 1, 1, 1), (336, 2, 5, 9), (368, 60, 20, 40)])
+def test_middle_widths_without_buckets(H, graphs, lo, hi):
+    _against_the_oracle(synth.make_batch(21, graphs, lo, hi, 1), H, 1, 20)
